@@ -3,8 +3,8 @@
 // Every kernel is a single pass over struct-of-arrays FP64 inputs: each lane
 // loads its quote once (coalesced: consecutive lanes read consecutive
 // quotes), keeps the whole solve in registers and stores once.  A thread
-// handles `qpt` quotes spaced one block apart so that every load of a wave
-// stays one contiguous 512-byte segment.  Divergent regions (solver
+// handles `qpt` quotes spaced one block apart (one in the LBR kernels) so
+// that every load of a wave stays one contiguous 512-byte segment.  Divergent regions (solver
 // branches, extra Householder steps, rare evaluator forms) are plain
 // per-lane control flow: the hardware skips a side whose exec mask is empty,
 // so a wave pays only for the branches its own lanes take.  The Halley
@@ -77,9 +77,6 @@ struct GreekOut {
   int any;
 };
 
-// LBR iteration policy: two Householder(3) steps always; a third (and at most
-// a fourth) only while the previous step still moved s by more than 1e-6
-// relative, i.e. only in waves that hold such a lane.
 // Largest workgroup the kernels are compiled for (8 waves).
 constexpr int kMaxBlock = 512;
 // Minimum resident waves per SIMD the solver kernels are register-allocated
@@ -104,9 +101,6 @@ constexpr int kMaxBlock = 512;
 #define FV_CHAINS_WAVES_PER_EU 6
 #endif
 
-constexpr int kLbrMinSteps = 2;
-constexpr int kLbrMaxSteps = 4;
-constexpr double kLbrStepTol = 1e-6;
 constexpr int kHalleySteps = 8;  // the paper's count; the default of fv_set_halley_steps
 constexpr int kMaxHalleySteps = 64;
 constexpr double kBisectTol = 1e-13;
@@ -134,43 +128,68 @@ __global__ __launch_bounds__(kMaxBlock) void k_price(KQuotes q, fv_arg sigma, do
   }
 }
 
+// An index whose value the compiler cannot follow: what is loaded through it
+// is loaded again, not kept in registers from an earlier use.
+__device__ __forceinline__ int64_t opaque(int64_t i) {
+  asm volatile("" : "+v"(i));
+  return i;
+}
+
+// The general solve of quote i, from its inputs in memory: neither they nor
+// what the scaled path derived from them stay in registers across that path
+// for the sake of a rare quote.
+template <int MODEL, bool ARR>
+__device__ __forceinline__ void lbr_general_at(const KQuotes& q, int64_t i, double* sg, uint8_t* st,
+                                               uint32_t* trace = nullptr) {
+  i = opaque(i);
+  fv::lbr_general(MODEL, ld<ARR>(q.price, i), ld<ARR>(q.fs, i), ld<ARR>(q.K, i), ld<ARR>(q.T, i),
+                  ld<ARR>(q.r, i), MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0,
+                  ldflag<ARR>(q, i), sg, st, trace);
+}
+
 // ------------------------------------------------------------- IV: LBR
+// Bound by the vector ALU's issue rate: about 730 vector instructions per
+// quote, every side of the guess a mixed wave takes included (1,157 with the
+// guess and the first step in binary64).  10M wide-wing BSM quotes: 190 us
+// (363 before), 1M BS quotes with the five Greeks: 31.5 us (54).
+// One quote per thread: with a loop over several the compiler keeps the
+// polynomials' constants in registers across the whole solve, 110 VGPRs in
+// place of 55, and the same book takes 220 us.
 template <int MODEL, bool GREEKS, bool ARR>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(KQuotes q, double* __restrict__ sig_out, uint8_t* __restrict__ st_out,
-                         GreekOut g, int qpt) {
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    if (i >= q.n) return;
-    const double P = ld<ARR>(q.price, i), fs = ld<ARR>(q.fs, i), K = ld<ARR>(q.K, i), T = ld<ARR>(q.T, i),
-                 r = ld<ARR>(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0;
-    const int th = ldflag<ARR>(q, i);
-    const Reduced rd = fv::reduce_quote(MODEL, P, fs, K, T, r, qy, th);
-    uint8_t st = rd.status;
-    double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
+                         GreekOut g) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= q.n) return;
+  const double P = ld<ARR>(q.price, i), fs = ld<ARR>(q.fs, i), K = ld<ARR>(q.K, i), T = ld<ARR>(q.T, i),
+               r = ld<ARR>(q.r, i);
+  const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0;
+  const int th = ldflag<ARR>(q, i);
+  const fv::ScaledQuote sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, th);
+  uint8_t st = sq.status;
+  double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
+  bool general = sq.general;
+  if (st == fv::kQOk && !general) {
+    double s;
+    general = !fv::lbr_solve_scaled(sq.x, sq.bh, sq.ch, &s);
+    sg = s * sq.isqrtT;
+  }
+  if (__builtin_expect(general, 0)) lbr_general_at<MODEL, ARR>(q, i, &sg, &st);
+  sig_out[i] = sg;
+  if (st_out) st_out[i] = st;
+  if (GREEKS) {
+    Greeks gr;
     if (st == fv::kQOk) {
-      const LbrResult res = fv::lbr_solve(rd.x, rd.beta, rd.bmax, rd.lnb, kLbrMinSteps, kLbrMaxSteps, kLbrStepTol);
-      sg = res.s * rd.isqrtT;
-      if (!res.converged) st = fv::kQNotConverged;
+      gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, sq.F, sq.D, P);
+    } else {
+      const double nan = __builtin_nan("");
+      gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
     }
-    sig_out[i] = sg;
-    if (st_out) st_out[i] = st;
-    if (GREEKS) {
-      Greeks gr;
-      if (st == fv::kQOk) {
-        gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, rd.F, rd.D, P);
-      } else {
-        const double nan = __builtin_nan("");
-        gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
-      }
-      if (g.p[0]) g.p[0][i] = gr.delta;
-      if (g.p[1]) g.p[1][i] = gr.gamma;
-      if (g.p[2]) g.p[2][i] = gr.vega;
-      if (g.p[3]) g.p[3][i] = gr.theta;
-      if (g.p[4]) g.p[4][i] = gr.rho;
-    }
+    if (g.p[0]) g.p[0][i] = gr.delta;
+    if (g.p[1]) g.p[1][i] = gr.gamma;
+    if (g.p[2]) g.p[2][i] = gr.vega;
+    if (g.p[3]) g.p[3][i] = gr.theta;
+    if (g.p[4]) g.p[4][i] = gr.rho;
   }
 }
 
@@ -186,11 +205,18 @@ __global__ __launch_bounds__(kMaxBlock) void k_lbr_trace(KQuotes q, uint32_t* __
     const double P = ld(q.price, i), fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i),
                  r = ld(q.r, i);
     const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    const Reduced rd = fv::reduce_quote(MODEL, P, fs, K, T, r, qy, ldflag(q, i));
+    const fv::ScaledQuote sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, ldflag(q, i));
     uint32_t code = 0xFFFFFFFFu;  // not solved (status != OK)
-    if (rd.status == fv::kQOk) {
-      code = 0;
-      fv::lbr_solve(rd.x, rd.beta, rd.bmax, rd.lnb, kLbrMinSteps, kLbrMaxSteps, kLbrStepTol, &code);
+    bool general = sq.general;
+    if (sq.status == fv::kQOk && !general) {
+      double s;
+      general = !fv::lbr_solve_scaled(sq.x, sq.bh, sq.ch, &s, &code);
+    }
+    if (general) {
+      double sg;
+      uint8_t st;
+      code = 0xFFFFFFFFu;
+      lbr_general_at<MODEL, false>(q, i, &sg, &st, &code);
     }
     out[i] = code;
   }
@@ -569,16 +595,28 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
       const double F = c.F[cc], r = c.r[cc], T = c.T[m];
       const double P = c.price[i], K = c.K[i];
       const int th = c.flag[i];
-      const Reduced rd = fv::reduce_quote(fv::kBlack76, P, F, K, T, r, 0.0, th);
-      uint8_t st = rd.status;
-      double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
-      if (st == fv::kQOk) {
-        if (!kHalley) {
-          const LbrResult res = fv::lbr_solve(rd.x, rd.beta, rd.bmax, rd.lnb, kLbrMinSteps,
-                                              kLbrMaxSteps, kLbrStepTol);
-          sg = res.s * rd.isqrtT;
-          if (!res.converged) st = fv::kQNotConverged;
-        } else {
+      uint8_t st;
+      double sg;
+      if (!kHalley) {
+        const fv::ScaledQuote sq = fv::scaled_quote(fv::kBlack76, P, F, K, T, r, 0.0, th);
+        st = sq.status;
+        sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
+        bool general = sq.general;
+        if (st == fv::kQOk && !general) {
+          double s;
+          general = !fv::lbr_solve_scaled(sq.x, sq.bh, sq.ch, &s);
+          sg = s * sq.isqrtT;
+        }
+        if (__builtin_expect(general, 0)) {
+          const int64_t io = opaque(i), co = opaque(cc), mo = opaque(m);
+          fv::lbr_general(fv::kBlack76, c.price[io], c.F[co], c.K[io], c.T[mo], c.r[co], 0.0,
+                          c.flag[io], &sg, &st);
+        }
+      } else {
+        const Reduced rd = fv::reduce_quote(fv::kBlack76, P, F, K, T, r, 0.0, th);
+        st = rd.status;
+        sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
+        if (st == fv::kQOk) {
           hs = fv::halley_solve(rd.x, rd.beta, rd.bmax, rd.lnb, c.hsteps);
           sg = hs.s * rd.isqrtT;
           fail = !hs.converged;
@@ -1008,11 +1046,11 @@ int fv_implied_vol(int model, int solver, const fv_quotes* q, double* sigma_out,
   const bool arr = q->price.ptr && q->fs.ptr && q->K.ptr && q->T.ptr && q->r.ptr && q->flag &&
                    (model != FV_MODEL_BSM || q->q.ptr);
   if (solver == FV_SOLVER_LBR) {
-    const LaunchShape sh = shape_for(FV_KERNEL_IV_LBR, model, q->n);
+    const LaunchShape sh{shape_for(FV_KERNEL_IV_LBR, model, q->n).block, 1};
     const dim3 grid = grid_for(q->n, sh), block(sh.block);
 #define FV_LBR(M, G)                                                                   \
-  (arr ? k_iv_lbr<M, G, true><<<grid, block, 0, s>>>(k, sigma_out, status_out, g, sh.qpt) \
-       : k_iv_lbr<M, G, false><<<grid, block, 0, s>>>(k, sigma_out, status_out, g, sh.qpt))
+  (arr ? k_iv_lbr<M, G, true><<<grid, block, 0, s>>>(k, sigma_out, status_out, g) \
+       : k_iv_lbr<M, G, false><<<grid, block, 0, s>>>(k, sigma_out, status_out, g))
     switch (model * 2 + (g.any ? 1 : 0)) {
       case 0: FV_LBR(0, false); break;
       case 1: FV_LBR(0, true); break;

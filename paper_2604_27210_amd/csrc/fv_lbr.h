@@ -17,6 +17,7 @@
 #pragma once
 
 #include "fv_math.h"
+#include "fv_start.h"
 
 namespace fv {
 
@@ -84,6 +85,13 @@ __host__ __device__ inline double rational_cubic_fit(double x, double xl, double
 }
 
 // ------------------------------------------------------- LBR
+// LBR iteration policy: two Householder(3) steps always; a third (and at most
+// a fourth) only while the previous step still moved s by more than 1e-6
+// relative, i.e. only in waves that hold such a lane.
+constexpr int kLbrMinSteps = 2;
+constexpr int kLbrMaxSteps = 4;
+constexpr double kLbrStepTol = 1e-6;
+
 enum Objective : int { kObjLower = 0, kObjMiddle = 1, kObjUpper = 2 };
 
 struct LbrResult {
@@ -320,6 +328,131 @@ __host__ __device__ __attribute__((always_inline)) inline LbrResult lbr_solve(
   return res;
 }
 
+// ------------------------------------------------------- scaled solves
+// The solvers' main path.  The guess and the first step (Halley: the first
+// two) run in binary32 (fv_start.h); the step that decides the root runs in
+// binary64 on the direct residual, scaled by b_max:
+//   nu = (beta - b)/b' = bh W - b/b'                with the difference form,
+//      = (b_max - b)/b' - (1 - bh) W                with the complement form,
+//   W = b_max/b' = sqrt(2 pi) e^{g^2/2},  g = h + t,
+// which takes one exponential, no logarithm and no division: near the root
+// every objective of the method gives the same step, and the step is small
+// enough (1e-7 s from binary32 rounding, 4e-6 s at most over the wide
+// workload) to leave its higher-order correction to binary32 as well.
+
+// b/b' (difference form) or (b_max - b)/b' (complement form) at s, with the
+// parts the step needs.  The reciprocal of the product R1 R2 is taken once:
+// for |x| <= 128 and 1e-24 < s < 1e3, which hold here, it stays in range.
+struct ScaledEval {
+  double rho, g, h, is;
+  bool comp;
+};
+
+__host__ __device__ __attribute__((always_inline)) inline ScaledEval scaled_eval(double x, double s) {
+  ScaledEval e;
+  e.is = rcp(s);
+  e.h = x * e.is;
+  const double t = 0.5 * s;
+  e.g = e.h + t;
+  const double q1 = -e.g * kInvSqrt2, q2 = (t - e.h) * kInvSqrt2;
+  e.comp = q1 < -coef::kErfcxZ0;
+  const double z1 = e.comp ? -q1 : q1;
+  constexpr double kB = coef::kErfcxB, k2BZ = 2.0 * (kB - coef::kErfcxZ0);
+  const double a1 = z1 + kB, a2 = q2 + kB;
+  const double R12 = rcp(a1 * a2);
+  const double R1 = R12 * a2, R2 = R12 * a1;
+  const double y1 = fma(-k2BZ, R1, 1.0), y2 = fma(-k2BZ, R2, 1.0);
+  double B = coef::kErfcx[kErfcxDeg], D = 0.0;
+#pragma unroll
+  for (int i = kErfcxDeg - 1; i >= 0; --i) {
+    D = fma(D, y1, B);
+    B = fma(B, y2, coef::kErfcx[i]);
+  }
+  if (!e.comp) {
+    e.rho = kSqrtPi * t * R12 * fma(-k2BZ * R1, D, B);
+  } else {
+    const double A = fma(y1 - y2, D, B);
+    e.rho = kSqrtPiOver2 * fma(A, R1, B * R2);
+  }
+  return e;
+}
+
+// One step of order 3 (Halley) or 4 (Householder(3)) from s; `w` receives
+// the step's relative size times 1 + |s b''/b'|, the measure of the error
+// it leaves.
+template <int ORDER>
+__host__ __device__ __attribute__((always_inline)) inline double scaled_step(double x, double bh,
+                                                                             double ch, double s,
+                                                                             float* w, bool* comp) {
+  const ScaledEval e = scaled_eval(x, s);
+  const double W = kSqrt2Pi * fexp(0.5 * e.g * e.g);
+  const double tgt = e.comp ? -ch : bh;
+  const double nu = fma(tgt, W, e.comp ? e.rho : -e.rho);
+  const float n = (float)(nu * e.is), hf = (float)e.h, sf = (float)s;
+  const float h2 = hf * hf, s2 = 0.25f * sf * sf;
+  const float H = h2 - s2;  // s b''/b'
+  float c;                  // step = nu (1 + c)
+  if (ORDER == 4) {
+    const float k = fmaf(H, H, -3.0f * h2 - s2) * n * (1.0f / 6.0f);  // s^2 b'''/b' times n/6
+    c = -n * fmaf(0.5f, H, k) * s32::rcp(fmaf(n, H + k, 1.0f));
+  } else {
+    const float k = 0.5f * H * n;
+    c = -k * s32::rcp(1.0f + k);
+  }
+  *w = fabsf(n) * (1.0f + fabsf(H));
+  *comp = e.comp;
+  return fma(nu, (double)c, nu);
+}
+
+// Quotes the scaled path takes: x, and beta/b_max away from 0 and 1 (the
+// ranges the binary32 start holds, fv_start.h).  1 - beta/b_max is taken
+// apart from beta/b_max: near the bound it is what decides the root, and a
+// rounding of beta/b_max would be amplified in the difference.
+__host__ __device__ inline bool scaled_domain(double x, double bh, double ch) {
+  return x >= -128.0 && (x <= -0x1p-60 || x == 0.0) && bh > 0x1p-960 && ch > 0x1p-40;
+}
+
+__host__ __device__ inline s32::Target scaled_target(double x, double bh, double ch) {
+  s32::Target q;
+  q.ax = -(float)x;
+  q.bh = (float)bh;
+  q.ch = (float)ch;
+  q.lbh = s32::log_of_double(bh);
+  return q;
+}
+
+// The binary64 step leaves about c w^3 |ds| with c below 1/24: 1e-16 s at
+// this w.  One quote in 1e5 of the wide workload is above it after the
+// binary32 step and takes one more.
+constexpr float kScaledStepTol = 2e-4f;
+constexpr int kScaledMaxSteps = 4;
+
+// LBR: guess and first Householder(3) step in binary32, then binary64 steps
+// until one settles.  Returns false (the caller takes lbr_solve) where none
+// does within the limit.  `trace` as lbr_solve's.
+__host__ __device__ __attribute__((always_inline)) inline bool lbr_solve_scaled(
+    double x, double bh, double ch, double* root, uint32_t* trace = nullptr) {
+  const s32::Target q = scaled_target(x, bh, ch);
+  const s32::Guess g = s32::initial_guess(q);
+  const s32::Eval e = s32::eval<false>(q.ax, g.s);
+  double s = (double)fmaf(g.s, s32::householder3(q, g.region, e, g.s), g.s);
+  // the first binary64 step apart from the loop, which few waves enter: its
+  // constants are then set up where they are used
+  float w;
+  bool comp;
+  s += scaled_step<4>(x, bh, ch, s, &w, &comp);
+  uint32_t forms = ((uint32_t)g.comp_o << 6) | ((uint32_t)e.comp << 8) | ((uint32_t)comp << 10);
+  int it = 2;
+  while (!(w <= kScaledStepTol) && it < kScaledMaxSteps) {
+    s += scaled_step<4>(x, bh, ch, s, &w, &comp);
+    forms |= (uint32_t)comp << (8 + 2 * it);
+    ++it;
+  }
+  if (trace) *trace = (uint32_t)g.region | ((uint32_t)(it - 2) << 2) | forms;
+  *root = s;
+  return w <= kScaledStepTol && s > 0.0;
+}
+
 // ------------------------------------------------------- Halley path
 struct HalleyState {
   double s, lo, hi;
@@ -460,6 +593,36 @@ __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_sol
   st.steps = k;
   st.converged = stop && fabs(res) <= (logres ? 1e-2 : 1e-2 * beta) && s > 0.0 &&
                  __builtin_isfinite(s);
+  return st;
+}
+
+// The Halley path's main form: guess and the first two steps in binary32
+// (one, when the limit leaves room for a single binary64 step only), then
+// binary64 steps to the same stop as halley_solve.  The binary32 steps work
+// on ln b - ln beta (in the complement form on the direct residual), which
+// converges from the guess at any depth of the wing.
+__host__ __device__ __attribute__((always_inline)) inline HalleyState halley_solve_scaled(
+    double x, double bh, double ch, int steps) {
+  const s32::Target q = scaled_target(x, bh, ch);
+  float s0 = s32::initial_guess(q).s;
+  HalleyState st;
+  st.lo = 0.0;
+  st.hi = 1e300;
+  st.steps = steps >= 3 ? 2 : 1;
+  s0 = fmaf(s0, s32::halley(q, s32::eval<false>(q.ax, s0), s0), s0);
+  if (steps >= 3) s0 = fmaf(s0, s32::halley(q, s32::eval<false>(q.ax, s0), s0), s0);
+  double s = (double)s0;
+  bool stop = false;
+  while (st.steps < steps && !stop) {
+    float w;
+    bool comp;
+    const double ds = scaled_step<3>(x, bh, ch, s, &w, &comp);
+    s += ds;
+    ++st.steps;
+    stop = fabs(ds) <= kHalleyStepTol * s && w <= 1e-2f;
+  }
+  st.s = s;
+  st.converged = stop && s > 0.0;
   return st;
 }
 

@@ -85,10 +85,21 @@ __host__ __device__ inline double fexp_carry(double r, double q, double T) {
   return fma(E, e, E);
 }
 
+// a - b with both operands rounded first (never contracted into an fma)
+__host__ __device__ inline double minus(double a, double b) {
+#pragma clang fp contract(off)
+  return a - b;
+}
+
+// F / fs
+__host__ __device__ inline double growth_of(int model, double T, double r, double q) {
+  if (model == kBlack76) return 1.0;
+  return model == kBlackScholesMerton ? fexp_carry(r, q, T) : fexp_prod(r, T);
+}
+
 __host__ __device__ inline double forward_of(int model, double fs, double T, double r,
                                              double q) {
-  if (model == kBlack76) return fs;
-  return fs * (model == kBlackScholesMerton ? fexp_carry(r, q, T) : fexp_prod(r, T));
+  return model == kBlack76 ? fs : fs * growth_of(model, T, r, q);
 }
 
 // ln(F/K) from the ratio while F/K is a normal number, else from the two
@@ -146,6 +157,75 @@ __host__ __device__ inline Reduced reduce_quote(int model, double price, double 
   if (!(ok_in && ok_f)) st = kQInvalid;
   o.status = st;
   return o;
+}
+
+// What the scaled solvers (fv_lbr.h) need of a quote.  The status is decided
+// by the very expressions of reduce_quote; `general` marks a quote that has
+// an implied volatility, or may have one, but lies outside the scaled
+// solvers' domain: it goes through reduce_quote and the general solver.
+// Against reduce_quote this drops ln beta (a logarithm) and 1/sqrt(F K)
+// (two reciprocal square roots): bh = beta/b_max = (Pu - I)/min(F, K).
+struct ScaledQuote {
+  double F, D;
+  double isqrtT;
+  double x, bh, ch;  // ln(F/K) <= 0, beta/b_max and 1 - beta/b_max
+  uint8_t status;
+  bool general;
+};
+
+__host__ __device__ inline ScaledQuote scaled_quote(int model, double price, double fs, double K,
+                                                    double T, double r, double q, int theta) {
+  ScaledQuote o;
+  const bool ok_in = finite_d(price) && finite_d(fs) && finite_d(K) && finite_d(T) &&
+                     finite_d(r) && finite_d(q) && fs >= kDblMin && K >= kDblMin && T > 0.0 &&
+                     (theta == 1 || theta == -1);
+  const double gr = growth_of(model, T, r, q);
+  const double F = fs * gr;
+  const bool ok_f = F >= kDblMin && finite_d(F);
+  const double cap = fexp_prod(r, T);  // 1/D
+  const double Pu = price * cap;
+  const double dth = (double)theta;
+  const double I = fmax(dth * minus(F, K), 0.0);
+  const double M = theta > 0 ? F : K;
+  o.F = F;
+  o.D = fexp_prod(-r, T);
+  o.isqrtT = rsqrt_pos(T);
+  const double m = fmin(F, K);
+  const double fk = F * rcp(K);
+  o.x = -fabs(flog(fk));
+  // the time value from the rounded forward and the unrounded price: in the
+  // money it is a small difference of large numbers, and what its operands'
+  // roundings leave of it is the quote's implied volatility
+  const double tv = fma(price, cap, -I), im = rcp(m);
+  o.bh = tv * im;
+  o.ch = (m - tv) * im;
+  uint8_t st = kQOk;
+  if (Pu >= M) st = kQAboveMax;
+  if (Pu == I) st = kQAtIntrinsic;
+  if (Pu < I) st = kQBelowIntrinsic;
+  if (!(ok_in && ok_f)) st = kQInvalid;
+  o.status = st;
+  // F and K away from the ends of the range, where rcp would lose bits
+  o.general = st == kQOk && !(scaled_domain(o.x, o.bh, o.ch) && m >= 0x1p-1000 &&
+                              fmax(F, K) <= 0x1p+1000);
+  return o;
+}
+
+// The general implied volatility of one quote: reduce_quote and lbr_solve.
+__host__ __device__ __attribute__((always_inline)) inline void lbr_general(
+    int model, double price, double fs, double K, double T, double r, double q, int theta,
+    double* sigma, uint8_t* status, uint32_t* trace = nullptr) {
+  const Reduced rd = reduce_quote(model, price, fs, K, T, r, q, theta);
+  uint8_t st = rd.status;
+  double sg = st == kQAtIntrinsic ? 0.0 : __builtin_nan("");
+  if (st == kQOk) {
+    const LbrResult res = lbr_solve(rd.x, rd.beta, rd.bmax, rd.lnb, kLbrMinSteps, kLbrMaxSteps,
+                                    kLbrStepTol, trace);
+    sg = res.s * rd.isqrtT;
+    if (!res.converged) st = kQNotConverged;
+  }
+  *sigma = sg;
+  *status = st;
 }
 
 // Accurate Phi(a) for either sign of a.
