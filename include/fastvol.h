@@ -300,10 +300,11 @@ int fv_halley_trace(int model, const fv_quotes *q, uint32_t *steps_out, void *st
  * Every Halley launch (fv_implied_vol with FV_SOLVER_HALLEY, the ragged
  * chains, fv_implied_vol_f32, fv_halley_trace) reads it when it is
  * enqueued; default 8.  In binary64 the iteration starts from the LBR
- * path's initial guess and its first step is at guess precision, so a quote
- * never stops before its second step: a limit of 1 sends every solvable
- * quote to the fallback, 2 the quotes that need a third step (binary32
- * starts from the Brenner-Subrahmanyam form and may stop after any step).
+ * path's initial guess; its first step (with a limit of 3 or more the first
+ * two) is in binary32 and only a later one may be the last: a limit of 1
+ * sends every solvable quote to the fallback, 2 the quotes that need a third
+ * step (binary32 starts from the Brenner-Subrahmanyam form and may stop
+ * after any step).
  * Results stay within the Halley tolerance at any
  * limit (the fallback bisects to 1e-13 relative); a lower limit only moves
  * work to the slower bisection, which makes it a way to exercise that path.
@@ -319,8 +320,9 @@ int fv_get_halley_steps(void);
  * per quote, 16 for binary32; the ragged-chain kernel, which takes two
  * 64-quote slices per wave and ignores quotes_per_thread, 64 bytes per
  * thread) must fit in 64 KiB of LDS
- * (FV_E_INVALID_ARG otherwise; the shape in force is kept).  The LBR kernels
- * take one quote per thread at any quotes_per_thread.
+ * (FV_E_INVALID_ARG otherwise; the shape in force is kept).  The
+ * binary64 LBR and Halley kernels take one quote per thread at any
+ * quotes_per_thread.
  * fv_get_launch reads the configured shape.  The shape applies as set to
  * batches large enough to fill the device; a batch that would give fewer
  * than 8 waves per SIMD (32 per compute unit) runs with fewer quotes per

@@ -76,6 +76,13 @@ struct GreekOut {
   double* p[5];
   int any;
 };
+__device__ __forceinline__ void store_greeks(const GreekOut& g, int64_t i, const Greeks& gr) {
+  if (g.p[0]) g.p[0][i] = gr.delta;
+  if (g.p[1]) g.p[1][i] = gr.gamma;
+  if (g.p[2]) g.p[2][i] = gr.vega;
+  if (g.p[3]) g.p[3][i] = gr.theta;
+  if (g.p[4]) g.p[4][i] = gr.rho;
+}
 
 // Largest workgroup the kernels are compiled for (8 waves).
 constexpr int kMaxBlock = 512;
@@ -128,9 +135,10 @@ __global__ __launch_bounds__(kMaxBlock) void k_price(KQuotes q, fv_arg sigma, do
   }
 }
 
-// An index whose value the compiler cannot follow: what is loaded through it
-// is loaded again, not kept in registers from an earlier use.
-__device__ __forceinline__ int64_t opaque(int64_t i) {
+// A value the compiler cannot follow: what is loaded or computed from it is
+// loaded or computed again, not kept in registers from an earlier use.
+template <class V>
+__device__ __forceinline__ V opaque(V i) {
   asm volatile("" : "+v"(i));
   return i;
 }
@@ -185,11 +193,7 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(KQuotes
       const double nan = __builtin_nan("");
       gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
     }
-    if (g.p[0]) g.p[0][i] = gr.delta;
-    if (g.p[1]) g.p[1][i] = gr.gamma;
-    if (g.p[2]) g.p[2][i] = gr.vega;
-    if (g.p[3]) g.p[3][i] = gr.theta;
-    if (g.p[4]) g.p[4][i] = gr.rho;
+    store_greeks(g, i, gr);
   }
 }
 
@@ -222,6 +226,27 @@ __global__ __launch_bounds__(kMaxBlock) void k_lbr_trace(KQuotes q, uint32_t* __
   }
 }
 
+// The Halley iteration of one quote: the scaled solve, or the general one for
+// a quote outside its domain.  Returns the status; hs is set where it is OK,
+// sq always.
+template <int MODEL>
+__device__ __forceinline__ uint8_t halley_quote(double P, double fs, double K, double T, double r,
+                                                double qy, int th, int steps,
+                                                fv::HalleyState* hs, fv::ScaledQuote* sq) {
+  *sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, th);
+  uint8_t st = sq->status;
+  if (st != fv::kQOk) return st;
+  if (__builtin_expect(sq->general, 0)) {
+    const Reduced rd = fv::reduce_quote(MODEL, opaque(P), opaque(fs), opaque(K), opaque(T),
+                                        opaque(r), opaque(qy), th);
+    st = rd.status;
+    if (st == fv::kQOk) *hs = fv::halley_solve(rd.x, rd.beta, rd.bmax, rd.lnb, steps);
+  } else {
+    *hs = fv::halley_solve_scaled(sq->x, sq->bh, sq->ch, steps);
+  }
+  return st;
+}
+
 // Diagnostic twin of k_iv_halley: the number of Halley steps each quote
 // takes, with bit 8 set when it fails the convergence check (and would go
 // through the bisection fallback).
@@ -235,12 +260,11 @@ __global__ __launch_bounds__(kMaxBlock) void k_halley_trace(KQuotes q, uint32_t*
     const double P = ld(q.price, i), fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i),
                  r = ld(q.r, i);
     const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    const Reduced rd = fv::reduce_quote(MODEL, P, fs, K, T, r, qy, ldflag(q, i));
+    fv::HalleyState hs;
+    fv::ScaledQuote sq;
+    const uint8_t st = halley_quote<MODEL>(P, fs, K, T, r, qy, ldflag(q, i), q.hsteps, &hs, &sq);
     uint32_t code = 0xFFFFFFFFu;  // not solved (status != OK)
-    if (rd.status == fv::kQOk) {
-      const fv::HalleyState hs = fv::halley_solve(rd.x, rd.beta, rd.bmax, rd.lnb, q.hsteps);
-      code = (uint32_t)hs.steps | (hs.converged ? 0u : 0x100u);
-    }
+    if (st == fv::kQOk) code = (uint32_t)hs.steps | (hs.converged ? 0u : 0x100u);
     out[i] = code;
   }
 }
@@ -257,94 +281,84 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return lane ? (~0ull >> (64 - lane)) : 0ull;
 }
 
+// Bound by the vector ALU like k_iv_lbr, on the same guess; its first two
+// steps are in binary32 and nearly every quote takes one binary64 step after
+// them (two full steps after one at guess precision before, with both in
+// binary64).  3M wide-wing BSM quotes: 62 us (133 before).  One quote per
+// thread, as k_iv_lbr; the queue holds one entry per thread.
 template <int MODEL, bool GREEKS, bool ARR>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(KQuotes q, double* __restrict__ sig_out,
-                            uint8_t* __restrict__ st_out, GreekOut g, int qpt) {
+                            uint8_t* __restrict__ st_out, GreekOut g) {
   extern __shared__ unsigned char smem_raw[];
   Pending* queue = reinterpret_cast<Pending*>(smem_raw);
   __shared__ int qcount;
   if (threadIdx.x == 0) qcount = 0;
   __syncthreads();
 
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    bool fail = false;
-    fv::HalleyState hs;
-    hs.lo = 0.0;
-    hs.hi = 0.0;
-    if (i < q.n) {
-      const double P = ld<ARR>(q.price, i), fs = ld<ARR>(q.fs, i), K = ld<ARR>(q.K, i), T = ld<ARR>(q.T, i),
-                   r = ld<ARR>(q.r, i);
-      const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0;
-      const int th = ldflag<ARR>(q, i);
-      const Reduced rd = fv::reduce_quote(MODEL, P, fs, K, T, r, qy, th);
-      uint8_t st = rd.status;
-      double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
-      if (st == fv::kQOk) {
-        hs = fv::halley_solve(rd.x, rd.beta, rd.bmax, rd.lnb, q.hsteps);
-        sg = hs.s * rd.isqrtT;
-        fail = !hs.converged;
-      }
-      if (!fail) {
-        sig_out[i] = sg;
-        if (st_out) st_out[i] = st;
-        if (GREEKS) {
-          Greeks gr;
-          if (st == fv::kQOk) {
-            gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, rd.F, rd.D, P);
-          } else {
-            const double nan = __builtin_nan("");
-            gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
-          }
-          if (g.p[0]) g.p[0][i] = gr.delta;
-          if (g.p[1]) g.p[1][i] = gr.gamma;
-          if (g.p[2]) g.p[2][i] = gr.vega;
-          if (g.p[3]) g.p[3][i] = gr.theta;
-          if (g.p[4]) g.p[4][i] = gr.rho;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  bool fail = false;
+  fv::HalleyState hs;
+  hs.lo = 0.0;
+  hs.hi = 0.0;
+  if (i < q.n) {
+    const double P = ld<ARR>(q.price, i), fs = ld<ARR>(q.fs, i), K = ld<ARR>(q.K, i), T = ld<ARR>(q.T, i),
+                 r = ld<ARR>(q.r, i);
+    const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0;
+    const int th = ldflag<ARR>(q, i);
+    fv::ScaledQuote sq;
+    const uint8_t st = halley_quote<MODEL>(P, fs, K, T, r, qy, th, q.hsteps, &hs, &sq);
+    double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
+    if (st == fv::kQOk) {
+      sg = hs.s * sq.isqrtT;
+      fail = !hs.converged;
+    }
+    if (!fail) {
+      sig_out[i] = sg;
+      if (st_out) st_out[i] = st;
+      if (GREEKS) {
+        Greeks gr;
+        if (st == fv::kQOk) {
+          gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, sq.F, sq.D, P);
+        } else {
+          const double nan = __builtin_nan("");
+          gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
         }
+        store_greeks(g, i, gr);
       }
     }
-    // wave-level compaction of the failing lanes into the LDS queue
-    const uint64_t mask = __ballot(fail);
-    if (mask) {
-      int wbase = 0;
-      const int cnt = __popcll(mask);
-      const unsigned first = __ffsll((unsigned long long)mask) - 1;
-      if (__lane_id() == first) wbase = atomicAdd(&qcount, cnt);
-      wbase = __shfl(wbase, first);
-      if (fail) {
-        const int slot = wbase + __popcll(mask & lanemask_lt());
-        queue[slot].i = i;
-        queue[slot].lo = hs.lo;
-        queue[slot].hi = hs.hi;
-      }
+  }
+  // wave-level compaction of the failing lanes into the LDS queue
+  const uint64_t mask = __ballot(fail);
+  if (mask) {
+    int wbase = 0;
+    const int cnt = __popcll(mask);
+    const unsigned first = __ffsll((unsigned long long)mask) - 1;
+    if (__lane_id() == first) wbase = atomicAdd(&qcount, cnt);
+    wbase = __shfl(wbase, first);
+    if (fail) {
+      const int slot = wbase + __popcll(mask & lanemask_lt());
+      queue[slot].i = i;
+      queue[slot].lo = hs.lo;
+      queue[slot].hi = hs.hi;
     }
   }
   __syncthreads();
   // bisection fallback over the packed queue: every lane of a wave works
   const int m = qcount;
   for (int j = threadIdx.x; j < m; j += blockDim.x) {
-    const int64_t i = queue[j].i;
-    const double P = ld<ARR>(q.price, i), fs = ld<ARR>(q.fs, i), K = ld<ARR>(q.K, i), T = ld<ARR>(q.T, i),
-                 r = ld<ARR>(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0;
-    const int th = ldflag<ARR>(q, i);
+    const int64_t iq = queue[j].i;
+    const double P = ld<ARR>(q.price, iq), fs = ld<ARR>(q.fs, iq), K = ld<ARR>(q.K, iq), T = ld<ARR>(q.T, iq),
+                 r = ld<ARR>(q.r, iq);
+    const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, iq) : 0.0;
+    const int th = ldflag<ARR>(q, iq);
     const Reduced rd = fv::reduce_quote(MODEL, P, fs, K, T, r, qy, th);
     const double s =
         fv::bisection_solve(rd.x, rd.beta, rd.bmax, rd.lnb, queue[j].lo, queue[j].hi, kBisectTol);
     const double sg = s * rd.isqrtT;
-    sig_out[i] = sg;
-    if (st_out) st_out[i] = fv::kQOk;
-    if (GREEKS) {
-      const Greeks gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, rd.F, rd.D, P);
-      if (g.p[0]) g.p[0][i] = gr.delta;
-      if (g.p[1]) g.p[1][i] = gr.gamma;
-      if (g.p[2]) g.p[2][i] = gr.vega;
-      if (g.p[3]) g.p[3][i] = gr.theta;
-      if (g.p[4]) g.p[4][i] = gr.rho;
-    }
+    sig_out[iq] = sg;
+    if (st_out) st_out[iq] = fv::kQOk;
+    if (GREEKS) store_greeks(g, iq, fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, rd.F, rd.D, P));
   }
 }
 
@@ -454,11 +468,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_greeks(KQuotes q, fv_arg sigma, G
       const double P = fv::price_at(F, K, D, sg, fv::sqrt_pos(T), th);
       gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, F, D, P);
     }
-    if (g.p[0]) g.p[0][i] = gr.delta;
-    if (g.p[1]) g.p[1][i] = gr.gamma;
-    if (g.p[2]) g.p[2][i] = gr.vega;
-    if (g.p[3]) g.p[3][i] = gr.theta;
-    if (g.p[4]) g.p[4][i] = gr.rho;
+    store_greeks(g, i, gr);
   }
 }
 
@@ -613,12 +623,11 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
                           c.flag[io], &sg, &st);
         }
       } else {
-        const Reduced rd = fv::reduce_quote(fv::kBlack76, P, F, K, T, r, 0.0, th);
-        st = rd.status;
+        fv::ScaledQuote sq;
+        st = halley_quote<fv::kBlack76>(P, F, K, T, r, 0.0, th, c.hsteps, &hs, &sq);
         sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
         if (st == fv::kQOk) {
-          hs = fv::halley_solve(rd.x, rd.beta, rd.bmax, rd.lnb, c.hsteps);
-          sg = hs.s * rd.isqrtT;
+          sg = hs.s * sq.isqrtT;
           fail = !hs.converged;
         }
       }
@@ -1062,12 +1071,12 @@ int fv_implied_vol(int model, int solver, const fv_quotes* q, double* sigma_out,
 #undef FV_LBR
     return launched("fv_implied_vol(LBR)");
   }
-  const LaunchShape sh = shape_for(FV_KERNEL_IV_HALLEY, model, q->n);
+  const LaunchShape sh{shape_for(FV_KERNEL_IV_HALLEY, model, q->n).block, 1};
   const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  const size_t lds = sizeof(Pending) * (size_t)sh.block * sh.qpt;
+  const size_t lds = sizeof(Pending) * (size_t)sh.block;
 #define FV_HAL(M, G)                                                                    \
-  (arr ? k_iv_halley<M, G, true><<<grid, block, lds, s>>>(k, sigma_out, status_out, g, sh.qpt) \
-       : k_iv_halley<M, G, false><<<grid, block, lds, s>>>(k, sigma_out, status_out, g, sh.qpt))
+  (arr ? k_iv_halley<M, G, true><<<grid, block, lds, s>>>(k, sigma_out, status_out, g) \
+       : k_iv_halley<M, G, false><<<grid, block, lds, s>>>(k, sigma_out, status_out, g))
   switch (model * 2 + (g.any ? 1 : 0)) {
     case 0: FV_HAL(0, false); break;
     case 1: FV_HAL(0, true); break;

@@ -596,6 +596,10 @@ __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_sol
   return st;
 }
 
+// Largest w of a Halley step that may be the last: below it the direct
+// residual was within about 1e-2 of beta, halley_solve's own check.
+constexpr float kScaledHalleyTol = 1e-2f;
+
 // The Halley path's main form: guess and the first two steps in binary32
 // (one, when the limit leaves room for a single binary64 step only), then
 // binary64 steps to the same stop as halley_solve.  The binary32 steps work
@@ -613,13 +617,19 @@ __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_sol
   if (steps >= 3) s0 = fmaf(s0, s32::halley(q, s32::eval<false>(q.ax, s0), s0), s0);
   double s = (double)s0;
   bool stop = false;
-  while (st.steps < steps && !stop) {
-    float w;
-    bool comp;
+  float w;
+  bool comp;
+  if (st.steps < steps) {  // apart from the loop, which few waves enter, as in lbr_solve_scaled
     const double ds = scaled_step<3>(x, bh, ch, s, &w, &comp);
     s += ds;
     ++st.steps;
-    stop = fabs(ds) <= kHalleyStepTol * s && w <= 1e-2f;
+    stop = fabs(ds) <= kHalleyStepTol * s && w <= kScaledHalleyTol;
+  }
+  while (st.steps < steps && !stop) {
+    const double ds = scaled_step<3>(x, bh, ch, s, &w, &comp);
+    s += ds;
+    ++st.steps;
+    stop = fabs(ds) <= kHalleyStepTol * s && w <= kScaledHalleyTol;
   }
   st.s = s;
   st.converged = stop && s > 0.0;
