@@ -28,9 +28,9 @@
 // The price is handed to the solver in the normalised coordinates it
 // reduces every quote to: the Black-76 price of the model is
 // D sqrt(F K) (b(x, s) + intrinsic), and the solver's reduction (undiscount,
-// subtract the intrinsic value, divide by sqrt(F K)) takes it back to
-// beta = b(x, s) exactly in exact arithmetic, so the kernel passes beta = b
-// of the out-of-the-money side to the LBR solve without the round trip.
+// subtract the intrinsic value, divide by min(F, K)) takes it back to
+// b(x, s)/b_max exactly in exact arithmetic, so the kernel passes that of the
+// out-of-the-money side to the LBR solve without the round trip.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -207,27 +207,40 @@ __global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))
       const double sigma = vv * fv::rsqrt(vv);
       const double isqT = fv::rsqrt(q.T);
       const double s1 = sigma * (q.T * isqT);
-      // out-of-the-money side: x = -|ln(F/K)| <= 0, beta = b(x, s1),
-      // b_max = e^{x/2} = sqrt(min(F/K, K/F))
+      // out-of-the-money side: x = -|ln(F/K)| <= 0, beta = b(x, s1)
       const double x = -fabs(lfk);
-      const double bmax = fk < 1.0 ? fk * fv::rsqrt(fk) : fv::rsqrt(fk);
-      const fv::NBlack nb = fv::normalised_black(x, s1, bmax);
       // IV(P(sigma)) through the LBR solver; where the model price is not
       // solvable in binary64 (b rounded onto 0 or onto its bound b_max) the
       // composite takes its exact value sigma and unit slope
+      double s2 = s1;
+      bool solved = false;
+      if (x >= -128.0 && s1 > 1e-20 && s1 < 1e3) {
+        const fv::ScaledEval ev = fv::scaled_eval(x, s1);
+        const double part = fv::kInvSqrt2Pi * fv::fexp(-0.5 * ev.g * ev.g) * ev.rho;
+        const double bh = ev.comp ? 1.0 - part : part, ch = ev.comp ? part : 1.0 - part;
+        solved = fv::scaled_domain(x, bh, ch) && fv::lbr_solve_scaled(x, bh, ch, &s2);
+      }
+      if (__builtin_expect(!solved, 0)) {
+        // b_max = e^{x/2} = sqrt(min(F/K, K/F))
+        const double bmax = fk < 1.0 ? fk * fv::rsqrt(fk) : fv::rsqrt(fk);
+        const fv::NBlack nb = fv::normalised_black(x, s1, bmax);
+        solved = nb.b > 0.0 && nb.b < bmax;
+        if (solved) {
+          // ln beta from the evaluator's logarithmic parts (accurate also
+          // where b is below the normal range)
+          const double ln_beta = nb.lnbp + fv::flog(nb.ratio);
+          s2 = fv::lbr_solve(x, nb.b, bmax, ln_beta, fv::kLbrMinSteps, fv::kLbrMaxSteps,
+                             fv::kLbrStepTol).s;
+        }
+      }
       double iv = sigma, ratio = 1.0;
-      if (nb.b > 0.0 && nb.b < bmax) {
-        // ln beta from the evaluator's logarithmic parts (accurate also where
-        // b is below the normal range)
-        const double ln_beta = nb.lnbp + fv::flog(nb.ratio);
-        const fv::LbrResult res = fv::lbr_solve(x, nb.b, bmax, ln_beta, 2, 4, 1e-6);
-        iv = res.s * isqT;
+      if (solved) {
+        iv = s2 * isqT;
         // vega(v) = D F phi(d1(v)) sqrt(T); only vega(sigma)/vega(iv) enters:
         // with s = v sqrt(T) and d1 = ln(F/K)/s + s/2,
         //   ln(vega(s1)/vega(s2)) = -(d1(s1)^2 - d1(s2)^2)/2
         //                         = -(s1^2 - s2^2)(1/4 - L^2)/2,  L = ln(F/K)/(s1 s2),
         // which vanishes up to rounding (IV(P(sigma)) = sigma)
-        const double s2 = res.s;
         const double L = lfk * fv::rcp(s1 * s2);
         const double dl = -0.5 * (s1 - s2) * (s1 + s2) * fma(-L, L, 0.25);
         ratio = fabs(dl) < 1e-8 ? 1.0 + dl : fv::fexp(dl);
