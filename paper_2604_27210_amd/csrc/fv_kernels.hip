@@ -67,21 +67,53 @@ template <bool ARR = false>
 __device__ __forceinline__ double ld(const fv_arg& a, int64_t i) {
   return ARR ? a.ptr[i] : (a.ptr ? a.ptr[i] : a.value);
 }
+// The same for quote b + t, b uniform over the workgroup and t below 2^16:
+// the base moves by scalar instructions and every field shares one 32-bit
+// lane offset, where a 64-bit index costs a vector add per field.
+template <bool ARR>
+__device__ __forceinline__ double ld(const fv_arg& a, int64_t b, unsigned t) {
+  return ARR ? (a.ptr + b)[t] : (a.ptr ? (a.ptr + b)[t] : a.value);
+}
+template <bool ARR>
+__device__ __forceinline__ int ldflag(const KQuotes& q, int64_t b, unsigned t) {
+  return ARR ? (int)(q.flag + b)[t] : (q.flag ? (int)(q.flag + b)[t] : (int)q.flag_value);
+}
 template <bool ARR = false>
 __device__ __forceinline__ int ldflag(const KQuotes& q, int64_t i) {
   return ARR ? (int)q.flag[i] : (q.flag ? (int)q.flag[i] : (int)q.flag_value);
+}
+
+// The kernel's argument block (its one parameter, an A), read again where it
+// is asked for: pointers that are needed once, at the end or on a rare path,
+// do not take up scalar registers until then (there the polynomials'
+// constants fill them, and what does not fit is moved to vector registers
+// and back, two instructions a value).
+template <class A>
+__device__ __forceinline__ const A* late_args() {
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return (const A*)p;
+}
+
+// A pointer read that way, as one to global memory (the compiler knows that of
+// parameters only, and would take the slower flat accesses).
+template <class V>
+__device__ __forceinline__ __attribute__((address_space(1))) V* global_ptr(V* p) {
+  return (__attribute__((address_space(1))) V*)p;
 }
 
 struct GreekOut {
   double* p[5];
   int any;
 };
-__device__ __forceinline__ void store_greeks(const GreekOut& g, int64_t i, const Greeks& gr) {
-  if (g.p[0]) g.p[0][i] = gr.delta;
-  if (g.p[1]) g.p[1][i] = gr.gamma;
-  if (g.p[2]) g.p[2][i] = gr.vega;
-  if (g.p[3]) g.p[3][i] = gr.theta;
-  if (g.p[4]) g.p[4][i] = gr.rho;
+// (entry b + t, split as for ld)
+__device__ __forceinline__ void store_greeks(const GreekOut& g, int64_t b, unsigned t,
+                                             const Greeks& gr) {
+  if (g.p[0]) (global_ptr(g.p[0]) + b)[t] = gr.delta;
+  if (g.p[1]) (global_ptr(g.p[1]) + b)[t] = gr.gamma;
+  if (g.p[2]) (global_ptr(g.p[2]) + b)[t] = gr.vega;
+  if (g.p[3]) (global_ptr(g.p[3]) + b)[t] = gr.theta;
+  if (g.p[4]) (global_ptr(g.p[4]) + b)[t] = gr.rho;
 }
 
 // Largest workgroup the kernels are compiled for (8 waves).
@@ -148,32 +180,41 @@ __device__ __forceinline__ V opaque(V i) {
 // for the sake of a rare quote.
 template <int MODEL, bool ARR>
 __device__ __forceinline__ void lbr_general_at(const KQuotes& q, int64_t i, double* sg, uint8_t* st,
-                                               uint32_t* trace = nullptr) {
+                                               fv::ScaledQuote* sq, uint32_t* trace = nullptr) {
   i = opaque(i);
   fv::lbr_general(MODEL, ld<ARR>(q.price, i), ld<ARR>(q.fs, i), ld<ARR>(q.K, i), ld<ARR>(q.T, i),
                   ld<ARR>(q.r, i), MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0,
-                  ldflag<ARR>(q, i), sg, st, trace);
+                  ldflag<ARR>(q, i), sg, st, sq, trace);
 }
 
+// Arguments of the implied-volatility kernels.
+struct IvArgs {
+  KQuotes q;
+  double* sig_out;
+  uint8_t* st_out;
+  GreekOut g;
+};
+
 // ------------------------------------------------------------- IV: LBR
-// Bound by the vector ALU's issue rate: about 730 vector instructions per
+// Bound by the vector ALU's issue rate: about 570 vector instructions per
 // quote, every side of the guess a mixed wave takes included (1,157 with the
-// guess and the first step in binary64).  10M wide-wing BSM quotes: 190 us
-// (363 before), 1M BS quotes with the five Greeks: 31.5 us (54).
+// guess and the first step in binary64).  10M wide-wing BSM quotes: 155 us
+// (355 with those), 1M BS quotes with the five Greeks: 27.5 us (54).
 // One quote per thread: with a loop over several the compiler keeps the
 // polynomials' constants in registers across the whole solve, 110 VGPRs in
-// place of 55, and the same book takes 220 us.
+// place of 55, and the book took 220 us where it then took 190.
 template <int MODEL, bool GREEKS, bool ARR>
 __global__ __launch_bounds__(kMaxBlock)
-__attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(KQuotes q, double* __restrict__ sig_out, uint8_t* __restrict__ st_out,
-                         GreekOut g) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= q.n) return;
-  const double P = ld<ARR>(q.price, i), fs = ld<ARR>(q.fs, i), K = ld<ARR>(q.K, i), T = ld<ARR>(q.T, i),
-               r = ld<ARR>(q.r, i);
-  const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0;
-  const int th = ldflag<ARR>(q, i);
-  const fv::ScaledQuote sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, th);
+__attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(IvArgs args) {
+  const KQuotes& q = args.q;
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x;
+  const unsigned t = threadIdx.x;
+  if ((int64_t)t >= q.n - b) return;
+  const double P = ld<ARR>(q.price, b, t), fs = ld<ARR>(q.fs, b, t), K = ld<ARR>(q.K, b, t),
+               T = ld<ARR>(q.T, b, t), r = ld<ARR>(q.r, b, t);
+  const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, b, t) : 0.0;
+  const int th = ldflag<ARR>(q, b, t);
+  fv::ScaledQuote sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, th);
   uint8_t st = sq.status;
   double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
   bool general = sq.general;
@@ -182,9 +223,13 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(KQuotes
     general = !fv::lbr_solve_scaled(sq.x, sq.bh, sq.ch, &s);
     sg = s * sq.isqrtT;
   }
-  if (__builtin_expect(general, 0)) lbr_general_at<MODEL, ARR>(q, i, &sg, &st);
-  sig_out[i] = sg;
-  if (st_out) st_out[i] = st;
+  if (__builtin_expect(general, 0)) {
+    const KQuotes& late = late_args<IvArgs>()->q;
+    lbr_general_at<MODEL, ARR>(late, b + t, &sg, &st, &sq);
+  }
+  const auto* out = late_args<IvArgs>();
+  (global_ptr(out->sig_out) + b)[t] = sg;
+  if (uint8_t* st_out = out->st_out) (global_ptr(st_out) + b)[t] = st;
   if (GREEKS) {
     Greeks gr;
     if (st == fv::kQOk) {
@@ -193,7 +238,8 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(KQuotes
       const double nan = __builtin_nan("");
       gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
     }
-    store_greeks(g, i, gr);
+    const GreekOut& g = out->g;
+    store_greeks(g, b, t, gr);
   }
 }
 
@@ -209,7 +255,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_lbr_trace(KQuotes q, uint32_t* __
     const double P = ld(q.price, i), fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i),
                  r = ld(q.r, i);
     const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    const fv::ScaledQuote sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, ldflag(q, i));
+    fv::ScaledQuote sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, ldflag(q, i));
     uint32_t code = 0xFFFFFFFFu;  // not solved (status != OK)
     bool general = sq.general;
     if (sq.status == fv::kQOk && !general) {
@@ -220,7 +266,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_lbr_trace(KQuotes q, uint32_t* __
       double sg;
       uint8_t st;
       code = 0xFFFFFFFFu;
-      lbr_general_at<MODEL, false>(q, i, &sg, &st, &code);
+      lbr_general_at<MODEL, false>(q, i, &sg, &st, &sq, &code);
     }
     out[i] = code;
   }
@@ -235,13 +281,15 @@ __device__ __forceinline__ uint8_t halley_quote(double P, double fs, double K, d
                                                 fv::HalleyState* hs, fv::ScaledQuote* sq) {
   *sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, th);
   uint8_t st = sq->status;
-  if (st != fv::kQOk) return st;
   if (__builtin_expect(sq->general, 0)) {
     const Reduced rd = fv::reduce_quote(MODEL, opaque(P), opaque(fs), opaque(K), opaque(T),
                                         opaque(r), opaque(qy), th);
     st = rd.status;
     if (st == fv::kQOk) *hs = fv::halley_solve(rd.x, rd.beta, rd.bmax, rd.lnb, steps);
-  } else {
+    sq->F = rd.F;  // an extreme exponent or maturity made nothing of scaled_quote's
+    sq->D = rd.D;
+    sq->isqrtT = rd.isqrtT;
+  } else if (st == fv::kQOk) {
     *hs = fv::halley_solve_scaled(sq->x, sq->bh, sq->ch, steps);
   }
   return st;
@@ -284,28 +332,29 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 // Bound by the vector ALU like k_iv_lbr, on the same guess; its first two
 // steps are in binary32 and nearly every quote takes one binary64 step after
 // them (two full steps after one at guess precision before, with both in
-// binary64).  3M wide-wing BSM quotes: 62 us (133 before).  One quote per
+// binary64).  3M wide-wing BSM quotes: 53 us (131 before).  One quote per
 // thread, as k_iv_lbr; the queue holds one entry per thread.
 template <int MODEL, bool GREEKS, bool ARR>
 __global__ __launch_bounds__(kMaxBlock)
-__attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(KQuotes q, double* __restrict__ sig_out,
-                            uint8_t* __restrict__ st_out, GreekOut g) {
+__attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(IvArgs args) {
+  const KQuotes& q = args.q;
   extern __shared__ unsigned char smem_raw[];
   Pending* queue = reinterpret_cast<Pending*>(smem_raw);
   __shared__ int qcount;
   if (threadIdx.x == 0) qcount = 0;
   __syncthreads();
 
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x;
+  const unsigned t = threadIdx.x;
   bool fail = false;
   fv::HalleyState hs;
   hs.lo = 0.0;
   hs.hi = 0.0;
-  if (i < q.n) {
-    const double P = ld<ARR>(q.price, i), fs = ld<ARR>(q.fs, i), K = ld<ARR>(q.K, i), T = ld<ARR>(q.T, i),
-                 r = ld<ARR>(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, i) : 0.0;
-    const int th = ldflag<ARR>(q, i);
+  if ((int64_t)t < q.n - b) {
+    const double P = ld<ARR>(q.price, b, t), fs = ld<ARR>(q.fs, b, t), K = ld<ARR>(q.K, b, t),
+                 T = ld<ARR>(q.T, b, t), r = ld<ARR>(q.r, b, t);
+    const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, b, t) : 0.0;
+    const int th = ldflag<ARR>(q, b, t);
     fv::ScaledQuote sq;
     const uint8_t st = halley_quote<MODEL>(P, fs, K, T, r, qy, th, q.hsteps, &hs, &sq);
     double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
@@ -314,8 +363,9 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(K
       fail = !hs.converged;
     }
     if (!fail) {
-      sig_out[i] = sg;
-      if (st_out) st_out[i] = st;
+      const auto* out = late_args<IvArgs>();
+      (global_ptr(out->sig_out) + b)[t] = sg;
+      if (uint8_t* st_out = out->st_out) (global_ptr(st_out) + b)[t] = st;
       if (GREEKS) {
         Greeks gr;
         if (st == fv::kQOk) {
@@ -324,7 +374,8 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(K
           const double nan = __builtin_nan("");
           gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
         }
-        store_greeks(g, i, gr);
+        const GreekOut& g = out->g;
+        store_greeks(g, b, t, gr);
       }
     }
   }
@@ -338,7 +389,7 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(K
     wbase = __shfl(wbase, first);
     if (fail) {
       const int slot = wbase + __popcll(mask & lanemask_lt());
-      queue[slot].i = i;
+      queue[slot].i = b + t;
       queue[slot].lo = hs.lo;
       queue[slot].hi = hs.hi;
     }
@@ -348,6 +399,9 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(K
   const int m = qcount;
   for (int j = threadIdx.x; j < m; j += blockDim.x) {
     const int64_t iq = queue[j].i;
+    const auto* late = late_args<IvArgs>();
+    const KQuotes& q = late->q;
+    const GreekOut& g = late->g;
     const double P = ld<ARR>(q.price, iq), fs = ld<ARR>(q.fs, iq), K = ld<ARR>(q.K, iq), T = ld<ARR>(q.T, iq),
                  r = ld<ARR>(q.r, iq);
     const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, iq) : 0.0;
@@ -356,9 +410,9 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(K
     const double s =
         fv::bisection_solve(rd.x, rd.beta, rd.bmax, rd.lnb, queue[j].lo, queue[j].hi, kBisectTol);
     const double sg = s * rd.isqrtT;
-    sig_out[iq] = sg;
-    if (st_out) st_out[iq] = fv::kQOk;
-    if (GREEKS) store_greeks(g, iq, fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, rd.F, rd.D, P));
+    late->sig_out[iq] = sg;
+    if (uint8_t* st_out = late->st_out) st_out[iq] = fv::kQOk;
+    if (GREEKS) store_greeks(g, iq, 0, fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, rd.F, rd.D, P));
   }
 }
 
@@ -468,7 +522,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_greeks(KQuotes q, fv_arg sigma, G
       const double P = fv::price_at(F, K, D, sg, fv::sqrt_pos(T), th);
       gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, F, D, P);
     }
-    store_greeks(g, i, gr);
+    store_greeks(g, i, 0, gr);
   }
 }
 
@@ -608,7 +662,7 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
       uint8_t st;
       double sg;
       if (!kHalley) {
-        const fv::ScaledQuote sq = fv::scaled_quote(fv::kBlack76, P, F, K, T, r, 0.0, th);
+        fv::ScaledQuote sq = fv::scaled_quote(fv::kBlack76, P, F, K, T, r, 0.0, th);
         st = sq.status;
         sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
         bool general = sq.general;
@@ -620,7 +674,7 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
         if (__builtin_expect(general, 0)) {
           const int64_t io = opaque(i), co = opaque(cc), mo = opaque(m);
           fv::lbr_general(fv::kBlack76, c.price[io], c.F[co], c.K[io], c.T[mo], c.r[co], 0.0,
-                          c.flag[io], &sg, &st);
+                          c.flag[io], &sg, &st, &sq);
         }
       } else {
         fv::ScaledQuote sq;
@@ -1049,7 +1103,7 @@ int fv_implied_vol(int model, int solver, const fv_quotes* q, double* sigma_out,
     g.p[j] = greeks_out ? greeks_out[j] : nullptr;
     g.any |= g.p[j] != nullptr;
   }
-  const KQuotes k = to_k(q);
+  const IvArgs args = {to_k(q), sigma_out, status_out, g};
   hipStream_t s = (hipStream_t)stream;
   // every per-quote field an array (q only matters for Black-Scholes-Merton)
   const bool arr = q->price.ptr && q->fs.ptr && q->K.ptr && q->T.ptr && q->r.ptr && q->flag &&
@@ -1058,8 +1112,8 @@ int fv_implied_vol(int model, int solver, const fv_quotes* q, double* sigma_out,
     const LaunchShape sh{shape_for(FV_KERNEL_IV_LBR, model, q->n).block, 1};
     const dim3 grid = grid_for(q->n, sh), block(sh.block);
 #define FV_LBR(M, G)                                                                   \
-  (arr ? k_iv_lbr<M, G, true><<<grid, block, 0, s>>>(k, sigma_out, status_out, g) \
-       : k_iv_lbr<M, G, false><<<grid, block, 0, s>>>(k, sigma_out, status_out, g))
+  (arr ? k_iv_lbr<M, G, true><<<grid, block, 0, s>>>(args) \
+       : k_iv_lbr<M, G, false><<<grid, block, 0, s>>>(args))
     switch (model * 2 + (g.any ? 1 : 0)) {
       case 0: FV_LBR(0, false); break;
       case 1: FV_LBR(0, true); break;
@@ -1075,8 +1129,8 @@ int fv_implied_vol(int model, int solver, const fv_quotes* q, double* sigma_out,
   const dim3 grid = grid_for(q->n, sh), block(sh.block);
   const size_t lds = sizeof(Pending) * (size_t)sh.block;
 #define FV_HAL(M, G)                                                                    \
-  (arr ? k_iv_halley<M, G, true><<<grid, block, lds, s>>>(k, sigma_out, status_out, g) \
-       : k_iv_halley<M, G, false><<<grid, block, lds, s>>>(k, sigma_out, status_out, g))
+  (arr ? k_iv_halley<M, G, true><<<grid, block, lds, s>>>(args) \
+       : k_iv_halley<M, G, false><<<grid, block, lds, s>>>(args))
   switch (model * 2 + (g.any ? 1 : 0)) {
     case 0: FV_HAL(0, false); break;
     case 1: FV_HAL(0, true); break;

@@ -362,9 +362,9 @@ __host__ __device__ __attribute__((always_inline)) inline ScaledEval scaled_eval
   const double R12 = rcp(a1 * a2);
   const double R1 = R12 * a2, R2 = R12 * a1;
   const double y1 = fma(-k2BZ, R1, 1.0), y2 = fma(-k2BZ, R2, 1.0);
-  double B = coef::kErfcx[kErfcxDeg], D = 0.0;
+  double D = coef::kErfcx[kErfcxDeg], B = fma(D, y2, coef::kErfcx[kErfcxDeg - 1]);
 #pragma unroll
-  for (int i = kErfcxDeg - 1; i >= 0; --i) {
+  for (int i = kErfcxDeg - 2; i >= 0; --i) {
     D = fma(D, y1, B);
     B = fma(B, y2, coef::kErfcx[i]);
   }
@@ -385,7 +385,7 @@ __host__ __device__ __attribute__((always_inline)) inline double scaled_step(dou
                                                                              double ch, double s,
                                                                              float* w, bool* comp) {
   const ScaledEval e = scaled_eval(x, s);
-  const double W = kSqrt2Pi * fexp(0.5 * e.g * e.g);
+  const double W = kSqrt2Pi * fexp_in(0.5 * e.g * e.g);
   const double tgt = e.comp ? -ch : bh;
   const double nu = fma(tgt, W, e.comp ? e.rho : -e.rho);
   const float n = (float)(nu * e.is), hf = (float)e.h, sf = (float)s;
@@ -409,7 +409,7 @@ __host__ __device__ __attribute__((always_inline)) inline double scaled_step(dou
 // apart from beta/b_max: near the bound it is what decides the root, and a
 // rounding of beta/b_max would be amplified in the difference.
 __host__ __device__ inline bool scaled_domain(double x, double bh, double ch) {
-  return x >= -128.0 && (x <= -0x1p-60 || x == 0.0) && bh > 0x1p-960 && ch > 0x1p-40;
+  return all(x >= -128.0, !all(x > -0x1p-60, x != 0.0), bh > 0x1p-960, ch > 0x1p-40);
 }
 
 __host__ __device__ inline s32::Target scaled_target(double x, double bh, double ch) {
@@ -417,7 +417,6 @@ __host__ __device__ inline s32::Target scaled_target(double x, double bh, double
   q.ax = -(float)x;
   q.bh = (float)bh;
   q.ch = (float)ch;
-  q.lbh = s32::log_of_double(bh);
   return q;
 }
 
@@ -425,30 +424,29 @@ __host__ __device__ inline s32::Target scaled_target(double x, double bh, double
 // this w.  One quote in 1e5 of the wide workload is above it after the
 // binary32 step and takes one more.
 constexpr float kScaledStepTol = 2e-4f;
-constexpr int kScaledMaxSteps = 4;
 
-// LBR: guess and first Householder(3) step in binary32, then binary64 steps
-// until one settles.  Returns false (the caller takes lbr_solve) where none
-// does within the limit.  `trace` as lbr_solve's.
+// LBR: guess and first Householder(3) step in binary32, then a binary64 step,
+// and a second where the first did not settle.  Returns false (the caller
+// takes lbr_solve) where neither does.  `trace` as lbr_solve's.
 __host__ __device__ __attribute__((always_inline)) inline bool lbr_solve_scaled(
     double x, double bh, double ch, double* root, uint32_t* trace = nullptr) {
-  const s32::Target q = scaled_target(x, bh, ch);
-  const s32::Guess g = s32::initial_guess(q);
-  const s32::Eval e = s32::eval<false>(q.ax, g.s);
-  double s = (double)fmaf(g.s, s32::householder3(q, g.region, e, g.s), g.s);
-  // the first binary64 step apart from the loop, which few waves enter: its
-  // constants are then set up where they are used
+  s32::Target q = scaled_target(x, bh, ch);
+  const float s0 = s32::initial_guess(bh, ch, q);
+  const s32::Eval e = s32::eval<false>(q.ax, s0);
+  double s = (double)fmaf(s0, s32::householder3(q, e, s0), s0);
   float w;
   bool comp;
   s += scaled_step<4>(x, bh, ch, s, &w, &comp);
-  uint32_t forms = ((uint32_t)g.comp_o << 6) | ((uint32_t)e.comp << 8) | ((uint32_t)comp << 10);
+  uint32_t forms = ((uint32_t)!q.lower << 6) | ((uint32_t)e.comp << 8) | ((uint32_t)comp << 10);
   int it = 2;
-  while (!(w <= kScaledStepTol) && it < kScaledMaxSteps) {
+  // no loop: the compiler would set up its constants ahead of the test, for
+  // every wave
+  if (__builtin_expect(!(w <= kScaledStepTol), 0)) {
     s += scaled_step<4>(x, bh, ch, s, &w, &comp);
-    forms |= (uint32_t)comp << (8 + 2 * it);
-    ++it;
+    forms |= (uint32_t)comp << 12;
+    it = 3;
   }
-  if (trace) *trace = (uint32_t)g.region | ((uint32_t)(it - 2) << 2) | forms;
+  if (trace) *trace = s32::region_of(q) | ((uint32_t)(it - 2) << 2) | forms;
   *root = s;
   return w <= kScaledStepTol && s > 0.0;
 }
@@ -601,14 +599,15 @@ __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_sol
 constexpr float kScaledHalleyTol = 1e-2f;
 
 // The Halley path's main form: guess and the first two steps in binary32
-// (one, when the limit leaves room for a single binary64 step only), then
-// binary64 steps to the same stop as halley_solve.  The binary32 steps work
+// (one, when the limit leaves room for a single binary64 step only), then a
+// binary64 step, and a second where the first misses halley_solve's stop; a
+// quote that misses it again is left to the bisection.  The binary32 steps work
 // on ln b - ln beta (in the complement form on the direct residual), which
 // converges from the guess at any depth of the wing.
 __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_solve_scaled(
     double x, double bh, double ch, int steps) {
-  const s32::Target q = scaled_target(x, bh, ch);
-  float s0 = s32::initial_guess(q).s;
+  s32::Target q = scaled_target(x, bh, ch);
+  float s0 = s32::initial_guess(bh, ch, q);
   HalleyState st;
   st.lo = 0.0;
   st.hi = 1e300;
@@ -619,13 +618,13 @@ __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_sol
   bool stop = false;
   float w;
   bool comp;
-  if (st.steps < steps) {  // apart from the loop, which few waves enter, as in lbr_solve_scaled
+  if (st.steps < steps) {
     const double ds = scaled_step<3>(x, bh, ch, s, &w, &comp);
     s += ds;
     ++st.steps;
     stop = fabs(ds) <= kHalleyStepTol * s && w <= kScaledHalleyTol;
   }
-  while (st.steps < steps && !stop) {
+  if (__builtin_expect(!stop && st.steps < steps, 0)) {
     const double ds = scaled_step<3>(x, bh, ch, s, &w, &comp);
     s += ds;
     ++st.steps;

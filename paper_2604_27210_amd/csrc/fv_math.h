@@ -34,17 +34,24 @@ constexpr double kSqrt3 = 1.73205080756887729353;
 constexpr double kEps = 2.220446049250313e-16;
 constexpr double kDblMin = 2.2250738585072014e-308;  // smallest normal binary64
 
+// Conjunction without short circuit: the tests of a quote's fields are one
+// instruction each, cheaper than the branches && makes of them.
+template <class... B>
+__host__ __device__ inline bool all(B... b) {
+  return ((int)b & ...);
+}
+
 // ----------------------------------------------------------- reciprocal
-// 1/x for finite, normal, non-zero x: the hardware estimate v_rcp_f64
-// refined by two Newton steps (r <- r + r (1 - x r)), within ~1 ulp.  Cheaper
+// 1/x for finite, normal, non-zero x: the hardware estimate v_rcp_f64 (good
+// to 2^-24.4) refined by one cubic step r (1 + e + e^2), e = 1 - x r: within
+// 0.5 ulp, as two Newton steps are, and one instruction shorter.  Cheaper
 // than an IEEE division, which also handles zero, infinite and denormal
 // operands: for those the refinement yields NaN (see rcp_safe).
 __host__ __device__ inline double rcp(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return r;
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 #else
   return 1.0 / x;
 #endif
@@ -55,30 +62,22 @@ __host__ __device__ inline double rcp(double x) {
 __host__ __device__ inline double rcp_safe(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const double r0 = __builtin_amdgcn_rcp(x);
-  double r = fma(r0, fma(-x, r0, 1.0), r0);
-  r = fma(r, fma(-x, r, 1.0), r);
+  const double e = fma(-x, r0, 1.0);
+  const double r = fma(r0, fma(e, e, e), r0);
   return r == r ? r : r0;
 #else
   return 1.0 / x;
 #endif
 }
 
-// a/b from the refined reciprocal plus one residual correction (~1 ulp).
-__host__ __device__ inline double fdiv(double a, double b) {
-  const double r = rcp(b);
-  const double q = a * r;
-  return fma(fma(-b, q, a), r, q);
-}
-
-// 1/sqrt(x) for finite positive normal x: v_rsq_f64 refined by two Newton
-// steps y <- y + y (1/2 - x y^2 / 2).
+// 1/sqrt(x) for finite positive normal x: v_rsq_f64 (2^-24.2) refined by one
+// cubic step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2 (0.7 ulp, as two Newton
+// steps; two instructions shorter).
 __host__ __device__ inline double rsqrt(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  double y = __builtin_amdgcn_rsq(x);
-  const double hx = 0.5 * x;
-  y = fma(y, fma(-hx * y, y, 0.5), y);
-  y = fma(y, fma(-hx * y, y, 0.5), y);
-  return y;
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
 #else
   return 1.0 / sqrt(x);
 #endif
@@ -90,38 +89,60 @@ __host__ __device__ inline double rsqrt(double x) {
 // never pass, at two to three times the instruction count).
 //
 // exp: Cody-Waite reduction x = n ln2 + r, |r| <= ln2/2, with ln2 split in a
-// high part exact in binary64 products and a low part; e^r by its Taylor
-// series to degree 13 (truncation < 4e-18 on |r| <= ln2/2); 2^n by ldexp.
-// Arguments below -1000 give 0 (ldexp underflows), NaN propagates.
+// high part exact in binary64 products and a low part; e^r = 1 + r + r^2/2 +
+// r^3 Q(r) with a fitted Q of degree 8 (5e-18 relative, fv_coeffs.h; the
+// Taylor series needs two terms more); 2^n by ldexp.  fexp_in is for
+// arguments within +-1000; fexp gives 0 below that and passes NaN on.
 constexpr double kLn2Hi = 6.93147180369123816490e-01;  // 0x3FE62E42FEE00000
 constexpr double kLn2Lo = 1.90821492927058770002e-10;  // ln2 - kLn2Hi
 constexpr double kLog2E = 1.44269504088896338700e+00;
+constexpr int kExpDeg = (int)(sizeof(coef::kExpQ) / sizeof(double)) - 1;
 
-__host__ __device__ inline double fexp(double x) {
-  x = x < -1000.0 ? -1000.0 : x;
+__host__ __device__ inline double fexp_in(double x) {
   const double n = rint(x * kLog2E);
   const double r = fma(-n, kLn2Lo, fma(-n, kLn2Hi, x));
-  double p = 1.0 / 6227020800.0;                      // 1/13!
-  p = fma(p, r, 1.0 / 479001600.0);                   // 1/12!
-  p = fma(p, r, 1.0 / 39916800.0);
-  p = fma(p, r, 1.0 / 3628800.0);
-  p = fma(p, r, 1.0 / 362880.0);
-  p = fma(p, r, 1.0 / 40320.0);
-  p = fma(p, r, 1.0 / 5040.0);
-  p = fma(p, r, 1.0 / 720.0);
-  p = fma(p, r, 1.0 / 120.0);
-  p = fma(p, r, 1.0 / 24.0);
-  p = fma(p, r, 1.0 / 6.0);
+  double p = coef::kExpQ[kExpDeg];
+#pragma unroll
+  for (int i = kExpDeg - 1; i >= 0; --i) p = fma(p, r, coef::kExpQ[i]);
   p = fma(p, r, 0.5);
   p = fma(p, r, 1.0);
   p = fma(p, r, 1.0);
   return ldexp(p, (int)n);
 }
 
+__host__ __device__ inline double fexp(double x) { return fexp_in(x < -1000.0 ? -1000.0 : x); }
+
+// a/b with one Newton step on the reciprocal: the residual a - b q is exact
+// in an fma, so q's own error is squared away (0.5 ulp).
+__host__ __device__ inline double fdiv(double a, double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double r0 = __builtin_amdgcn_rcp(b);
+  const double r = fma(r0, fma(-b, r0, 1.0), r0);
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+#else
+  return a / b;
+#endif
+}
+
+// e ln2 + ln((1 + f)/(1 - f)) for |f| <= 0.1716 (1 +- f from sqrt(1/2) to
+// sqrt(2) apart): 2 f (1 + z S(z)), z = f^2, with a fitted S of degree 6
+// (1.2e-18 relative, fv_coeffs.h; the series needs three terms more), and
+// ln2 split as in fexp.
+constexpr int kAtanhDeg = (int)(sizeof(coef::kAtanh) / sizeof(double)) - 1;
+
+__host__ __device__ inline double log_of(double f, int e) {
+  const double z = f * f;
+  double S = coef::kAtanh[kAtanhDeg];
+#pragma unroll
+  for (int i = kAtanhDeg - 1; i >= 0; --i) S = fma(S, z, coef::kAtanh[i]);
+  const double f2 = f + f;
+  const double de = (double)e;
+  return fma(de, kLn2Hi, fma(de, kLn2Lo, fma(f2 * z, S, f2)));
+}
+
 // log for positive finite x (0 gives -inf): x = 2^e m with m in
-// [sqrt(1/2), sqrt(2)), f = (m - 1)/(m + 1), ln m = 2 atanh(f) =
-// 2f (1 + f^2/3 + f^4/5 + ...), |f| <= 0.1716 so ten terms reach binary64
-// precision; ln x = e ln2 + ln m with ln2 split as in fexp.
+// [sqrt(1/2), sqrt(2)), f = (m - 1)/(m + 1).
 __host__ __device__ inline double flog(double x) {
   int e;
   double m = frexp(x, &e);  // m in [1/2, 1)
@@ -129,23 +150,22 @@ __host__ __device__ inline double flog(double x) {
     m += m;
     --e;
   }
-  const double f = fdiv(m - 1.0, m + 1.0);  // m + 1 in [1.7, 2.5]
-  const double z = f * f;
-  double S = 1.0 / 21.0;
-  S = fma(S, z, 1.0 / 19.0);
-  S = fma(S, z, 1.0 / 17.0);
-  S = fma(S, z, 1.0 / 15.0);
-  S = fma(S, z, 1.0 / 13.0);
-  S = fma(S, z, 1.0 / 11.0);
-  S = fma(S, z, 1.0 / 9.0);
-  S = fma(S, z, 1.0 / 7.0);
-  S = fma(S, z, 1.0 / 5.0);
-  S = fma(S, z, 1.0 / 3.0);
-  const double f2 = f + f;
-  const double de = (double)e;
-  const double lm = fma(f2 * z, S, f2);  // 2f + 2f z S(z)
-  const double res = fma(de, kLn2Hi, fma(de, kLn2Lo, lm));
+  const double res = log_of(fdiv(m - 1.0, m + 1.0), e);
   return x == 0.0 ? -__builtin_inf() : res;
+}
+
+// ln(a/b) for positive finite a and b, whatever their ratio: the significands
+// are brought within a factor sqrt(2) of each other and f = (a' - b')/(a' + b')
+// takes the place of the quotient, whose rounding is what limits ln(a/b) near
+// a = b (there a' - b' is exact).  `exp_a` receives a's exponent.
+__host__ __device__ inline double log_ratio(double a, double b, int* exp_a = nullptr) {
+  int ea, eb;
+  double ma = frexp(a, &ea);
+  const double mb = frexp(b, &eb);
+  if (exp_a) *exp_a = ea;
+  const int k = (int)(ma * 0.70710678118654752440 > mb) - (int)(ma < mb * 0.70710678118654752440);
+  ma = ldexp(ma, -k);
+  return log_of(fdiv(ma - mb, ma + mb), ea - eb + k);
 }
 
 // ------------------------------------------------ guess-precision helpers
@@ -426,9 +446,9 @@ __host__ __device__ inline NBlack normalised_black_t(double x, double s, double 
   }
   const double y1 = (z1 - kShift) * R1, y2 = (q2 - kShift) * R2;
   // B = p(y2), D = (p(y1) - p(y2))/(y1 - y2) by two Horner recurrences
-  double B = kC[kDeg], D = 0.0;
+  double D = kC[kDeg], B = fma(D, y2, kC[kDeg - 1]);
 #pragma unroll
-  for (int i = kDeg - 1; i >= 0; --i) {
+  for (int i = kDeg - 2; i >= 0; --i) {
     D = fma(D, y1, B);
     B = fma(B, y2, kC[i]);
   }

@@ -66,22 +66,25 @@ __host__ __device__ inline double rsqrt_pos(double T) {
 // reaches tens, where dropping e would put tens of ulps into the forward or
 // the discount factor, errors that the inputs' own conditioning does not
 // cover (the exact sensitivity to r cancels between forward and discount).
+// IN: the caller knows |a b| <= 700 (fexp_in).
+template <bool IN = false>
 __host__ __device__ inline double fexp_prod(double a, double b) {
   const double p = a * b;
   const double e = fma(a, b, -p);
-  const double E = fexp(p);
+  const double E = IN ? fexp_in(p) : fexp(p);
   return fma(E, e, E);
 }
 
 // e^{(r - q) T}, carrying the rounding of r - q as well (Knuth's two-sum:
 // r - q = c + ce exactly)
+template <bool IN = false>
 __host__ __device__ inline double fexp_carry(double r, double q, double T) {
   const double c = r - q;
   const double bb = c - r;
   const double ce = (r - (c - bb)) + (-q - bb);
   const double p = c * T;
   const double e = fma(c, T, -p) + ce * T;
-  const double E = fexp(p);
+  const double E = IN ? fexp_in(p) : fexp(p);
   return fma(E, e, E);
 }
 
@@ -92,9 +95,10 @@ __host__ __device__ inline double minus(double a, double b) {
 }
 
 // F / fs
+template <bool IN = false>
 __host__ __device__ inline double growth_of(int model, double T, double r, double q) {
   if (model == kBlack76) return 1.0;
-  return model == kBlackScholesMerton ? fexp_carry(r, q, T) : fexp_prod(r, T);
+  return model == kBlackScholesMerton ? fexp_carry<IN>(r, q, T) : fexp_prod<IN>(r, T);
 }
 
 __host__ __device__ inline double forward_of(int model, double fs, double T, double r,
@@ -102,13 +106,8 @@ __host__ __device__ inline double forward_of(int model, double fs, double T, dou
   return model == kBlack76 ? fs : fs * growth_of(model, T, r, q);
 }
 
-// ln(F/K) from the ratio while F/K is a normal number, else from the two
-// logarithms (|ln(F/K)| beyond about 708, or an operand the refined
-// reciprocal cannot take: the comparisons fail on a NaN ratio).
-__host__ __device__ inline double log_moneyness(double F, double K) {
-  const double fk = F * rcp(K);
-  return (fk > kDblMin && fk < 0x1p1023) ? flog(fk) : flog(F) - flog(K);
-}
+// ln(F/K) for positive finite F and K
+__host__ __device__ inline double log_moneyness(double F, double K) { return log_ratio(F, K); }
 
 __host__ __device__ inline Reduced reduce_quote(int model, double price, double fs, double K,
                                                 double T, double r, double q, int theta) {
@@ -160,9 +159,9 @@ __host__ __device__ inline Reduced reduce_quote(int model, double price, double 
 }
 
 // What the scaled solvers (fv_lbr.h) need of a quote.  The status is decided
-// by the very expressions of reduce_quote; `general` marks a quote that has
-// an implied volatility, or may have one, but lies outside the scaled
-// solvers' domain: it goes through reduce_quote and the general solver.
+// by the very expressions of reduce_quote; `general` marks a quote outside
+// the scaled solvers' domain, or whose status these forms cannot decide: it
+// goes through reduce_quote and the general solver.
 // Against reduce_quote this drops ln beta (a logarithm) and 1/sqrt(F K)
 // (two reciprocal square roots): bh = beta/b_max = (Pu - I)/min(F, K).
 struct ScaledQuote {
@@ -173,29 +172,39 @@ struct ScaledQuote {
   bool general;
 };
 
+__host__ __device__ inline bool positive_normal(double v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_class(v, 0x100);
+#else
+  return v >= kDblMin && finite_d(v);
+#endif
+}
+
 __host__ __device__ inline ScaledQuote scaled_quote(int model, double price, double fs, double K,
                                                     double T, double r, double q, int theta) {
   ScaledQuote o;
-  const bool ok_in = finite_d(price) && finite_d(fs) && finite_d(K) && finite_d(T) &&
-                     finite_d(r) && finite_d(q) && fs >= kDblMin && K >= kDblMin && T > 0.0 &&
-                     (theta == 1 || theta == -1);
-  const double gr = growth_of(model, T, r, q);
+  const double rT = r * T;
+  const double cT = model == kBlackScholesMerton ? minus(r, q) * T : rT;
+  // The plain forms below need T normal and both exponents in range.  A
+  // quote outside (an infinite or NaN rate among them) goes to the general
+  // path whole, so T, r and q need no test of their own.
+  const bool plain = all(T >= 1e-290, fabs(rT) <= 700.0, fabs(cT) <= 700.0);
+  const double gr = growth_of<true>(model, T, r, q);
   const double F = fs * gr;
-  const bool ok_f = F >= kDblMin && finite_d(F);
-  const double cap = fexp_prod(r, T);  // 1/D
+  const double cap = fexp_prod<true>(r, T);  // 1/D
   const double Pu = price * cap;
   const double dth = (double)theta;
   const double I = fmax(dth * minus(F, K), 0.0);
   const double M = theta > 0 ? F : K;
   o.F = F;
-  o.D = fexp_prod(-r, T);
-  o.isqrtT = rsqrt_pos(T);
-  const double m = fmin(F, K);
-  const double fk = F * rcp(K);
-  o.x = -fabs(flog(fk));
+  o.D = fexp_prod<true>(-r, T);
+  o.isqrtT = rsqrt(T);
+  int eF;
+  o.x = -fabs(log_ratio(F, K, &eF));
   // the time value from the rounded forward and the unrounded price: in the
   // money it is a small difference of large numbers, and what its operands'
   // roundings leave of it is the quote's implied volatility
+  const double m = F < K ? F : K;
   const double tv = fma(price, cap, -I), im = rcp(m);
   o.bh = tv * im;
   o.ch = (m - tv) * im;
@@ -203,19 +212,25 @@ __host__ __device__ inline ScaledQuote scaled_quote(int model, double price, dou
   if (Pu >= M) st = kQAboveMax;
   if (Pu == I) st = kQAtIntrinsic;
   if (Pu < I) st = kQBelowIntrinsic;
-  if (!(ok_in && ok_f)) st = kQInvalid;
+  const bool valid = all(finite_d(price), positive_normal(fs), positive_normal(K),
+                         positive_normal(F), ((theta + 1) & ~2) == 0);
+  st = valid ? st : (uint8_t)kQInvalid;
   o.status = st;
-  // F and K away from the ends of the range, where rcp would lose bits
-  o.general = st == kQOk && !(scaled_domain(o.x, o.bh, o.ch) && m >= 0x1p-1000 &&
-                              fmax(F, K) <= 0x1p+1000);
+  // m below 2^1001, where rcp keeps its precision (its lower end holds to the
+  // smallest normal number)
+  o.general = !all(plain, st != kQOk || all(scaled_domain(o.x, o.bh, o.ch), eF <= 1000));
   return o;
 }
 
 // The general implied volatility of one quote: reduce_quote and lbr_solve.
+// Replaces what scaled_quote made of F and D.
 __host__ __device__ __attribute__((always_inline)) inline void lbr_general(
     int model, double price, double fs, double K, double T, double r, double q, int theta,
-    double* sigma, uint8_t* status, uint32_t* trace = nullptr) {
+    double* sigma, uint8_t* status, ScaledQuote* sq, uint32_t* trace = nullptr) {
   const Reduced rd = reduce_quote(model, price, fs, K, T, r, q, theta);
+  sq->F = rd.F;  // an extreme exponent or maturity made nothing of scaled_quote's
+  sq->D = rd.D;
+  sq->isqrtT = rd.isqrtT;
   uint8_t st = rd.status;
   double sg = st == kQAtIntrinsic ? 0.0 : __builtin_nan("");
   if (st == kQOk) {

@@ -8,7 +8,7 @@
 // polynomial step takes its constant as a 32-bit literal where binary64
 // first moves it into a register pair.  Per quote of the wide workload the
 // binary64 guess and first step took 640 vector and 270 scalar
-// instructions; these take about 240 and 60.
+// instructions; these take about 280 and 40.
 //
 // Binary32 cannot hold b itself deep in a wing, so everything is scaled by
 // the bound b_max = e^{x/2}: bh = b/b_max in (0, 1) and
@@ -81,22 +81,24 @@ __host__ __device__ inline float log_of_double(double v) {
 }
 
 constexpr float kZ0 = (float)coef::kErfcxZ0;
-constexpr int kGDeg = (int)(sizeof(coef::kErfcxG) / sizeof(double)) - 1;
-constexpr int kLoDeg = (int)(sizeof(coef::kErfcxLo) / sizeof(double)) - 1;
+// erfcx(z), z >= -1/2, by the guess's fit (6e-4)
+constexpr int kSDeg = (int)(sizeof(coef::kErfcxS) / sizeof(double)) - 1;
+constexpr int kTDeg = (int)(sizeof(coef::kErfcxT) / sizeof(double)) - 1;
 
-// erfcx(z), z >= -1/2, by the initial guess's fit (4e-6)
 __host__ __device__ inline float erfcx(float z) {
-  constexpr float kB = (float)coef::kErfcxGB;
+  constexpr float kB = (float)coef::kErfcxSB;
   const float R = rcp(z + kB);
   const float y = fmaf(-2.0f * (kB - kZ0), R, 1.0f);
-  float p = (float)coef::kErfcxG[kGDeg];
+  float p = (float)coef::kErfcxS[kSDeg];
 #pragma unroll
-  for (int i = kGDeg - 1; i >= 0; --i) p = fmaf(p, y, (float)coef::kErfcxG[i]);
+  for (int i = kSDeg - 1; i >= 0; --i) p = fmaf(p, y, (float)coef::kErfcxS[i]);
   return p * R;
 }
 
 // The normalised Black function at s, as ratios to b' (fv_math.h has the
-// two forms): GUESS picks the degree-7 fit of erfcx, else the degree-12 one.
+// two forms): GUESS picks the degree-4 fit of erfcx (6e-4, its derivative
+// 1e-2: far within the few percent the guess is off), else the degree-9 one
+// (4e-7, 7e-6: the step it serves lands as near) and the form by g.
 struct Eval {
   float is, h2;  // 1/s, h^2
   float g2;      // g^2/2: b'/b_max = e^{-g2}/sqrt(2 pi)
@@ -105,10 +107,10 @@ struct Eval {
 };
 
 template <bool GUESS>
-__host__ __device__ inline Eval eval(float ax, float s) {
-  constexpr int kDeg = GUESS ? kGDeg : kLoDeg;
-  constexpr const double* kC = GUESS ? coef::kErfcxG : coef::kErfcxLo;
-  constexpr float kB = (float)(GUESS ? coef::kErfcxGB : coef::kErfcxLoB);
+__host__ __device__ inline Eval eval(float ax, float s, bool comp = false) {
+  constexpr int kDeg = GUESS ? kSDeg : kTDeg;
+  constexpr const double* kC = GUESS ? coef::kErfcxS : coef::kErfcxT;
+  constexpr float kB = (float)(GUESS ? coef::kErfcxSB : coef::kErfcxTB);
   Eval e;
   e.is = rcp(s);
   const float h = -ax * e.is, t = 0.5f * s;
@@ -116,16 +118,16 @@ __host__ __device__ inline Eval eval(float ax, float s) {
   e.h2 = h * h;
   e.g2 = 0.5f * g * g;
   const float q1 = -g * kInvSqrt2, q2 = (t - h) * kInvSqrt2;
-  e.comp = q1 < -kZ0;
+  e.comp = GUESS ? comp : g > kInvSqrt2;
   const float z1 = e.comp ? -q1 : q1;
   const float a1 = z1 + kB, a2 = q2 + kB;
   const float R12 = rcp(a1 * a2);
   const float R1 = R12 * a2, R2 = R12 * a1;
   constexpr float k2BZ = 2.0f * (kB - kZ0);
   const float y1 = fmaf(-k2BZ, R1, 1.0f), y2 = fmaf(-k2BZ, R2, 1.0f);
-  float B = (float)kC[kDeg], D = 0.0f;
+  float D = (float)kC[kDeg], B = fmaf(D, y2, (float)kC[kDeg - 1]);
 #pragma unroll
-  for (int i = kDeg - 1; i >= 0; --i) {
+  for (int i = kDeg - 2; i >= 0; --i) {
     D = fmaf(D, y1, B);
     B = fmaf(B, y2, (float)kC[i]);
   }
@@ -136,120 +138,111 @@ __host__ __device__ inline Eval eval(float ax, float s) {
   return e;
 }
 
-// What the start needs of a quote.
+// What the start needs of a quote.  `lower`: beta below b(s_c), the value at
+// the inflection point s_c = sqrt(2|x|); v = bh there and 1 - bh above, the
+// scaled distance from the bound on beta's side, and lv = ln v.
 struct Target {
-  float ax;   // |x|
-  float bh;   // beta/b_max (flushed to 0 below the binary32 range)
-  float ch;   // 1 - beta/b_max
-  float lbh;  // ln(beta/b_max)
+  float ax;      // |x|
+  float bh, ch;  // beta/b_max and 1 - beta/b_max (flushed to 0 below the binary32 range)
+  float v, lv;
+  bool lower, wing;  // the guess's region: R1 lower wing, R2, R3, R4 upper wing
 };
 
-enum Region : int { kR1 = 0, kR2 = 1, kR3 = 2, kR4 = 3 };
-
-struct Guess {
-  float s;
-  int region;
-  bool comp_o;  // evaluation form at the boundary point (diagnostics)
-};
+__host__ __device__ inline uint32_t region_of(const Target& q) {
+  return q.lower ? (q.wing ? 0u : 1u) : (q.wing ? 3u : 2u);
+}
 
 // The four-region initial guess (fv_lbr.h, lbr_initial_guess, states the
-// regions, the maps and the rational cubic) in scaled form.  With
-// P(z) = Phi(z) e^{z^2/2} = erfcx(-z/sqrt2)/2 the maps' values and slopes at
-// the boundary point are free of exponentials that leave the range:
-//   R1, everything divided by D = bh_l:  f/D = cl P^3 e^{t^2/2} sqrt(2 pi)/rho,
-//       f'_beta = (2 pi/3) h^2 P^2 e^{t^2/2}  (z = h/sqrt3),
-//       D f''_beta = (rho/s) f'_beta (2 phi(0) |z|/P - 2 h^2/3 - 2 + s^2/4),
-//       and the cubic gives f/beta, so ln f = ln beta + ln(f/beta);
-//   R4, divided by f_u = Phi(-t):  D f'_beta = -(c/b')/(2 sqrt(2 pi) P)  (z = -t),
-//       at b_max that times e^{-h^2/2},
-//       D^2 f''_beta = -D f'_beta (c/b') h^2/s.
-__host__ __device__ inline Guess initial_guess(const Target& q) {
-  Guess out;
+// regions, the maps and the rational cubic), in scaled form and in the
+// distance v from the bound on beta's side, which makes the two halves
+// mirror images: the tangent point s_o lies below s_c with the difference
+// form's value b/b_max = v_o, or above it with the complement form's
+// 1 - b/b_max = v_o; every cubic is fitted at its right end; and the maps,
+// divided by their slope at v = 0, start with f/v = 1:
+//   interior, v in [v_o, v_c]:  s from s_o to s_c, slopes -+b_max/b', no
+//     curvature at s_c;
+//   R1, v in [0, v_o]:  f = f_l, ln f = ln v - |x|/2 + ln(f/v),
+//     f' = (2 pi/3) h^2 P^2 e^{t^2/2},  f/v_o = 3.03 |x| P^3 e^{t^2/2} b'/b,
+//     v_o f'' = (b/(s b')) f' (2 phi(0) z/P - 2 h^2/3 - 2 + s^2/4),
+//     z = |h|/sqrt3;
+//   R4, v in [0, v_o]:  f = f_u, ln f = ln v - |x|/2 - ln 2 + ln(f/v),
+//     f' = e^{h^2/2},  f/v_o = 2 sqrt(2 pi) P e^{h^2/2} b'/(b_max - b),
+//     v_o f'' = ((b_max - b)/(s b')) f' h^2,  z = t,
+// with P = Phi(-z) e^{z^2/2} = erfcx(z/sqrt2)/2 and everything at s_o.
+// Returns s0 and completes q.
+__host__ __device__ inline float initial_guess(double bh, double ch, Target& q) {
   const float a = sqrt(q.ax);
   const float sc = kSqrt2 * a;
-  float om = 1.0f - erfcx(a);  // 1 - erfcx(sqrt|x|)
-  float sl = sc - kSqrtPiOver2 * om;
-  if (a < 0.03f) {  // both differences cancel near the money: series in a
-    constexpr float c3 = 0.752252778063675f, c5 = 0.300901111225470f, c7 = 0.0859717460644200f;
-    const float tail =
-        fmaf(-a, fmaf(-a, fmaf(-a, fmaf(-a, fmaf(-a, c7, 1.0f / 6.0f), c5), 0.5f), c3), 1.0f);
-    om = a * fmaf(-a, tail, kTwoOverSqrtPi);
-    sl = kSqrtPiOver2 * q.ax * tail;
-  }
-  const float bc = 0.5f * om;  // bh(s_c); b'(s_c) = b_max/sqrt(2 pi)
-  const bool lower = q.bh < bc;
-  const float so = lower ? sl : fmaf(1.0f - bc, kSqrt2Pi, sc);
-  const Eval e = eval<true>(q.ax, so);
-  out.comp_o = e.comp;
-  const float ibo = kSqrt2Pi * exp(e.g2);  // b_max/b'(s_o)
-  const float ro = e.rho * rcp(ibo);       // bh(s_o), or 1 - bh(s_o)
-  const float bo = e.comp ? 1.0f - ro : ro;
-  const float t = 0.5f * so;
-  const bool wing = lower ? q.bh < bo : q.bh > bo;
-  out.region = lower ? (wing ? kR1 : kR2) : (wing ? kR4 : kR3);
-  // the rational cubic's end data: values Yl, Yr, slopes Dl, Dr times the
-  // interval and C half the second derivative times its square
-  float Yl, Yr, Dl, Dr, C, D, xl;
-  float Pz = 0.0f;
-  if (wing) {
-    const float z = lower ? sqrt(e.h2) * kInvSqrt3 : t;  // |z|
-    Pz = 0.5f * erfcx(z * kInvSqrt2);
-    if (lower) {
-      const float et = exp(0.5f * t * t);
-      const float P2 = Pz * Pz * et;
-      D = bo;
-      xl = 0.0f;
-      Yl = 0.0f;
-      Yr = (kCl * kSqrt2Pi) * q.ax * P2 * Pz * rcp(e.rho);
-      Dl = 1.0f;
-      Dr = (2.0f * 1.04719755119659775f) * e.h2 * P2;
-      C = 0.5f * e.rho * e.is * Dr *
-          (fmaf(-2.0f / 3.0f, e.h2, (2.0f * kInvSqrt2Pi) * z * rcp(Pz)) + fmaf(t, t, -2.0f));
-    } else {
-      const float cr = e.comp ? e.rho : (1.0f - bo) * ibo;  // c/b'
-      D = 1.0f - bo;
-      xl = bo;
-      Yl = 1.0f;
-      Yr = 0.0f;
-      Dl = -0.5f * kInvSqrt2Pi * cr * rcp(Pz);
-      Dr = Dl * exp(-0.5f * e.h2);
-      C = -0.5f * Dl * cr * e.h2 * e.is;
-    }
+  // The lower tangent point s_l = sqrt2 a - sqrt(pi/2) (1 - erfcx(a)) and
+  // 1 - erfcx(a) itself are differences that cancel near the money; both
+  // come from tail(a) = (2 a/sqrt(pi) - 1 + erfcx(a))/a^2, fitted to 1e-5.
+  constexpr float kB = (float)coef::kTailB;
+  const float Rt = rcp(a + kB);
+  const float yt = fmaf(-2.0f * kB, Rt, 1.0f);
+  constexpr int kDeg = (int)(sizeof(coef::kTail) / sizeof(double)) - 1;
+  float tail = (float)coef::kTail[kDeg];
+#pragma unroll
+  for (int i = kDeg - 1; i >= 0; --i) tail = fmaf(tail, yt, (float)coef::kTail[i]);
+  tail *= Rt;
+  const float om = a * fmaf(-a, tail, kTwoOverSqrtPi);  // 1 - erfcx(a)
+  const float bc = 0.5f * om, cc = fmaf(-0.5f, om, 1.0f);  // bh(s_c); b'(s_c) = b_max/sqrt(2 pi)
+  q.lower = q.bh < bc;
+  q.v = q.lower ? q.bh : q.ch;
+  q.lv = log_of_double(q.lower ? bh : ch);
+  const float vc = q.lower ? bc : cc;
+  const float so = q.lower ? kSqrtPiOver2 * q.ax * tail : fmaf(cc, kSqrt2Pi, sc);
+  const Eval e = eval<true>(q.ax, so, !q.lower);
+  const float bp = kInvSqrt2Pi * exp(-e.g2);  // b'(s_o)/b_max
+  const float vo = e.rho * bp;
+  q.wing = q.v < vo;
+  // end data of the rational cubic: Yl, Yr its values, Dl, Dr its slopes
+  // times the interval, C half its right second derivative times the
+  // interval's square (in a wing all divided by v_o times the slope at 0)
+  float Yl, Yr, Dl, Dr, C, D, x0;
+  if (q.wing) {
+    const float t = 0.5f * so, t2 = t * t, ah = q.ax * e.is;
+    const float z = q.lower ? ah * kInvSqrt3 : t;
+    const float P = 0.5f * erfcx(z * kInvSqrt2);
+    float M = exp(0.5f * (q.lower ? t2 : e.h2));
+    M = q.lower ? M * P * P : M;
+    Yr = M * P * rcp(e.rho) * (q.lower ? (kCl * kSqrt2Pi) * q.ax : 2.0f * kSqrt2Pi);
+    Dr = q.lower ? (2.0f * 1.04719755119659775f) * e.h2 * M : M;
+    const float k = fmaf(-2.0f / 3.0f, e.h2, (2.0f * kInvSqrt2Pi) * z * rcp(P)) + (t2 - 2.0f);
+    C = 0.5f * e.rho * e.is * Dr * (q.lower ? k : e.h2);
+    Yl = 0.0f;
+    Dl = 1.0f;
+    D = vo;
+    x0 = 0.0f;
   } else {
-    D = lower ? bc - bo : bo - bc;
-    xl = lower ? bo : bc;
-    Yl = lower ? so : sc;
-    Yr = lower ? sc : so;
-    const float dc = D * kSqrt2Pi, dd = D * ibo;
-    Dl = lower ? dd : dc;
-    Dr = lower ? dc : dd;
+    D = vc - vo;
+    x0 = vo;
+    Yl = so;
+    Yr = sc;
+    const float sd = q.lower ? D : -D;
+    Dl = sd * rcp(bp);
+    Dr = sd * kSqrt2Pi;
     C = 0.0f;
   }
-  const float S = Yr - Yl;
-  const float gl = S - Dl, gr = Dr - S;
-  // control parameter: reproduces the second derivative at the inner end,
-  // held above the monotone and the convex or concave minimum
-  float r = (C + Dr - Dl) * rcp(lower ? gr : gl);
-  float rmin = -1.0f + 1e-6f;
-  if (Dl * S >= 0.0f && Dr * S >= 0.0f && S != 0.0f) rmin = fmaxf(rmin, (Dl + Dr) * rcp(S));
-  if (gl * gr >= 0.0f) {
-    const float gap = fminf(fabsf(gl), fabsf(gr));
-    rmin = fmaxf(rmin, fabsf(Dr - Dl) * rcp(fmaxf(gap, 1e-30f)));
-  }
-  r = fminf(fmaxf(r, rmin), 1e6f);  // fmaxf drops a NaN
-  const float tau = fminf(fmaxf((q.bh - xl) * rcp(D), 0.0f), 1.0f);
-  const float w = 1.0f - tau;
-  const float den = fmaf((r - 3.0f) * tau, w, 1.0f);
-  const float A = fmaf(Yr * tau, tau, fmaf(fmaf(r, Yr, -Dr) * tau, w, fmaf(r, Yl, Dl) * w * w));
-  const float num = fmaf(tau, A, Yl * w * w * w);
-  if (!wing) {
-    out.s = num * rcp(den);
-    return out;
-  }
-  // invert the map from ln p: R1 p = Phi(z) = (f/cl)^{1/3}, s = |x|/(sqrt3 |z|);
-  // R4 p = f, s = 2 |z|
-  const float lq = log(fmaxf(lower ? A : num * Pz, 1e-30f) * rcp(lower ? den * (kCl * q.ax) : den));
-  const float lnp = lower ? (q.lbh - 0.5f * q.ax + lq) * (1.0f / 3.0f) : fmaf(-0.5f * t, t, lq);
+  // The control parameter reproduces the second derivative at the right end.
+  // Held at 0 or more the denominator stays away from zero; the lower bounds
+  // that would keep the cubic monotone and convex never bind in a region
+  // (the guess is the same to four digits with and without them).
+  const float r = fminf(fmaxf((C + Dr - Dl) * rcp(Dr - (Yr - Yl)), 0.0f), 1e6f);
+  // the position in the interval, measured from the end whose s is the
+  // smaller: near the money the two ends are many decades apart
+  const bool left = q.wing || q.lower;
+  const float from = left ? q.v - x0 : q.bh - bc;
+  const float near = fminf(fmaxf(from * rcp(D), 0.0f), 1.0f);
+  const float far = 1.0f - near;
+  const float tau = left ? near : far, w = left ? far : near, tw = near * far;
+  const float den = fmaf(r - 3.0f, tw, 1.0f);
+  const float A = fmaf(Yr, tau * tau, fmaf(fmaf(r, Yr, -Dr), tw, fmaf(r, Yl, Dl) * (w * w)));
+  if (!q.wing) return fmaf(tau, A, Yl * w * w * w) * rcp(den);
+  // invert the map from ln p: R1 p = Phi(-z) = (f/cl)^{1/3}, s = |x|/(sqrt3 z);
+  // R4 p = Phi(-z) = f, s = 2 z
+  const float lf =
+      fmaf(-0.5f, q.ax, q.lv) + log(fmaxf(A, 1e-30f) * rcp(den * (q.lower ? kCl * q.ax : 2.0f)));
+  const float lnp = q.lower ? lf * (1.0f / 3.0f) : lf;
   const float rr = sqrt(-2.0f * fminf(lnp, -0.69314719f));
   const float pn = fmaf(rr, fmaf(rr, fmaf(rr, (float)coef::kPhiInvGP[3], (float)coef::kPhiInvGP[2]),
                                  (float)coef::kPhiInvGP[1]),
@@ -257,61 +250,59 @@ __host__ __device__ inline Guess initial_guess(const Target& q) {
   const float pd = fmaf(rr, fmaf(rr, fmaf(rr, (float)coef::kPhiInvGQ[3], (float)coef::kPhiInvGQ[2]),
                                  (float)coef::kPhiInvGQ[1]),
                         (float)coef::kPhiInvGQ[0]);
-  const float zi = ((float)coef::kPhiInvGR0 - rr) * pn;  // |z| pd
-  out.s = lower ? q.ax * kInvSqrt3 * pd * rcp(zi) : 2.0f * zi * rcp(pd);
-  return out;
+  const float zn = ((float)coef::kPhiInvGR0 - rr) * pn;  // z = zn/pd
+  return q.lower ? q.ax * kInvSqrt3 * pd * rcp(zn) : 2.0f * zn * rcp(pd);
 }
 
-// One Householder(3) step on the region's objective (fv_lbr.h,
-// householder3_step_t), as ds/s: every quantity is made dimensionless by
-// powers of s, so nothing overflows for small s.
-__host__ __device__ inline float householder3(const Target& q, int region, const Eval& e, float s) {
+// The steps' objectives, each in the logarithm of the distance from its
+// bound or in b itself (fv_lbr.h):
+//   R1 1/ln b, R4 ln(1 - b/b_max), else b.
+// In a wing an iterate near the root has that wing's form; one that does
+// not gives a step that the binary64 iteration finds too large.
+// n = -g/(s g') of the objective g, E2 and E3 its s g''/g' and s^2 g'''/g'.
+// Every quantity is dimensionless, so nothing overflows for small s.
+//
+// One Householder(3) step, as ds/s.
+__host__ __device__ inline float householder3(const Target& q, const Eval& e, float s) {
   const float s2 = 0.25f * s * s;
   const float H = e.h2 - s2;                       // s b''/b'
   const float H3 = fmaf(H, H, -3.0f * e.h2 - s2);  // s^2 b'''/b'
   float n, E2, E3;
-  if (region == kR2 || region == kR3) {
+  if (!q.wing) {
     const float W = kSqrt2Pi * exp(e.g2);  // b_max/b'
     n = (e.comp ? fmaf(-q.ch, W, e.rho) : fmaf(q.bh, W, -e.rho)) * e.is;
     E2 = H;
     E3 = H3;
   } else {
-    const bool lo = region == kR1;
-    // b/b' or (b_max - b)/b', whichever the objective takes
-    float rho = e.rho;
-    if (lo == e.comp) rho = kSqrt2Pi * exp(e.g2) - e.rho;
-    const float rs = rho * e.is;
-    const float w = rcp(rs);  // s b'/b or s b'/(b_max - b)
-    const float lb = log(rho) - e.g2 - kLnSqrt2Pi;  // ln bh or ln(1 - bh)
-    if (lo) {
-      const float u = lb - q.lbh;  // ln(b/beta)
-      const float L = lb - 0.5f * q.ax;
-      const float iL = rcp(L);
-      n = -(L * rcp(q.lbh - 0.5f * q.ax)) * u * rs;
-      E2 = H - w * fmaf(2.0f, iL, 1.0f);
-      E3 = H3 - 3.0f * w * H + 2.0f * w * w - 6.0f * w * (H - w) * iL + 6.0f * w * w * iL * iL;
-    } else {
-      n = -(log(q.ch) - lb) * rs;
-      E2 = H + w;
-      E3 = H3 + 3.0f * w * H + 2.0f * w * w;
-    }
+    const float rs = e.rho * e.is;
+    const float w = q.lower ? -rcp(rs) : rcp(rs);   // -s b'/b or s b'/(b_max - b)
+    const float lb = log(e.rho) - (e.g2 + kLnSqrt2Pi);  // ln(b/b_max) or ln(1 - b/b_max)
+    const float u = lb - q.lv;
+    const float iL = q.lower ? rcp(fmaf(-0.5f, q.ax, lb)) : 0.0f;  // 1/ln b
+    const float k = q.lower ? -1.0f - u * rcp(fmaf(-0.5f, q.ax, q.lv)) : 1.0f;  // -+ln b/ln beta
+    n = u * rs * k;
+    const float wi = w * iL;
+    E2 = fmaf(2.0f, wi, H + w);
+    E3 = fmaf(6.0f * wi, H + w + wi, fmaf(w, fmaf(2.0f, w, 3.0f * H), H3));
   }
   const float d = n * fmaf(0.5f * E2, n, 1.0f) * rcp(fmaf(n, fmaf(E3 * (1.0f / 6.0f), n, E2), 1.0f));
   return fmaxf(d, -0.5f);
 }
 
-// One Halley step as ds/s: on ln b - ln beta in the difference form, on the
-// direct residual in the complement form.
+// One Halley step, as ds/s (in R1 on ln b).
 __host__ __device__ inline float halley(const Target& q, const Eval& e, float s) {
-  const float H = e.h2 - 0.25f * s * s;  // s b''/b'
+  const float H = e.h2 - 0.25f * s * s;
   float n, E2;
-  if (e.comp) {
-    n = fmaf(-q.ch, kSqrt2Pi * exp(e.g2), e.rho) * e.is;
+  if (!q.wing) {
+    const float W = kSqrt2Pi * exp(e.g2);
+    n = (e.comp ? fmaf(-q.ch, W, e.rho) : fmaf(q.bh, W, -e.rho)) * e.is;
     E2 = H;
   } else {
     const float rs = e.rho * e.is;
-    n = (q.lbh - (log(e.rho) - e.g2 - kLnSqrt2Pi)) * rs;
-    E2 = H - rcp(rs);
+    const float w = rcp(rs);
+    const float u = (log(e.rho) - (e.g2 + kLnSqrt2Pi)) - q.lv;
+    n = q.lower ? -u * rs : u * rs;
+    E2 = q.lower ? H - w : H + w;
   }
   return fmaxf(n * rcp(fmaf(0.5f * E2, n, 1.0f)), -0.5f);
 }

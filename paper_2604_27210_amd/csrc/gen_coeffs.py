@@ -39,6 +39,19 @@ definitions evaluated in mpmath (no coefficients are taken from any library):
    ln p, never p itself.  Fitted by iteratively re-weighted linearised
    least squares (relative error ~2e-6, ample for a starting point that
    lands a few percent from the root).
+
+3. The binary32 start's own fits, in the Moebius form of 1 with the
+   derivative weighted beside the value (the evaluator's divided difference
+   is the derivative where the total volatility is small): ``kErfcxS``,
+   degree 4, for the guess's boundary point and wing maps, and ``kErfcxT``,
+   degree 9, for the iteration's steps; and the lower tangent point as
+   s_l = sqrt(pi/2) |x| tail(a), tail(a) = (2 a/sqrt(pi) - 1 + erfcx(a))/a^2,
+   a = sqrt|x| in [0, sqrt(128)], as p(y)/(a + B), y = (a - B)/(a + B).
+
+4. ln m = 2 f + 2 f z S(z), z = f^2, f = (m - 1)/(m + 1), for m in
+   [sqrt(1/2), sqrt(2)], and e^r = 1 + r + r^2/2 + r^3 Q(r) for |r| <= ln2/2:
+   minimax coefficients (Lawson's re-weighted least squares), two and three
+   terms fewer than the Taylor series of the same accuracy.
 """
 from __future__ import annotations
 
@@ -57,6 +70,10 @@ ERFCX_G_B = mp.mpf("3.0")
 ERFCX_G_DEG = 7
 PHI_INV_G_DEG = (3, 3)
 P_MIN = mp.mpf("1e-310")
+ERFCX_S = (mp.mpf("2.75"), 4, mp.mpf("0.05"))  # B, degree, weight of the derivative
+ERFCX_T = (mp.mpf("3.0"), 9, mp.mpf("0.05"))
+TAIL_B = mp.mpf("1.5")
+TAIL_DEG = 4
 
 
 def erfcx(z):
@@ -125,6 +142,88 @@ def check_erfcx(c, B, n=2000):
     return ev, ed
 
 
+def _erfcx_df(y, B):
+    """d/dy of (z + B) erfcx(z)."""
+    z = _erfcx_z(y, B)
+    dz = 2 * (B - ERFCX_Z0) / (1 - y) ** 2
+    return (erfcx(z) + (z + B) * (2 * z * erfcx(z) - 2 / mp.sqrt(mp.pi))) * dz
+
+
+def fit_erfcx_deriv(B, deg, lw):
+    """As fit_erfcx, with the relative error of the derivative weighted by lw
+    (z up to 30, beyond which it plays no part)."""
+    M = 100
+    ys = [mp.cos(mp.pi * (k + mp.mpf(1) / 2) / M) for k in range(M)]
+    rows, rhs = [], []
+    for y in ys:
+        f = _erfcx_f(y, B)
+        rows.append([y ** j / f for j in range(deg + 1)])
+        rhs.append(1)
+        if _erfcx_z(y, B) < 30:
+            d = _erfcx_df(y, B)
+            rows.append([lw * j * y ** max(j - 1, 0) / d for j in range(deg + 1)])
+            rhs.append(lw)
+    c = _lstsq(rows, rhs)
+    return [c[j] for j in range(deg + 1)]
+
+
+def tail(a):
+    if a < mp.mpf("1e-8"):
+        return 1 - a * 4 / (3 * mp.sqrt(mp.pi)) + a * a / 2
+    return (2 * a / mp.sqrt(mp.pi) - 1 + erfcx(a)) / a ** 2
+
+
+def fit_tail():
+    top = mp.mpf("11.35")
+    ymax = (top - TAIL_B) / (top + TAIL_B)
+    M = 60
+    rows, rhs, ys = [], [], []
+    for k in range(M):
+        y = (mp.cos(mp.pi * (k + mp.mpf(1) / 2) / M) + 1) / 2 * (ymax + 1) - 1
+        a = TAIL_B * (1 + y) / (1 - y)
+        f = tail(a) * (a + TAIL_B)
+        rows.append([y ** j / f for j in range(TAIL_DEG + 1)])
+        rhs.append(1)
+    c = _lstsq(rows, rhs)
+    c = [c[j] for j in range(TAIL_DEG + 1)]
+    err = max(abs(mp.fsum(v * b for v, b in zip(c, r)) - 1) for r in rows)
+    return c, err
+
+
+def minimax(xs, basis, target, weight, iters=30):
+    """Lawson's algorithm: least squares re-weighted by the error itself."""
+    lam = [mp.mpf(1)] * len(xs)
+    for _ in range(iters):
+        rows = [[b * weight(x) * mp.sqrt(l) for b in basis(x)] for x, l in zip(xs, lam)]
+        rhs = [target(x) * weight(x) * mp.sqrt(l) for x, l in zip(xs, lam)]
+        sol = _lstsq(rows, rhs)
+        c = [sol[j] for j in range(len(rows[0]))]
+        e = [abs(mp.fsum(v * b for v, b in zip(c, basis(x))) - target(x)) * weight(x) for x in xs]
+        tot = mp.fsum(l * v for l, v in zip(lam, e))
+        lam = [l * v / tot * len(xs) for l, v in zip(lam, e)]
+    return c, max(e)
+
+
+def _nodes(a, b, n):
+    return [(a + b) / 2 + (b - a) / 2 * mp.cos(mp.pi * (k + mp.mpf(1) / 2) / n) for k in range(n)]
+
+
+def fit_atanh(deg=6):
+    """S(z) of ln m = 2 f (1 + z S(z)); the error is relative to ln m."""
+    z1 = ((mp.sqrt(2) - 1) / (mp.sqrt(2) + 1)) ** 2
+    S = lambda z: (mp.atanh(mp.sqrt(z)) / mp.sqrt(z) - 1) / z
+    return minimax(_nodes(mp.mpf("1e-10"), z1, 60), lambda z: [z ** j for j in range(deg + 1)], S,
+                   lambda z: z)
+
+
+def fit_exp(deg=11):
+    """Q(r) of e^r = 1 + r + r^2/2 + r^3 Q(r); the error is relative to e^r."""
+    top = mp.log(2) / 2 * mp.mpf("1.0005")
+    Q = lambda r: (mp.exp(r) - 1 - r - r * r / 2) / r ** 3
+    return minimax(_nodes(-top, top, 80), lambda r: [r ** j for j in range(deg - 2)], Q,
+                   lambda r: abs(r) ** 3 / mp.exp(r))
+
+
 def fit_rational(ts, fs, m, n, iters=4):
     qprev = [mp.mpf(1)] * len(ts)
     for _ in range(iters):
@@ -182,6 +281,15 @@ def main():
     eg = fit_erfcx(ERFCX_G_B, ERFCX_G_DEG)
     g_err, g_deriv = check_erfcx(eg, ERFCX_G_B)
     gP, gQ, gr0, gerr = fit_phi_inv()
+    es = fit_erfcx_deriv(*ERFCX_S)
+    s_err, s_deriv = check_erfcx(es, ERFCX_S[0], 400)
+    et = fit_erfcx_deriv(*ERFCX_T)
+    t_err, t_deriv = check_erfcx(et, ERFCX_T[0], 400)
+    tl, tl_err = fit_tail()
+    mp.mp.dps = 40
+    at, at_err = fit_atanh()
+    ex, ex_err = fit_exp()
+    mp.mp.dps = 30
     n3 = lambda v: mp.nstr(v, 3)
     out = [
         "// Generated by gen_coeffs.py -- do not edit by hand.\n",
@@ -195,6 +303,10 @@ def main():
         % (n3(g_err), n3(g_deriv)),
         "// Inverse normal CDF on (0, 1/2]: Phi^{-1}(p) = (r - r0) P(r)/Q(r),\n",
         "// r = sqrt(-2 ln p), r0 = sqrt(2 ln 2), [3/3]; max rel err %s\n" % n3(gerr),
+        "// binary32 start, erfcx of the guess: max rel err %s, derivative %s;\n"
+        % (n3(s_err), n3(s_deriv)),
+        "// of its steps: %s, %s; tangent point's tail: %s\n" % (n3(t_err), n3(t_deriv), n3(tl_err)),
+        "// atanh series: %s of the logarithm; exponential: %s\n" % (n3(at_err), n3(ex_err)),
         "#pragma once\n\nnamespace fv {\nnamespace coef {\n\n",
         "constexpr double kErfcxZ0 = %s;\n" % mp.nstr(ERFCX_Z0, 20),
         "constexpr double kErfcxB = %s;\n" % mp.nstr(ERFCX_B, 20),
@@ -209,6 +321,15 @@ def main():
         "constexpr double kPhiInvGR0 = %s;\n" % mp.nstr(gr0, 20),
         _arr("kPhiInvGP", gP),
         _arr("kPhiInvGQ", gQ),
+        "\nconstexpr double kErfcxSB = %s;\n" % mp.nstr(ERFCX_S[0], 20),
+        _arr("kErfcxS", es),
+        "\nconstexpr double kErfcxTB = %s;\n" % mp.nstr(ERFCX_T[0], 20),
+        _arr("kErfcxT", et),
+        "\nconstexpr double kTailB = %s;\n" % mp.nstr(TAIL_B, 20),
+        _arr("kTail", tl),
+        "\n",
+        _arr("kAtanh", at),
+        _arr("kExpQ", ex),
         "\n}  // namespace coef\n}  // namespace fv\n",
     ]
     path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "fv_coeffs.h")
