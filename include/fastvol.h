@@ -320,8 +320,8 @@ int fv_get_halley_steps(void);
  * per quote, 16 for binary32; the ragged-chain kernel, which takes two
  * 64-quote slices per wave and ignores quotes_per_thread, 64 bytes per
  * thread) must fit in 64 KiB of LDS
- * (FV_E_INVALID_ARG otherwise; the shape in force is kept).  The
- * binary64 LBR and Halley kernels take one quote per thread at any
+ * (FV_E_INVALID_ARG otherwise; the shape in force is kept).  All
+ * binary64 kernels but the ragged one take one quote per thread at any
  * quotes_per_thread.
  * fv_get_launch reads the configured shape.  The shape applies as set to
  * batches large enough to fill the device; a batch that would give fewer

@@ -90,9 +90,10 @@ __device__ __forceinline__ int ldflag(const KQuotes& q, int64_t i) {
 // and back, two instructions a value).
 template <class A>
 __device__ __forceinline__ const A* late_args() {
-  auto p = __builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return (const A*)p;
+  uint32_t zero;
+  asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+  return (const A*)((const __attribute__((address_space(4))) char*)
+                        __builtin_amdgcn_kernarg_segment_ptr() + zero);
 }
 
 // A pointer read that way, as one to global memory (the compiler knows that of
@@ -106,14 +107,21 @@ struct GreekOut {
   double* p[5];
   int any;
 };
-// (entry b + t, split as for ld)
+// Entry b + t (split as for ld) of each output row that is wanted.
+template <int N>
+__device__ __forceinline__ void store_rows(double* const* rows, int64_t b, unsigned t,
+                                           const double (&v)[N]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    if (double* p = rows[j]) (global_ptr(p) + b)[t] = v[j];
+}
 __device__ __forceinline__ void store_greeks(const GreekOut& g, int64_t b, unsigned t,
                                              const Greeks& gr) {
-  if (g.p[0]) (global_ptr(g.p[0]) + b)[t] = gr.delta;
-  if (g.p[1]) (global_ptr(g.p[1]) + b)[t] = gr.gamma;
-  if (g.p[2]) (global_ptr(g.p[2]) + b)[t] = gr.vega;
-  if (g.p[3]) (global_ptr(g.p[3]) + b)[t] = gr.theta;
-  if (g.p[4]) (global_ptr(g.p[4]) + b)[t] = gr.rho;
+  store_rows<5>(g.p, b, t, {gr.delta, gr.gamma, gr.vega, gr.theta, gr.rho});
+}
+__device__ __forceinline__ Greeks no_greeks() {
+  const double nan = __builtin_nan("");
+  return Greeks{nan, nan, nan, nan, nan};
 }
 
 // Largest workgroup the kernels are compiled for (8 waves).
@@ -144,35 +152,92 @@ constexpr int kHalleySteps = 8;  // the paper's count; the default of fv_set_hal
 constexpr int kMaxHalleySteps = 64;
 constexpr double kBisectTol = 1e-13;
 
-// ------------------------------------------------------------- price
-template <int MODEL>
-__global__ __launch_bounds__(kMaxBlock) void k_price(KQuotes q, fv_arg sigma, double* __restrict__ out, int qpt) {
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    if (i >= q.n) return;
-    const double fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i), r = ld(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    const double sg = ld(sigma, i);
-    const int th = ldflag(q, i);
-    double p = __builtin_nan("");
-    if (fv::finite_d(fs) && fv::finite_d(K) && fv::finite_d(T) && fv::finite_d(r) &&
-        fv::finite_d(qy) && fv::finite_d(sg) && fs > 0.0 && K > 0.0 && T > 0.0 &&
-        sg >= 0.0 && (th == 1 || th == -1)) {
-      const double F = fv::forward_of(MODEL, fs, T, r, qy);
-      const double D = fv::fexp_prod(-r, T);
-      p = fv::price_at(F, K, D, sg, fv::sqrt_pos(T), th);
-    }
-    out[i] = p;
-  }
-}
-
 // A value the compiler cannot follow: what is loaded or computed from it is
 // loaded or computed again, not kept in registers from an earlier use.
 template <class V>
 __device__ __forceinline__ V opaque(V i) {
   asm volatile("" : "+v"(i));
   return i;
+}
+
+// The closed-form kernels below (price, Greeks, adjoints) are bound by
+// memory: one evaluation and three exponentials a quote (about 230 vector
+// instructions, 340 to 560 with the general forms) against 57 to 113 bytes.
+// 5M BSM prices: 57 to 60 us (70 before; 55 at the 5.2 TB/s of a copy), 2M
+// Black-76 Greeks 32 to 36 us (46; 31), the adjoint of 1M BSM quotes 20.5 us
+// (27; 22, part of it served from cache).  One quote per thread, every field
+// on a scalar base.  Quotes outside the scaled forms' domain take the general
+// ones, read again from memory.
+
+// Inputs of a quote at a volatility.
+struct SigmaQuote {
+  double fs, K, T, r, q, sigma;
+  int th;
+};
+// Arguments of the closed-form kernels: `up` is the upstream gradient of the
+// adjoints.
+struct FormArgs {
+  KQuotes q;
+  fv_arg sigma;
+  const double* up;
+  double* out[6];
+};
+
+template <int MODEL, bool ARR>
+__device__ __forceinline__ SigmaQuote load_quote(const FormArgs& a, int64_t b, unsigned t) {
+  SigmaQuote v;
+  v.fs = ld<ARR>(a.q.fs, b, t);
+  v.K = ld<ARR>(a.q.K, b, t);
+  v.T = ld<ARR>(a.q.T, b, t);
+  v.r = ld<ARR>(a.q.r, b, t);
+  v.q = MODEL == fv::kBlackScholesMerton ? ld<ARR>(a.q.q, b, t) : 0.0;
+  v.sigma = ld<ARR>(a.sigma, b, t);
+  v.th = ldflag<ARR>(a.q, b, t);
+  return v;
+}
+
+// The pricing domain (sigma may be zero for a price).
+__device__ __forceinline__ bool price_domain(const SigmaQuote& v) {
+  return fv::finite_d(v.fs) && fv::finite_d(v.K) && fv::finite_d(v.T) && fv::finite_d(v.r) &&
+         fv::finite_d(v.q) && fv::finite_d(v.sigma) && v.fs > 0.0 && v.K > 0.0 && v.T > 0.0 &&
+         v.sigma >= 0.0 && (v.th == 1 || v.th == -1);
+}
+
+template <int MODEL>
+__device__ __forceinline__ SigmaQuote load_late(int64_t i) {
+  const FormArgs* a = late_args<FormArgs>();
+  i = opaque(i);
+  SigmaQuote v;
+  v.fs = ld(a->q.fs, i);
+  v.K = ld(a->q.K, i);
+  v.T = ld(a->q.T, i);
+  v.r = ld(a->q.r, i);
+  v.q = MODEL == fv::kBlackScholesMerton ? ld(a->q.q, i) : 0.0;
+  v.sigma = ld(a->sigma, i);
+  v.th = ldflag(a->q, i);
+  return v;
+}
+
+// ------------------------------------------------------------- price
+template <int MODEL, bool ARR>
+__global__ __launch_bounds__(kMaxBlock) void k_price(FormArgs args) {
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x;
+  const unsigned t = threadIdx.x;
+  if ((int64_t)t >= args.q.n - b) return;
+  const SigmaQuote v = load_quote<MODEL, ARR>(args, b, t);
+  fv::ClosedForm c;
+  const bool fast = fv::closed_form(MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, &c);
+  double p = c.D * c.t.P;
+  if (__builtin_expect(!fast, 0)) {
+    const SigmaQuote w = load_late<MODEL>(b + t);
+    p = __builtin_nan("");
+    if (price_domain(w)) {
+      const double F = fv::forward_of(MODEL, w.fs, w.T, w.r, w.q);
+      const double D = fv::fexp_prod(-w.r, w.T);
+      p = fv::price_at(F, w.K, D, w.sigma, fv::sqrt_pos(w.T), w.th);
+    }
+  }
+  (global_ptr(late_args<FormArgs>()->out[0]) + b)[t] = p;
 }
 
 // The general solve of quote i, from its inputs in memory: neither they nor
@@ -195,11 +260,30 @@ struct IvArgs {
   GreekOut g;
 };
 
+// The fused Greeks of a quote of status st at its volatility sg (s in total),
+// NaN where it has none.
+template <int MODEL>
+__device__ __forceinline__ Greeks greeks_solved(uint8_t st, bool general,
+                                                const fv::ScaledQuote& sq, double s, double sg,
+                                                double P, double fs, double K, double T, double r,
+                                                double qy, int th) {
+  fv::ClosedForm c;
+  const bool fast = !general && fv::closed_form_at(MODEL, sq, s, fs, K, T, r, qy, th, &c);
+  Greeks gr = fv::greeks_of(c, MODEL, fs, T, r, qy, sg, th, P);
+  if (__builtin_expect(!fast, 0)) {
+    gr = no_greeks();
+    if (st == fv::kQOk)
+      gr = fv::greeks_at(MODEL, opaque(fs), opaque(K), opaque(T), opaque(r), opaque(qy), sg, th,
+                         sq.F, sq.D, P);
+  }
+  return st == fv::kQOk ? gr : no_greeks();
+}
+
 // ------------------------------------------------------------- IV: LBR
 // Bound by the vector ALU's issue rate: about 570 vector instructions per
 // quote, every side of the guess a mixed wave takes included (1,157 with the
 // guess and the first step in binary64).  10M wide-wing BSM quotes: 155 us
-// (355 with those), 1M BS quotes with the five Greeks: 27.5 us (54).
+// (355 with those), 1M BS quotes with the five Greeks: 26.5 us (54).
 // One quote per thread: with a loop over several the compiler keeps the
 // polynomials' constants in registers across the whole solve, 110 VGPRs in
 // place of 55, and the book took 220 us where it then took 190.
@@ -218,8 +302,8 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(IvArgs 
   uint8_t st = sq.status;
   double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
   bool general = sq.general;
+  double s = 0.0;
   if (st == fv::kQOk && !general) {
-    double s;
     general = !fv::lbr_solve_scaled(sq.x, sq.bh, sq.ch, &s);
     sg = s * sq.isqrtT;
   }
@@ -231,15 +315,8 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(IvArgs 
   (global_ptr(out->sig_out) + b)[t] = sg;
   if (uint8_t* st_out = out->st_out) (global_ptr(st_out) + b)[t] = st;
   if (GREEKS) {
-    Greeks gr;
-    if (st == fv::kQOk) {
-      gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, sq.F, sq.D, P);
-    } else {
-      const double nan = __builtin_nan("");
-      gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
-    }
-    const GreekOut& g = out->g;
-    store_greeks(g, b, t, gr);
+    const Greeks gr = greeks_solved<MODEL>(st, general, sq, s, sg, P, fs, K, T, r, qy, th);
+    store_greeks(out->g, b, t, gr);
   }
 }
 
@@ -367,15 +444,9 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(I
       (global_ptr(out->sig_out) + b)[t] = sg;
       if (uint8_t* st_out = out->st_out) (global_ptr(st_out) + b)[t] = st;
       if (GREEKS) {
-        Greeks gr;
-        if (st == fv::kQOk) {
-          gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, sq.F, sq.D, P);
-        } else {
-          const double nan = __builtin_nan("");
-          gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
-        }
-        const GreekOut& g = out->g;
-        store_greeks(g, b, t, gr);
+        const Greeks gr =
+            greeks_solved<MODEL>(st, sq.general, sq, hs.s, sg, P, fs, K, T, r, qy, th);
+        store_greeks(out->g, b, t, gr);
       }
     }
   }
@@ -395,8 +466,10 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(I
     }
   }
   __syncthreads();
-  // bisection fallback over the packed queue: every lane of a wave works
-  const int m = qcount;
+  // Bisection fallback over the packed queue: every lane of a wave works.  An
+  // empty queue, the rule, ends here, ahead of what the loop sets up.
+  const int m = __builtin_amdgcn_readfirstlane(qcount);
+  if (m == 0) return;
   for (int j = threadIdx.x; j < m; j += blockDim.x) {
     const int64_t iq = queue[j].i;
     const auto* late = late_args<IvArgs>();
@@ -416,7 +489,6 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(I
   }
 }
 
-// ------------------------------------------------------------- Greeks
 // ------------------------------------------------------------- IV: Halley, binary32
 struct KQuotes32 {
   int64_t n;
@@ -487,7 +559,8 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4))) 
     }
   }
   __syncthreads();
-  const int m = qcount;
+  const int m = __builtin_amdgcn_readfirstlane(qcount);
+  if (m == 0) return;
   for (int j = threadIdx.x; j < m; j += blockDim.x) {
     const int64_t i = queue[j].i;
     const float P = ld32(q.price, i), fs = ld32(q.fs, i), K = ld32(q.K, i), T = ld32(q.T, i),
@@ -501,99 +574,89 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4))) 
   }
 }
 
-template <int MODEL>
-__global__ __launch_bounds__(kMaxBlock) void k_greeks(KQuotes q, fv_arg sigma, GreekOut g, int qpt) {
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    if (i >= q.n) return;
-    const double fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i), r = ld(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    const double sg = ld(sigma, i);
-    const int th = ldflag(q, i);
-    Greeks gr;
-    const double nan = __builtin_nan("");
-    gr.delta = gr.gamma = gr.vega = gr.theta = gr.rho = nan;
-    if (fv::finite_d(fs) && fv::finite_d(K) && fv::finite_d(T) && fv::finite_d(r) &&
-        fv::finite_d(qy) && fv::finite_d(sg) && fs > 0.0 && K > 0.0 && T > 0.0 && sg > 0.0 &&
-        (th == 1 || th == -1)) {
-      const double F = fv::forward_of(MODEL, fs, T, r, qy);
-      const double D = fv::fexp_prod(-r, T);
-      const double P = fv::price_at(F, K, D, sg, fv::sqrt_pos(T), th);
-      gr = fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, F, D, P);
+// ------------------------------------------------------------- Greeks
+template <int MODEL, bool ARR>
+__global__ __launch_bounds__(kMaxBlock) void k_greeks(FormArgs args) {
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x;
+  const unsigned t = threadIdx.x;
+  if ((int64_t)t >= args.q.n - b) return;
+  const SigmaQuote v = load_quote<MODEL, ARR>(args, b, t);
+  fv::ClosedForm c;
+  const bool fast = fv::closed_form(MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, &c);
+  Greeks gr = fv::greeks_of(c, MODEL, v.fs, v.T, v.r, v.q, v.sigma, v.th, c.D * c.t.P);
+  if (__builtin_expect(!fast, 0)) {
+    const SigmaQuote w = load_late<MODEL>(b + t);
+    gr = no_greeks();
+    if (price_domain(w) && w.sigma > 0.0) {
+      const double F = fv::forward_of(MODEL, w.fs, w.T, w.r, w.q);
+      const double D = fv::fexp_prod(-w.r, w.T);
+      const double P = fv::price_at(F, w.K, D, w.sigma, fv::sqrt_pos(w.T), w.th);
+      gr = fv::greeks_at(MODEL, w.fs, w.K, w.T, w.r, w.q, w.sigma, w.th, F, D, P);
     }
-    store_greeks(g, i, 0, gr);
   }
+  const FormArgs* late = late_args<FormArgs>();
+  store_rows<5>(late->out, b, t, {gr.delta, gr.gamma, gr.vega, gr.theta, gr.rho});
 }
 
 // ------------------------------------------------------------- backward
-struct BwdOut {
-  double* p[6];
-};
-
-template <int MODEL>
-__global__ __launch_bounds__(kMaxBlock) void k_iv_backward(KQuotes q, const double* __restrict__ sigma,
-                              const double* __restrict__ gsig, BwdOut o, int qpt) {
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    if (i >= q.n) return;
-    const double P = ld(q.price, i), fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i),
-                 r = ld(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    const double sg = sigma[i], gs = gsig[i];
-    const int th = ldflag(q, i);
-    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (fv::finite_d(sg) && sg > 0.0 && fv::finite_d(fs) && fv::finite_d(K) &&
-        fv::finite_d(T) && fs > 0.0 && K > 0.0 && T > 0.0) {
-      const IvGrad d = fv::iv_gradient(MODEL, fs, K, T, r, qy, sg, th, P);
-      if (fv::finite_d(d.dP)) {
-        v[0] = gs * d.dP;
-        v[1] = gs * d.dfs;
-        v[2] = gs * d.dK;
-        v[3] = gs * d.dT;
-        v[4] = gs * d.dr;
-        v[5] = gs * d.dq;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 6; ++j)
-      if (o.p[j]) o.p[j][i] = v[j];
+template <int MODEL, bool ARR>
+__global__ __launch_bounds__(kMaxBlock) void k_iv_backward(FormArgs args) {
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x;
+  const unsigned t = threadIdx.x;
+  if ((int64_t)t >= args.q.n - b) return;
+  const SigmaQuote v = load_quote<MODEL, ARR>(args, b, t);
+  const double gs = (args.up + b)[t];
+  // the price enters Black-76's theta alone
+  const double P = MODEL == fv::kBlack76 ? ld<ARR>(args.q.price, b, t) : 0.0;
+  fv::ClosedForm c;
+  const bool fast = fv::closed_form(MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, &c);
+  const fv::PricePartials pp =
+      fv::partials_of(c, MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, P);
+  IvGrad d = fv::implicit_gradient(pp);
+  bool ok = true;
+  if (__builtin_expect(!fast, 0)) {
+    const SigmaQuote w = load_late<MODEL>(b + t);
+    ok = fv::finite_d(w.sigma) && w.sigma > 0.0 && fv::finite_d(w.fs) && fv::finite_d(w.K) &&
+         fv::finite_d(w.T) && w.fs > 0.0 && w.K > 0.0 && w.T > 0.0;
+    if (ok)
+      d = fv::iv_gradient(MODEL, w.fs, w.K, w.T, w.r, w.q, w.sigma, w.th,
+                          ld(late_args<FormArgs>()->q.price, b + t));
   }
+  const double g = ok && fv::finite_d(d.dP) ? gs : 0.0;
+  const FormArgs* late = late_args<FormArgs>();
+  const bool z = !(ok && fv::finite_d(d.dP));
+  store_rows<6>(late->out, b, t,
+                {z ? 0.0 : g * d.dP, z ? 0.0 : g * d.dfs, z ? 0.0 : g * d.dK, z ? 0.0 : g * d.dT,
+                 z ? 0.0 : g * d.dr, z ? 0.0 : g * d.dq});
 }
 
 // ------------------------------------------------------------- price adjoint
-template <int MODEL>
-__global__ __launch_bounds__(kMaxBlock) void k_price_backward(KQuotes q, fv_arg sigma,
-                                                              const double* __restrict__ gp,
-                                                              BwdOut o, int qpt) {
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    if (i >= q.n) return;
-    const double fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i), r = ld(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    const double sg = ld(sigma, i), g = gp[i];
-    const int th = ldflag(q, i);
-    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (fv::finite_d(fs) && fv::finite_d(K) && fv::finite_d(T) && fv::finite_d(r) &&
-        fv::finite_d(qy) && fv::finite_d(sg) && fs > 0.0 && K > 0.0 && T > 0.0 && sg > 0.0 &&
-        (th == 1 || th == -1)) {
-      const double F = fv::forward_of(MODEL, fs, T, r, qy);
-      const double D = fv::fexp_prod(-r, T);
-      const double P = fv::price_at(F, K, D, sg, fv::sqrt_pos(T), th);
-      const fv::PricePartials pp = fv::price_partials(MODEL, fs, K, T, r, qy, sg, th, F, D, P);
-      v[0] = g * pp.dfs;
-      v[1] = g * pp.dK;
-      v[2] = g * pp.dT;
-      v[3] = g * pp.dr;
-      v[4] = g * pp.dq;
-      v[5] = g * pp.dsigma;
+template <int MODEL, bool ARR>
+__global__ __launch_bounds__(kMaxBlock) void k_price_backward(FormArgs args) {
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x;
+  const unsigned t = threadIdx.x;
+  if ((int64_t)t >= args.q.n - b) return;
+  const SigmaQuote v = load_quote<MODEL, ARR>(args, b, t);
+  const double g = (args.up + b)[t];
+  fv::ClosedForm c;
+  const bool fast = fv::closed_form(MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, &c);
+  fv::PricePartials pp =
+      fv::partials_of(c, MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, c.D * c.t.P);
+  bool ok = true;
+  if (__builtin_expect(!fast, 0)) {
+    const SigmaQuote w = load_late<MODEL>(b + t);
+    ok = price_domain(w) && w.sigma > 0.0;
+    if (ok) {
+      const double F = fv::forward_of(MODEL, w.fs, w.T, w.r, w.q);
+      const double D = fv::fexp_prod(-w.r, w.T);
+      const double P = fv::price_at(F, w.K, D, w.sigma, fv::sqrt_pos(w.T), w.th);
+      pp = fv::price_partials(MODEL, w.fs, w.K, w.T, w.r, w.q, w.sigma, w.th, F, D, P);
     }
-#pragma unroll
-    for (int j = 0; j < 6; ++j)
-      if (o.p[j]) o.p[j][i] = v[j];
   }
+  const FormArgs* late = late_args<FormArgs>();
+  store_rows<6>(late->out, b, t,
+                {ok ? g * pp.dfs : 0.0, ok ? g * pp.dK : 0.0, ok ? g * pp.dT : 0.0,
+                 ok ? g * pp.dr : 0.0, ok ? g * pp.dq : 0.0, ok ? g * pp.dsigma : 0.0});
 }
 
 // ------------------------------------------------------------- chains
@@ -713,7 +776,8 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
   if (!kHalley) return;
   __syncthreads();
   // bisection fallback over the packed queue: every lane of a wave works
-  const int nq = qcount;
+  const int nq = __builtin_amdgcn_readfirstlane(qcount);
+  if (nq == 0) return;
   for (int j = threadIdx.x; j < nq; j += blockDim.x) {
     const int64_t iq = queue[j].i;
     const int64_t mq = queue[j].m, cq = queue[j].cc;
@@ -1072,20 +1136,27 @@ int fv_get_launch(int kernel, int* block, int* qpt) {
   return FV_OK;
 }
 
+// Launches the closed-form kernel KERN of `model` on `args` with the shape of
+// family FAMILY, one quote per thread.
+#define FV_LAUNCH_FORM(KERN, FAMILY)                                                      \
+  do {                                                                                    \
+    const LaunchShape sh{shape_for(FAMILY, model, q->n).block, 1};                        \
+    const dim3 grid = grid_for(q->n, sh), block(sh.block);                                \
+    hipStream_t s = (hipStream_t)stream;                                                  \
+    switch (model) {                                                                      \
+      case FV_MODEL_BLACK76: KERN<0, false><<<grid, block, 0, s>>>(args); break;          \
+      case FV_MODEL_BLACK_SCHOLES: KERN<1, false><<<grid, block, 0, s>>>(args); break;    \
+      default: KERN<2, false><<<grid, block, 0, s>>>(args); break;                        \
+    }                                                                                     \
+  } while (0)
+
 int fv_price(int model, const fv_quotes* q, fv_arg sigma, double* price_out, void* stream) {
   int rc = check_quotes(model, q);
   if (rc) return rc;
   if (q->n == 0) return FV_OK;
   if (!price_out) return fail(FV_E_INVALID_ARG, "price_out is NULL");
-  const LaunchShape sh = shape_for(FV_KERNEL_PRICE, model, q->n);
-  const KQuotes k = to_k(q);
-  hipStream_t s = (hipStream_t)stream;
-  const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  switch (model) {
-    case FV_MODEL_BLACK76: k_price<0><<<grid, block, 0, s>>>(k, sigma, price_out, sh.qpt); break;
-    case FV_MODEL_BLACK_SCHOLES: k_price<1><<<grid, block, 0, s>>>(k, sigma, price_out, sh.qpt); break;
-    default: k_price<2><<<grid, block, 0, s>>>(k, sigma, price_out, sh.qpt); break;
-  }
+  const FormArgs args = {to_k(q), sigma, nullptr, {price_out}};
+  FV_LAUNCH_FORM(k_price, FV_KERNEL_PRICE);
   return launched("fv_price");
 }
 
@@ -1182,19 +1253,9 @@ int fv_greeks(int model, const fv_quotes* q, fv_arg sigma, double* delta, double
   int rc = check_quotes(model, q);
   if (rc) return rc;
   if (q->n == 0) return FV_OK;
-  GreekOut g;
-  g.p[0] = delta; g.p[1] = gamma; g.p[2] = vega; g.p[3] = theta; g.p[4] = rho;
-  g.any = 1;
   if (!delta && !gamma && !vega && !theta && !rho) return FV_OK;
-  const LaunchShape sh = shape_for(FV_KERNEL_GREEKS, model, q->n);
-  const KQuotes k = to_k(q);
-  hipStream_t s = (hipStream_t)stream;
-  const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  switch (model) {
-    case FV_MODEL_BLACK76: k_greeks<0><<<grid, block, 0, s>>>(k, sigma, g, sh.qpt); break;
-    case FV_MODEL_BLACK_SCHOLES: k_greeks<1><<<grid, block, 0, s>>>(k, sigma, g, sh.qpt); break;
-    default: k_greeks<2><<<grid, block, 0, s>>>(k, sigma, g, sh.qpt); break;
-  }
+  const FormArgs args = {to_k(q), sigma, nullptr, {delta, gamma, vega, theta, rho}};
+  FV_LAUNCH_FORM(k_greeks, FV_KERNEL_GREEKS);
   return launched("fv_greeks");
 }
 
@@ -1205,17 +1266,8 @@ int fv_implied_vol_backward(int model, const fv_quotes* q, const double* sigma,
   if (rc) return rc;
   if (q->n == 0) return FV_OK;
   if (!sigma || !grad_sigma) return fail(FV_E_INVALID_ARG, "sigma or grad_sigma is NULL");
-  BwdOut o;
-  o.p[0] = g_price; o.p[1] = g_fs; o.p[2] = g_K; o.p[3] = g_T; o.p[4] = g_r; o.p[5] = g_q;
-  const LaunchShape sh = shape_for(FV_KERNEL_BACKWARD, model, q->n);
-  const KQuotes k = to_k(q);
-  hipStream_t s = (hipStream_t)stream;
-  const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  switch (model) {
-    case FV_MODEL_BLACK76: k_iv_backward<0><<<grid, block, 0, s>>>(k, sigma, grad_sigma, o, sh.qpt); break;
-    case FV_MODEL_BLACK_SCHOLES: k_iv_backward<1><<<grid, block, 0, s>>>(k, sigma, grad_sigma, o, sh.qpt); break;
-    default: k_iv_backward<2><<<grid, block, 0, s>>>(k, sigma, grad_sigma, o, sh.qpt); break;
-  }
+  const FormArgs args = {to_k(q), fv_arg{sigma, 0.0}, grad_sigma, {g_price, g_fs, g_K, g_T, g_r, g_q}};
+  FV_LAUNCH_FORM(k_iv_backward, FV_KERNEL_BACKWARD);
   return launched("fv_implied_vol_backward");
 }
 
@@ -1226,17 +1278,8 @@ int fv_price_backward(int model, const fv_quotes* q, fv_arg sigma, const double*
   if (rc) return rc;
   if (q->n == 0) return FV_OK;
   if (!grad_price) return fail(FV_E_INVALID_ARG, "grad_price is NULL");
-  BwdOut o;
-  o.p[0] = g_fs; o.p[1] = g_K; o.p[2] = g_T; o.p[3] = g_r; o.p[4] = g_q; o.p[5] = g_sigma;
-  const LaunchShape sh = shape_for(FV_KERNEL_BACKWARD, model, q->n);
-  const KQuotes k = to_k(q);
-  hipStream_t s = (hipStream_t)stream;
-  const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  switch (model) {
-    case FV_MODEL_BLACK76: k_price_backward<0><<<grid, block, 0, s>>>(k, sigma, grad_price, o, sh.qpt); break;
-    case FV_MODEL_BLACK_SCHOLES: k_price_backward<1><<<grid, block, 0, s>>>(k, sigma, grad_price, o, sh.qpt); break;
-    default: k_price_backward<2><<<grid, block, 0, s>>>(k, sigma, grad_price, o, sh.qpt); break;
-  }
+  const FormArgs args = {to_k(q), sigma, grad_price, {g_fs, g_K, g_T, g_r, g_q, g_sigma}};
+  FV_LAUNCH_FORM(k_price_backward, FV_KERNEL_BACKWARD);
   return launched("fv_price_backward");
 }
 

@@ -345,6 +345,7 @@ __host__ __device__ __attribute__((always_inline)) inline LbrResult lbr_solve(
 // for |x| <= 128 and 1e-24 < s < 1e3, which hold here, it stays in range.
 struct ScaledEval {
   double rho, g, h, is;
+  double e2;  // erfcx(q2)
   bool comp;
 };
 
@@ -368,11 +369,12 @@ __host__ __device__ __attribute__((always_inline)) inline ScaledEval scaled_eval
     D = fma(D, y1, B);
     B = fma(B, y2, coef::kErfcx[i]);
   }
+  e.e2 = B * R2;
   if (!e.comp) {
     e.rho = kSqrtPi * t * R12 * fma(-k2BZ * R1, D, B);
   } else {
     const double A = fma(y1 - y2, D, B);
-    e.rho = kSqrtPiOver2 * fma(A, R1, B * R2);
+    e.rho = kSqrtPiOver2 * fma(A, R1, e.e2);
   }
   return e;
 }

@@ -109,7 +109,7 @@ __host__ __device__ inline double forward_of(int model, double fs, double T, dou
 // ln(F/K) for positive finite F and K
 __host__ __device__ inline double log_moneyness(double F, double K) { return log_ratio(F, K); }
 
-__host__ __device__ inline Reduced reduce_quote(int model, double price, double fs, double K,
+__host__ __device__ __attribute__((always_inline)) inline Reduced reduce_quote(int model, double price, double fs, double K,
                                                 double T, double r, double q, int theta) {
   // One exit: every lane computes every field and the status is decided at
   // the end, in the order of the checks below (invalid input first).  The
@@ -298,7 +298,7 @@ __host__ __device__ inline Greeks greeks_from(const BsTerms& c, int model, doubl
   return g;
 }
 
-__host__ __device__ inline Greeks greeks_at(int model, double fs, double K, double T, double r,
+__host__ __device__ __attribute__((always_inline)) inline Greeks greeks_at(int model, double fs, double K, double T, double r,
                                             double q, double sigma, int theta, double F,
                                             double D, double price) {
   return greeks_from(bs_terms(F, K, D, sigma, T, theta), model, fs, K, T, r, q, sigma, theta, F,
@@ -313,7 +313,7 @@ struct PricePartials {
   double dfs, dK, dT, dr, dq, dsigma;
 };
 
-__host__ __device__ inline PricePartials price_partials(int model, double fs, double K,
+__host__ __device__ __attribute__((always_inline)) inline PricePartials price_partials(int model, double fs, double K,
                                                         double T, double r, double q,
                                                         double sigma, int theta, double F,
                                                         double D, double price) {
@@ -329,6 +329,134 @@ __host__ __device__ inline PricePartials price_partials(int model, double fs, do
   return o;
 }
 
+// ------------------------------------------------- closed forms, scaled
+// Price, Greeks and partials at a volatility from ONE evaluation of the
+// normalised Black function (scaled_eval) and one exponential E =
+// e^{-g^2/2}, g = h + t, for the out-of-the-money side (x <= 0, m = min(F, K)):
+//   m b/b_max                     its undiscounted price,
+//   m U1 and m U2                 its two terms (F Phi and K Phi of d1 and d2
+//                                 in some order), U2 = E erfcx(q2)/2 and
+//                                 U1 = U2 + b/b_max without cancellation (and
+//                                 1 - U1 in the complement form, where the
+//                                 in-the-money side needs it),
+//   m E/sqrt(2 pi) = F phi(d1) = K phi(d2),
+// and the in-the-money side by parity.  The general forms above and below
+// evaluate two normal tails, a density and (for the Greeks) a price, with an
+// exponential each, four roots and four divisions.
+struct ScaledTerms {
+  double P;       // undiscounted price
+  double FN, KN;  // F Phi(theta d1), K Phi(theta d2)
+  double V;       // F phi(d1)
+};
+
+// False outside the domain (the caller takes the general forms): |x| above
+// 128, total volatility outside [2^-60, 64], a density below e^-690.
+__host__ __device__ __attribute__((always_inline)) inline bool scaled_terms(double F, double K,
+                                                                            double x, double s,
+                                                                            int theta,
+                                                                            ScaledTerms* o) {
+  const ScaledEval e = scaled_eval(x, s);
+  const double ea = -0.5 * e.g * e.g;
+  const double E = fexp_in(fmax(ea, -700.0));
+  const double dens = kInvSqrt2Pi * E;  // b'/b_max
+  const double part = dens * e.rho;
+  const double bh = e.comp ? 1.0 - part : part;
+  const double U2 = 0.5 * E * e.e2, U1 = U2 + bh;
+  const double V1 = e.comp ? part - U2 : 1.0 - U1;  // 1 - U1
+  const bool low = F < K, call = theta > 0, itm = call ? F > K : low;
+  const double m = low ? F : K, M = low ? K : F;
+  const bool as_call = call != itm;  // the out-of-the-money counterpart's kind
+  const double t1 = m * (itm ? V1 : U1), t2 = m * U2, t3 = itm ? M - t2 : t2;
+  o->FN = as_call ? t1 : t3;
+  o->KN = as_call ? t3 : t1;
+  o->P = fma(m, bh, itm ? fabs(F - K) : 0.0);
+  o->V = m * dens;
+  return all(x >= -128.0, s >= 0x1p-60, s <= 64.0, ea >= -690.0);
+}
+
+// A quote the scaled closed forms take: every quantity they divide by or
+// square a normal number with room to spare, both exponents in range.
+__host__ __device__ inline bool closed_form_domain(double fs, double K, double T, double rT,
+                                                   double cT) {
+  return all(fs >= 0x1p-300, fs <= 0x1p+300, K >= 0x1p-300, K <= 0x1p+300, T >= 1e-290,
+             fabs(rT) <= 200.0, fabs(cT) <= 200.0);
+}
+
+// Forward, discount factor and terms of a quote at a volatility.
+struct ClosedForm {
+  double F, D, sqT, isqT, s;
+  ScaledTerms t;
+};
+
+__host__ __device__ __attribute__((always_inline)) inline bool closed_form(
+    int model, double fs, double K, double T, double r, double q, double sigma, int theta,
+    ClosedForm* o) {
+  const double cT = model == kBlackScholesMerton ? minus(r, q) * T : r * T;
+  const bool in = closed_form_domain(fs, K, T, r * T, cT);
+  o->F = fs * growth_of<true>(model, T, r, q);
+  o->D = fexp_prod<true>(-r, T);
+  o->isqT = rsqrt(T);
+  o->sqT = T * o->isqT;
+  o->s = sigma * o->sqT;
+  const double x = -fabs(log_ratio(o->F, K));
+  return all(scaled_terms(o->F, K, x, o->s, theta, &o->t), in, ((theta + 1) & ~2) == 0);
+}
+
+// The same for a quote the scaled path has just solved: its total volatility
+// s, and F, D, x and 1/sqrt(T) from its reduction.
+__host__ __device__ __attribute__((always_inline)) inline bool closed_form_at(
+    int model, const ScaledQuote& sq, double s, double fs, double K, double T, double r, double q,
+    int theta, ClosedForm* o) {
+  const double cT = model == kBlackScholesMerton ? minus(r, q) * T : r * T;
+  o->F = sq.F;
+  o->D = sq.D;
+  o->isqT = sq.isqrtT;
+  o->sqT = T * sq.isqrtT;
+  o->s = s;
+  return all(scaled_terms(sq.F, K, sq.x, s, theta, &o->t),
+             closed_form_domain(fs, K, T, r * T, cT));
+}
+
+// The Greeks and the partials of price_partials from those terms; `price` is
+// the discounted price (Black-76 theta and rho read it).
+__host__ __device__ inline Greeks greeks_of(const ClosedForm& c, int model, double fs, double T,
+                                            double r, double q, double sigma, int theta,
+                                          double price) {
+  Greeks g;
+  const double ifs = rcp(fs), dth = (double)theta;
+  const double V = c.D * c.t.V;  // D F phi(d1)
+  const double decay = 0.5 * sigma * V * c.isqT;
+  const double dFN = dth * c.D * c.t.FN;
+  g.vega = V * c.sqT;
+  g.delta = dFN * ifs;
+  g.gamma = V * ifs * ifs * rcp(c.s);
+  if (model == kBlack76) {
+    g.theta = fma(r, price, -decay);
+    g.rho = -T * price;
+  } else {
+    const double dKN = dth * c.D * c.t.KN;
+    g.theta = -decay - r * dKN;
+    if (model == kBlackScholesMerton) g.theta = fma(q, dFN, g.theta);
+    g.rho = T * dKN;
+  }
+  return g;
+}
+
+__host__ __device__ inline PricePartials partials_of(const ClosedForm& c, int model, double fs,
+                                                     double K, double T, double r, double q,
+                                                     double sigma, int theta, double price) {
+  PricePartials o;
+  const Greeks g = greeks_of(c, model, fs, T, r, q, sigma, theta, price);
+  const double dth = (double)theta;
+  o.dfs = g.delta;
+  o.dK = -dth * c.D * c.t.KN * rcp(K);
+  o.dT = -g.theta;
+  o.dr = g.rho;
+  o.dq = model == kBlackScholesMerton ? -dth * T * c.D * c.t.FN : 0.0;
+  o.dsigma = g.vega;
+  return o;
+}
+
 // Implicit-function adjoint of the implied volatility (the paper's section 3,
 // "Differentiable IV"): with vega = dP/dsigma,
 //   dsigma/dP = 1/vega,   dsigma/dX = -(dP/dX at fixed sigma)/vega,
@@ -337,13 +465,8 @@ struct IvGrad {
   double dP, dfs, dK, dT, dr, dq;
 };
 
-__host__ __device__ inline IvGrad iv_gradient(int model, double fs, double K, double T,
-                                              double r, double q, double sigma, int theta,
-                                              double price) {
+__host__ __device__ inline IvGrad implicit_gradient(const PricePartials& pp) {
   IvGrad o;
-  const double F = forward_of(model, fs, T, r, q);
-  const double D = fexp_prod(-r, T);
-  const PricePartials pp = price_partials(model, fs, K, T, r, q, sigma, theta, F, D, price);
   const double iv = 1.0 / pp.dsigma;
   o.dP = iv;
   o.dfs = -pp.dfs * iv;
@@ -354,10 +477,18 @@ __host__ __device__ inline IvGrad iv_gradient(int model, double fs, double K, do
   return o;
 }
 
+__host__ __device__ __attribute__((always_inline)) inline IvGrad iv_gradient(int model, double fs, double K, double T,
+                                              double r, double q, double sigma, int theta,
+                                              double price) {
+  const double F = forward_of(model, fs, T, r, q);
+  const double D = fexp_prod(-r, T);
+  return implicit_gradient(price_partials(model, fs, K, T, r, q, sigma, theta, F, D, price));
+}
+
 // Price at sigma from the normalised Black function (accurate in the wings):
 // price = D sqrt(F K) b(x, s, theta), with b of a put or an in-the-money
 // option obtained from the out-of-the-money call by parity.
-__host__ __device__ inline double price_at(double F, double K, double D, double sigma,
+__host__ __device__ __attribute__((always_inline)) inline double price_at(double F, double K, double D, double sigma,
                                            double sqrtT, int theta) {
   const double lx = log_moneyness(F, K);
   // out-of-the-money side: x_otm <= 0

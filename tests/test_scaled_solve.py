@@ -132,3 +132,67 @@ def test_domain_edges_against_the_oracle(solver, entry):
     assert len(res["status_bad"]) == 0, res["status_bad"][:5]
     assert len(res["value_bad"]) == 0, (res["value_bad"][:5], res["max_ratio"])
     assert len(res["nan_bad"]) == 0 and res["n_ok"] > 0.8 * n
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("model", ["black76", "bsm"])
+def test_closed_form_edges_against_the_oracle(model):
+    """Price, Greeks and the price adjoint on both sides of every edge of the
+    scaled closed forms' domain: spot and strike around 2^+-300, total
+    volatility around 2^-60 and 64, exponents around 200, a density around
+    e^-690, F = K and one ulp from it, maturities from 1e-300 up; calls and
+    puts.  Each value within 64 u times the conditioning that binary64
+    arguments give a density or tail probability at d (greek_terms), the
+    price as the Greeks."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2604_27210_amd as fv
+    from _helpers import GREEK_NAMES, greek_terms, greeks_bad
+    rows = []
+    for e in (-301, -300, -299, 299, 300, 301):
+        rows.append((2.0 ** e, 1.1 * 2.0 ** e, 0.5, 0.02, 0.01, 0.4))
+    for s in (2.0 ** -61, 2.0 ** -60, 2.0 ** -59, 2.0 ** -30, 40.0, 63.9, 64.1):
+        rows.append((100.0, 100.0, 1.0, 0.0, 0.0, s))
+    for rT in (190.0, 199.9, 200.1, 260.0):
+        rows.append((100.0, 100.0, 50.0, rT / 50.0, rT / 50.0, 0.3))
+        rows.append((100.0, 100.0, 50.0, -rT / 50.0, -rT / 50.0, 0.3))
+    for h in np.linspace(36.5, 37.6, 23):
+        rows.append((100.0, 100.0 * np.exp(h * 0.25), 1.0, 0.0, 0.0, 0.25))
+        rows.append((100.0, 100.0 * np.exp(-h * 0.25), 1.0, 0.0, 0.0, 0.25))
+    for K in (100.0, np.nextafter(100.0, 200.0), np.nextafter(100.0, 0.0), 60.0, 170.0):
+        for sg in (1e-3, 0.2, 2.0, 12.0):
+            rows.append((100.0, K, 0.7, 0.0, 0.0, sg))
+    for T in (1e-300, 1e-291, 1e-289, 1e-12, 60.0):
+        rows.append((100.0, 100.0 * np.exp(0.4 * np.sqrt(T)), T, 0.03, 0.01, 0.5))
+    cols = [np.array(c, dtype=np.float64) for c in zip(*rows)]
+    cols = [np.concatenate([c, c]) for c in cols]
+    S, K, T, r, q, sg = cols
+    n = len(S)
+    flag = np.where(np.arange(n) < n // 2, 1, -1).astype(np.int8)
+    if model == "black76":
+        q = np.zeros(n)
+    d = lambda a, dt=torch.float64: torch.from_numpy(np.ascontiguousarray(a)).to("cuda", dt)
+    kw = dict(flag=d(flag, torch.int8), q=d(q) if model == "bsm" else None)
+    p = fv.price(model, d(S), d(K), d(T), d(r), d(sg), **kw).cpu().numpy()
+    ref = oracle.price(model, S, K, T, r, q, sg, flag)
+    # binary128 itself has no digits of F Phi(d1) - K Phi(d2) left at a total
+    # volatility below 1e-30; at the money the price is m s/sqrt(2 pi) (1 +
+    # O(s^2)) there
+    tiny = (sg * np.sqrt(T) < 1e-30) & (S == K)
+    ref = np.where(tiny, S * sg * np.sqrt(T) / np.sqrt(2.0 * np.pi), ref)
+    kappa, _ = greek_terms(model, S, K, T, r, q, sg, flag, ref)
+    bad = np.where(~(np.abs(p - ref) <= 64 * U * kappa * np.abs(ref) + 1e-300))[0]
+    assert len(bad) == 0, [(S[i], K[i], T[i], sg[i], p[i], ref[i]) for i in bad[:4]]
+    g = {k: v.cpu().numpy()
+         for k, v in fv.greeks(model, d(S), d(K), d(T), d(r), d(sg), **kw).items()}
+    bad, worst = greeks_bad(model, S, K, T, r, q, sg, flag, g, P=ref)
+    print("closed-form edges %s: %d quotes, max err/tol %.3g" % (model, n, worst))
+    for name in GREEK_NAMES:
+        assert len(bad[name]) == 0, (name, [(S[i], K[i], T[i], sg[i]) for i in bad[name][:4]])
+    a = {k: v.cpu().numpy()
+         for k, v in fv.price_backward(model, d(S), d(K), d(T), d(r), d(sg), d(np.ones(n)),
+                                       **kw).items()}
+    for mine, theirs, sign in (("fs", "delta", 1.0), ("T", "theta", -1.0), ("r", "rho", 1.0),
+                               ("sigma", "vega", 1.0)):
+        assert np.array_equal(a[mine], sign * g[theirs]), mine
