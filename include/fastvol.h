@@ -303,8 +303,8 @@ int fv_halley_trace(int model, const fv_quotes *q, uint32_t *steps_out, void *st
  * path's initial guess; its first step (with a limit of 3 or more the first
  * two) is in binary32 and only a later one may be the last: a limit of 1
  * sends every solvable quote to the fallback, 2 the quotes that need a third
- * step (binary32 starts from the Brenner-Subrahmanyam form and may stop
- * after any step).
+ * step (the binary32 solver starts from the same guess, and its second step
+ * may be the last).
  * Results stay within the Halley tolerance at any
  * limit (the fallback bisects to 1e-13 relative); a lower limit only moves
  * work to the slower bisection, which makes it a way to exercise that path.

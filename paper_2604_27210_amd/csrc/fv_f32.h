@@ -9,9 +9,11 @@
 //   * exp and log from a two-part ln 2 reduction with the hardware 2^x and
 //     an atanh series, reciprocals and square roots from the hardware
 //     single-precision instructions (about 1 ulp each);
-//   * Brenner-Subrahmanyam start, at most 8 Halley steps with the far-field
-//     log-Newton step and the sign bracket, bisection for the lanes that fail
-//     the convergence check.
+//   * the four-region guess and one Householder(3) step of the binary64
+//     solvers' binary32 start (fv_start.h), then Halley steps; outside that
+//     start's domain the Brenner-Subrahmanyam form and Halley steps with the
+//     far-field log-Newton step and the sign bracket; bisection for the lanes
+//     that fail the convergence check.
 // Domain: a normalised price beta below 2^-100 is left to the binary64 path
 // (the caller gets NaN and FV_Q_NOT_CONVERGED): binary32 keeps full relative
 // precision only down to 2^-126, and the evaluator's intermediate products
@@ -22,6 +24,8 @@
 #include <stdint.h>
 
 #include "fv_coeffs.h"
+#include "fv_math.h"
+#include "fv_start.h"
 
 namespace fv32 {
 
@@ -243,6 +247,109 @@ __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_sol
   st.s = s;
   st.converged = fabsf(ds) <= 1e-5f * s && fabsf(res) <= 1e-5f * beta;
   return st;
+}
+
+// What the scaled solve needs of a quote, as fv::scaled_quote: the status by
+// the very expressions of reduce_quote; `general` marks a quote outside its
+// domain, or whose status these forms cannot decide, which goes through
+// reduce_quote and halley_solve.  ln(F/K) comes from the significands'
+// difference (fv::log_ratio), 1/sqrt(T) from the hardware reciprocal root and
+// one Newton step.
+struct ScaledQuote {
+  float ax, bh, ch;  // |ln(F/K)|, beta/b_max, 1 - beta/b_max
+  float isqrtT;
+  uint8_t status;
+  bool general;
+};
+
+__host__ __device__ inline float minus(float a, float b) {
+#pragma clang fp contract(off)
+  return a - b;
+}
+__host__ __device__ inline bool positive_normal(float v) { return v >= kFltMin && finite(v); }
+
+__host__ __device__ inline float abs_log_ratio(float a, float b) {
+  int ea, eb;
+  float ma = frexpf(a, &ea);
+  const float mb = frexpf(b, &eb);
+  const int k = (int)(ma * 0.70710678f > mb) - (int)(ma < mb * 0.70710678f);
+  ma = ldexpf(ma, -k);
+  const float f = (ma - mb) * rcp(ma + mb);
+  const float z = f * f;
+  float S = 1.0f / 9.0f;
+  S = fmaf(S, z, 1.0f / 7.0f);
+  S = fmaf(S, z, 1.0f / 5.0f);
+  S = fmaf(S, z, 1.0f / 3.0f);
+  const float f2 = f + f;
+  const float de = (float)(ea - eb + k);
+  return fabsf(fmaf(de, kLn2Hi, fmaf(de, kLn2Lo, fmaf(f2 * z, S, f2))));
+}
+
+__host__ __device__ inline ScaledQuote scaled_quote(int model, float price, float fs, float K,
+                                                    float T, float r, float q, int theta) {
+  ScaledQuote o;
+  const float rT = r * T;
+  const float cT = model == 2 ? minus(r, q) * T : rT;
+  const bool plain = fv::all(T >= 0x1p-100f, fabsf(rT) <= 80.0f, fabsf(cT) <= 80.0f);
+  const float F = model == 0 ? fs : fs * (model == 2 ? fexp_carry(r, q, T) : fexp_prod(r, T));
+  const float cap = fexp_prod(r, T);
+  const float Pu = price * cap;
+  const float dth = (float)theta;
+  const float I = fmaxf(dth * minus(F, K), 0.0f);
+  const float M = theta > 0 ? F : K, m = F < K ? F : K;
+  uint8_t st = 0;
+  if (Pu >= M) st = 3;
+  if (Pu == I) st = 1;
+  if (Pu < I) st = 2;
+  const bool valid = fv::all(finite(price), positive_normal(fs), positive_normal(K),
+                             positive_normal(F), ((theta + 1) & ~2) == 0);
+  st = valid ? st : (uint8_t)4;
+  o.ax = abs_log_ratio(F, K);
+  const float tv = Pu - I, im = rcp(m);
+  o.bh = tv * im;
+  o.ch = (m - tv) * im;
+  const float y = rsqrt(T);
+  o.isqrtT = fmaf(0.5f * y, fmaf(-T * y, y, 1.0f), y);
+  o.status = st;
+  // beta close to its bound: whether it rounds onto it is reduce_quote's to say
+  const bool in = fv::all(o.ax <= 128.0f, !fv::all(o.ax < 0x1p-60f, o.ax != 0.0f),
+                          o.bh >= 0x1p-120f, o.ch >= 0x1p-20f, m <= 0x1p+100f);
+  o.general = !fv::all(plain, st != 0 || in);
+  return o;
+}
+
+// The scaled solve: the binary32 start of the binary64 solvers (fv_start.h:
+// four-region guess and one Householder(3) step, which leaves about 1e-6),
+// then Halley steps on the direct residual, nu = (beta - b)/b' scaled by
+// b_max, with the solver's own erfcx fit until one is below 1e-5 s: Halley's
+// cubic convergence leaves less than binary32 resolves after it, and nearly
+// every quote takes one.  False where beta may be below the solver's domain
+// (2^-100): reduce_quote decides.
+__host__ __device__ __attribute__((always_inline)) inline bool halley_solve_scaled(
+    const ScaledQuote& sq, int steps, HalleyState* st) {
+  namespace s32 = fv::s32;
+  s32::Target q;
+  q.ax = sq.ax;
+  q.bh = sq.bh;
+  q.ch = sq.ch;
+  float s = s32::initial_guess(q.bh, q.ch, q);
+  const s32::Eval e0 = s32::eval<s32::kFitStep>(q.ax, s);
+  s = fmaf(s, s32::householder3(q, e0, s), s);
+  bool done = false;
+  for (int k = 1; k < steps && !done; ++k) {
+    const s32::Eval e = s32::eval<s32::kFitSolve>(q.ax, s);
+    const float W = s32::kSqrt2Pi * s32::exp(e.g2);  // b_max/b'
+    const float n = (e.comp ? fmaf(-q.ch, W, e.rho) : fmaf(q.bh, W, -e.rho)) * e.is;
+    const float H = e.h2 - 0.25f * s * s;
+    const float d = n * s32::rcp(fmaf(0.5f * H, n, 1.0f));
+    s = fmaf(s, d, s);
+    done = fabsf(d) <= 1e-5f && fabsf(n) * (1.0f + fabsf(H)) <= 1e-2f;
+  }
+  st->lo = 0.0f;
+  st->hi = 3.0e38f;
+  st->s = s;
+  st->converged = done && s > 0.0f;
+  return !q.lower || fmaf(-0.5f, q.ax, q.lv) >= -69.0f;  // ln 2^-100 = -69.3
 }
 
 // Geometric bisection on s inside [lo, hi] to rel_tol (midpoints as

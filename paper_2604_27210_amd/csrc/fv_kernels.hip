@@ -498,8 +498,20 @@ struct KQuotes32 {
   int hsteps;
 };
 
+// Arguments of k_iv_halley32.
+struct Iv32Args {
+  KQuotes32 q;
+  float* sig_out;
+  uint8_t* st_out;
+};
+
 __device__ __forceinline__ float ld32(const fv_arg_f32& a, int64_t i) {
   return a.ptr ? a.ptr[i] : a.value;
+}
+// quote b + t, split as for ld
+template <bool ARR>
+__device__ __forceinline__ float ld32(const fv_arg_f32& a, int64_t b, unsigned t) {
+  return ARR || a.ptr ? (a.ptr + b)[t] : a.value;
 }
 
 struct Pending32 {
@@ -507,61 +519,79 @@ struct Pending32 {
   float lo, hi;
 };
 
-// The binary32 twin of k_iv_halley: same per-lane Halley, same ballot + LDS
-// compaction of the lanes that fail the convergence check and bisection over
-// the packed queue, in float arithmetic throughout.
-template <int MODEL>
+// The binary32 twin of k_iv_halley: the same ballot + LDS compaction of the
+// lanes that fail the convergence check and bisection over the packed queue,
+// in float arithmetic throughout.  Bound by the vector ALU: about 430 vector
+// instructions per quote (1,224 with the at-the-money start, whose lanes took
+// up to 8 steps and a wave its slowest lane's).  10M wide-wing BSM quotes:
+// 104 us (288 with that start).
+template <int MODEL, bool ARR>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_iv_halley32(
-    KQuotes32 q, float* __restrict__ sig_out, uint8_t* __restrict__ st_out, int qpt) {
+    Iv32Args args) {
   extern __shared__ unsigned char smem_raw[];
   Pending32* queue = reinterpret_cast<Pending32*>(smem_raw);
   __shared__ int qcount;
   if (threadIdx.x == 0) qcount = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    bool fail = false;
-    fv32::HalleyState hs;
-    hs.lo = 0.0f;
-    hs.hi = 0.0f;
-    if (i < q.n) {
-      const float P = ld32(q.price, i), fs = ld32(q.fs, i), K = ld32(q.K, i),
-                  T = ld32(q.T, i), r = ld32(q.r, i);
-      const float qy = MODEL == fv::kBlackScholesMerton ? ld32(q.q, i) : 0.0f;
-      const int th = q.flag ? (int)q.flag[i] : (int)q.flag_value;
-      const fv32::Reduced rd = fv32::reduce_quote(MODEL, P, fs, K, T, r, qy, th);
-      const uint8_t st = rd.status;
-      float sg = st == fv::kQAtIntrinsic ? 0.0f : __builtin_nanf("");
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x;
+  const unsigned t = threadIdx.x;
+  bool fail = false;
+  fv32::HalleyState hs;
+  hs.lo = 0.0f;
+  hs.hi = 0.0f;
+  if ((int64_t)t < args.q.n - b) {
+    const KQuotes32& q = args.q;
+    const float P = ld32<ARR>(q.price, b, t), fs = ld32<ARR>(q.fs, b, t),
+                K = ld32<ARR>(q.K, b, t), T = ld32<ARR>(q.T, b, t), r = ld32<ARR>(q.r, b, t);
+    const float qy = MODEL == fv::kBlackScholesMerton ? ld32<ARR>(q.q, b, t) : 0.0f;
+    const int th = ARR || q.flag ? (int)(q.flag + b)[t] : (int)q.flag_value;
+    const fv32::ScaledQuote sq = fv32::scaled_quote(MODEL, P, fs, K, T, r, qy, th);
+    uint8_t st = sq.status;
+    float sg = st == fv::kQAtIntrinsic ? 0.0f : __builtin_nanf("");
+    bool general = sq.general;
+    if (st == fv::kQOk && !general) {
+      general = !fv32::halley_solve_scaled(sq, q.hsteps, &hs);
+      sg = hs.s * sq.isqrtT;
+      fail = !hs.converged;
+    }
+    if (__builtin_expect(general, 0)) {
+      const fv32::Reduced rd = fv32::reduce_quote(MODEL, opaque(P), opaque(fs), opaque(K),
+                                                  opaque(T), opaque(r), opaque(qy), th);
+      st = rd.status;
+      sg = st == fv::kQAtIntrinsic ? 0.0f : __builtin_nanf("");
+      fail = false;
       if (st == fv::kQOk) {
         hs = fv32::halley_solve(rd.x, rd.beta, rd.bmax, rd.lnb, q.hsteps);
         sg = hs.s / rd.sqrtT;
         fail = !hs.converged;
       }
-      if (!fail) {
-        sig_out[i] = sg;
-        if (st_out) st_out[i] = st;
-      }
     }
-    const uint64_t mask = __ballot(fail);
-    if (mask) {
-      int wbase = 0;
-      const int cnt = __popcll(mask);
-      const unsigned first = __ffsll((unsigned long long)mask) - 1;
-      if (__lane_id() == first) wbase = atomicAdd(&qcount, cnt);
-      wbase = __shfl(wbase, first);
-      if (fail) {
-        const int slot = wbase + __popcll(mask & lanemask_lt());
-        queue[slot].i = i;
-        queue[slot].lo = hs.lo;
-        queue[slot].hi = hs.hi;
-      }
+    if (!fail) {
+      const Iv32Args* out = late_args<Iv32Args>();
+      (global_ptr(out->sig_out) + b)[t] = sg;
+      if (uint8_t* st_out = out->st_out) (global_ptr(st_out) + b)[t] = st;
+    }
+  }
+  const uint64_t mask = __ballot(fail);
+  if (mask) {
+    int wbase = 0;
+    const int cnt = __popcll(mask);
+    const unsigned first = __ffsll((unsigned long long)mask) - 1;
+    if (__lane_id() == first) wbase = atomicAdd(&qcount, cnt);
+    wbase = __shfl(wbase, first);
+    if (fail) {
+      const int slot = wbase + __popcll(mask & lanemask_lt());
+      queue[slot].i = b + t;
+      queue[slot].lo = hs.lo;
+      queue[slot].hi = hs.hi;
     }
   }
   __syncthreads();
   const int m = __builtin_amdgcn_readfirstlane(qcount);
   if (m == 0) return;
   for (int j = threadIdx.x; j < m; j += blockDim.x) {
+    const Iv32Args* late = late_args<Iv32Args>();
+    const KQuotes32& q = late->q;
     const int64_t i = queue[j].i;
     const float P = ld32(q.price, i), fs = ld32(q.fs, i), K = ld32(q.K, i), T = ld32(q.T, i),
                 r = ld32(q.r, i);
@@ -569,8 +599,8 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4))) 
     const int th = q.flag ? (int)q.flag[i] : (int)q.flag_value;
     const fv32::Reduced rd = fv32::reduce_quote(MODEL, P, fs, K, T, r, qy, th);
     const float s = fv32::bisection_solve(rd.x, rd.beta, rd.bmax, queue[j].lo, queue[j].hi, 2e-7f);
-    sig_out[i] = s / rd.sqrtT;
-    if (st_out) st_out[i] = fv::kQOk;
+    late->sig_out[i] = s / rd.sqrtT;
+    if (uint8_t* st_out = late->st_out) st_out[i] = fv::kQOk;
   }
 }
 
@@ -1236,15 +1266,22 @@ int fv_implied_vol_f32(int model, const fv_quotes_f32* q, float* sigma_out,
   k.flag = q->flag;
   k.flag_value = q->flag_value;
   k.hsteps = g_halley_steps.load(std::memory_order_relaxed);
-  const LaunchShape sh = shape_for(FV_KERNEL_IV_HALLEY_F32, model, q->n);
+  const LaunchShape sh{shape_for(FV_KERNEL_IV_HALLEY_F32, model, q->n).block, 1};
   const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  const size_t lds = sizeof(Pending32) * (size_t)sh.block * sh.qpt;
+  const size_t lds = sizeof(Pending32) * (size_t)sh.block;
+  const Iv32Args args = {k, sigma_out, status_out};
   hipStream_t s = (hipStream_t)stream;
+  const bool arr = q->price.ptr && q->fs.ptr && q->K.ptr && q->T.ptr && q->r.ptr && q->flag &&
+                   (model != FV_MODEL_BSM || q->q.ptr);
+#define FV_HAL32(M)                                           \
+  (arr ? k_iv_halley32<M, true><<<grid, block, lds, s>>>(args) \
+       : k_iv_halley32<M, false><<<grid, block, lds, s>>>(args))
   switch (model) {
-    case FV_MODEL_BLACK76: k_iv_halley32<0><<<grid, block, lds, s>>>(k, sigma_out, status_out, sh.qpt); break;
-    case FV_MODEL_BLACK_SCHOLES: k_iv_halley32<1><<<grid, block, lds, s>>>(k, sigma_out, status_out, sh.qpt); break;
-    default: k_iv_halley32<2><<<grid, block, lds, s>>>(k, sigma_out, status_out, sh.qpt); break;
+    case FV_MODEL_BLACK76: FV_HAL32(0); break;
+    case FV_MODEL_BLACK_SCHOLES: FV_HAL32(1); break;
+    default: FV_HAL32(2); break;
   }
+#undef FV_HAL32
   return launched("fv_implied_vol_f32");
 }
 

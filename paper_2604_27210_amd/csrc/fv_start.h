@@ -70,7 +70,7 @@ __host__ __device__ inline float log(float x) {
 #endif
 }
 // ln of a positive normal binary64 number of any exponent
-__host__ __device__ inline float log_of_double(double v) {
+__host__ __device__ inline float log_of(double v) {
   int e;
   const float m = (float)frexp(v, &e);
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -80,10 +80,13 @@ __host__ __device__ inline float log_of_double(double v) {
 #endif
 }
 
+__host__ __device__ inline float log_of(float v) { return log(v); }
+
 constexpr float kZ0 = (float)coef::kErfcxZ0;
 // erfcx(z), z >= -1/2, by the guess's fit (6e-4)
 constexpr int kSDeg = (int)(sizeof(coef::kErfcxS) / sizeof(double)) - 1;
 constexpr int kTDeg = (int)(sizeof(coef::kErfcxT) / sizeof(double)) - 1;
+constexpr int kFDeg = (int)(sizeof(coef::kErfcxF32) / sizeof(double)) - 1;
 
 __host__ __device__ inline float erfcx(float z) {
   constexpr float kB = (float)coef::kErfcxSB;
@@ -96,9 +99,10 @@ __host__ __device__ inline float erfcx(float z) {
 }
 
 // The normalised Black function at s, as ratios to b' (fv_math.h has the
-// two forms): GUESS picks the degree-4 fit of erfcx (6e-4, its derivative
-// 1e-2: far within the few percent the guess is off), else the degree-9 one
-// (4e-7, 7e-6: the step it serves lands as near) and the form by g.
+// two forms), by the erfcx fit of degree 4 for the guess (6e-4, its derivative
+// 1e-2: far within the few percent the guess is off; the caller knows the
+// form), of degree 9 for the binary32 steps (4e-7, 7e-6: they land as near),
+// or of degree 13 for the binary32 solver's own residual (6e-10).
 struct Eval {
   float is, h2;  // 1/s, h^2
   float g2;      // g^2/2: b'/b_max = e^{-g2}/sqrt(2 pi)
@@ -106,11 +110,16 @@ struct Eval {
   bool comp;
 };
 
-template <bool GUESS>
+enum Fit : int { kFitGuess, kFitStep, kFitSolve };
+
+template <Fit FIT>
 __host__ __device__ inline Eval eval(float ax, float s, bool comp = false) {
-  constexpr int kDeg = GUESS ? kSDeg : kTDeg;
-  constexpr const double* kC = GUESS ? coef::kErfcxS : coef::kErfcxT;
-  constexpr float kB = (float)(GUESS ? coef::kErfcxSB : coef::kErfcxTB);
+  constexpr int kDeg = FIT == kFitGuess ? kSDeg : (FIT == kFitStep ? kTDeg : kFDeg);
+  constexpr const double* kC =
+      FIT == kFitGuess ? coef::kErfcxS : (FIT == kFitStep ? coef::kErfcxT : coef::kErfcxF32);
+  constexpr float kB = (float)(FIT == kFitGuess ? coef::kErfcxSB
+                                                : (FIT == kFitStep ? coef::kErfcxTB
+                                                                   : coef::kErfcxF32B));
   Eval e;
   e.is = rcp(s);
   const float h = -ax * e.is, t = 0.5f * s;
@@ -118,7 +127,7 @@ __host__ __device__ inline Eval eval(float ax, float s, bool comp = false) {
   e.h2 = h * h;
   e.g2 = 0.5f * g * g;
   const float q1 = -g * kInvSqrt2, q2 = (t - h) * kInvSqrt2;
-  e.comp = GUESS ? comp : g > kInvSqrt2;
+  e.comp = FIT == kFitGuess ? comp : g > kInvSqrt2;
   const float z1 = e.comp ? -q1 : q1;
   const float a1 = z1 + kB, a2 = q2 + kB;
   const float R12 = rcp(a1 * a2);
@@ -169,8 +178,11 @@ __host__ __device__ inline uint32_t region_of(const Target& q) {
 //     f' = e^{h^2/2},  f/v_o = 2 sqrt(2 pi) P e^{h^2/2} b'/(b_max - b),
 //     v_o f'' = ((b_max - b)/(s b')) f' h^2,  z = t,
 // with P = Phi(-z) e^{z^2/2} = erfcx(z/sqrt2)/2 and everything at s_o.
-// Returns s0 and completes q.
-__host__ __device__ inline float initial_guess(double bh, double ch, Target& q) {
+// Returns s0 and completes q.  bh and ch come in the caller's precision V (a
+// binary64 bh may be below the binary32 range; only its logarithm is read
+// there).
+template <class V>
+__host__ __device__ inline float initial_guess(V bh, V ch, Target& q) {
   const float a = sqrt(q.ax);
   const float sc = kSqrt2 * a;
   // The lower tangent point s_l = sqrt2 a - sqrt(pi/2) (1 - erfcx(a)) and
@@ -188,10 +200,10 @@ __host__ __device__ inline float initial_guess(double bh, double ch, Target& q) 
   const float bc = 0.5f * om, cc = fmaf(-0.5f, om, 1.0f);  // bh(s_c); b'(s_c) = b_max/sqrt(2 pi)
   q.lower = q.bh < bc;
   q.v = q.lower ? q.bh : q.ch;
-  q.lv = log_of_double(q.lower ? bh : ch);
+  q.lv = log_of(q.lower ? bh : ch);
   const float vc = q.lower ? bc : cc;
   const float so = q.lower ? kSqrtPiOver2 * q.ax * tail : fmaf(cc, kSqrt2Pi, sc);
-  const Eval e = eval<true>(q.ax, so, !q.lower);
+  const Eval e = eval<kFitGuess>(q.ax, so, !q.lower);
   const float bp = kInvSqrt2Pi * exp(-e.g2);  // b'(s_o)/b_max
   const float vo = e.rho * bp;
   q.wing = q.v < vo;

@@ -196,3 +196,50 @@ def test_closed_form_edges_against_the_oracle(model):
     for mine, theirs, sign in (("fs", "delta", 1.0), ("T", "theta", -1.0), ("r", "rho", 1.0),
                                ("sigma", "vega", 1.0)):
         assert np.array_equal(a[mine], sign * g[theirs]), mine
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("broadcast", [False, True])
+def test_binary32_domain_edges(broadcast):
+    """The binary32 solver on both sides of the edges that send a quote to its
+    general path: beta around 2^-100, 1 - beta/b_max around 2^-20 (s ~ 9.5),
+    maturities around 2^-100, r T around 80, F and K one ulp apart, F and K
+    far from 1; with arrays and with broadcast r and q.  The binary32
+    contract, as test_gpu_f32 has it."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2604_27210_amd as fv
+    from test_gpu_f32 import compare_f32
+    f32 = np.float32
+    rows = []  # F, K, T, sigma (r = 0)
+    for h in np.linspace(10.8, 11.6, 17):
+        rows.append((100.0, 100.0 * np.exp(0.25 * h), 1.0, 0.25))
+    for s in np.linspace(8.5, 10.5, 17):
+        rows += [(100.0, 130.0, 1.0, s), (100.0, 70.0, 1.0, s)]
+    for T in (2.0 ** -101, 2.0 ** -100, 2.0 ** -99, 1e-12):
+        rows.append((100.0, 100.0 * np.exp(0.5 * np.sqrt(T)), T, 0.5))
+    for K in (f32(100.0), np.nextafter(f32(100.0), f32(200.0)), np.nextafter(f32(100.0), f32(0.0))):
+        rows += [(100.0, float(K), 0.5, sg) for sg in (0.01, 0.3, 2.0)]
+    for e in (-99.0, -60.0, 60.0, 99.0, 101.0):
+        rows.append((2.0 ** e, 1.2 * 2.0 ** e, 0.5, 0.4))
+    F, K, T, sg = (np.array(c).astype(f32).astype(np.float64) for c in zip(*rows))
+    r = np.zeros(len(F))
+    if not broadcast:  # long exponents: the forward grows as the strike does
+        rT = np.array([70.0, 79.9, 80.1, 85.0])
+        F, T = np.concatenate([F, np.full(4, 1e-20)]), np.concatenate([T, np.full(4, 50.0)])
+        r = np.concatenate([r, (rT / 50.0).astype(f32).astype(np.float64)])
+        K = np.concatenate([K, (1e-20 * np.exp(r[-4:] * 50.0)).astype(f32).astype(np.float64)])
+        sg = np.concatenate([sg, np.full(4, f32(0.3), dtype=np.float64)])
+    n = len(F)
+    flag = np.where(K >= F * np.exp(r * T), 1, -1).astype(np.int8)
+    P = oracle.price("bs", F, K, T, r, np.zeros(n), sg, flag).astype(f32).astype(np.float64)
+    keep = P >= np.finfo(f32).tiny
+    F, K, T, r, P, flag = (a[keep] for a in (F, K, T, r, P, flag))
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=f32)).to("cuda")
+    sig, st = fv.implied_vol_f32("bs", d(P), d(F), d(K), d(T), 0.0 if broadcast else d(r),
+                                 flag=torch.from_numpy(flag).to("cuda"))
+    ok, worst = compare_f32("bs", [P, F, K, T, r, np.zeros(len(F))], flag,
+                            sig.cpu().numpy().astype(np.float64), st.cpu().numpy())
+    print("binary32 edges: %d of %d solved, max err/tol %.3g" % (ok, len(F), worst))
+    assert ok > 0.7 * len(F)
