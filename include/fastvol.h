@@ -146,7 +146,8 @@ typedef struct {
 
 /* Implied volatility in binary32 arithmetic with the Halley path (paper
  * section 2.2: the throughput solver for label pipelines that train in
- * float32): Brenner-Subrahmanyam start, at most 8 Halley steps (the
+ * float32): the four-region guess of the LBR path and one step on its
+ * objective, then Halley steps (at most 8 steps in all, the
  * fv_set_halley_steps limit), bisection for the quotes that fail the
  * convergence check, all in float.
  * sigma_out: float [n] (required); status_out: uint8 [n] or NULL.  Statuses
