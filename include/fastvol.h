@@ -222,14 +222,14 @@ typedef struct {
  * Negative (an FV_E_* code) when p is invalid. */
 int64_t fv_svi_workspace_size(const fv_svi_problem *p);
 
-/* One Adam step of the calibration, as four launches on `stream` that
+/* One Adam step of the calibration, as three launches on `stream` that
  * allocate nothing and never synchronise (capturable in a hipGraph): the
  * per-maturity natural parameters; the per-quote chain SVI -> Black-76
  * price -> LBR implied volatility -> implicit-function adjoint, one wave per
  * 64 consecutive quotes, summed per (wave, maturity) run; per maturity the
- * sums of its runs in a fixed order, the gradient and the Adam update; the
- * loss, a fixed-order sum (not launched when loss is NULL or loss_len is
- * 0).  No atomics: results are bitwise reproducible.  The price reaches the
+ * sums of its runs in a fixed order, the gradient and the Adam update, and
+ * beside them the loss, a fixed-order sum (none when loss is NULL or
+ * loss_len is 0).  No atomics: results are bitwise reproducible.  The price reaches the
  * solver as the normalised price b(x, s) of its out-of-the-money side, the
  * value the solver's own reduction of the discounted price recovers.
  *   theta, adam_m, adam_v: [5 n_maturities] in/out (moments start at 0);
