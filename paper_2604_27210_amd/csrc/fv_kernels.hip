@@ -730,7 +730,9 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
   }
   // two consecutive 64-quote slices per wave, both located before either is
   // solved (the second location reuses the first's window of starts)
-  const int64_t w0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 128;
+  // (the wave's number as a scalar: the location runs on the scalar unit)
+  const int64_t w0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) +
+                      __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * 128;
   const int lane = (int)__lane_id();
   int64_t ms[2] = {0, 0}, cs[2] = {0, 0};
   const bool any = w0 < c.n;  // wave-uniform
