@@ -22,9 +22,12 @@ def __getattr__(name):
                 "autotune_all", "launch_shape", "save_tuning", "load_tuning", "reset_tuning",
                 "price_backward", "lbr_trace", "halley_trace", "set_halley_steps",
                 "get_halley_steps"):
-        from . import api
-        return getattr(api, name)
-    if name in ("IVFunction", "implied_vol_autograd", "PriceFunction", "price_autograd"):
-        from . import autograd
-        return getattr(autograd, name)
-    raise AttributeError(name)
+        from . import api as module
+    elif name in ("IVFunction", "implied_vol_autograd", "PriceFunction", "price_autograd"):
+        from . import autograd as module
+    else:
+        raise AttributeError(name)
+    # kept as the package's own attribute: this function runs once per name
+    # (0.8 us a call otherwise)
+    value = globals()[name] = getattr(module, name)
+    return value

@@ -1,4 +1,5 @@
-"""ctypes declarations of the C ABI in ``include/fastvol.h``.
+"""ctypes declarations of the C ABI in ``include/fastvol.h``, and the loader
+of the compiled tensor marshalling (``csrc/fv_bind.cpp``).
 
 Only argument marshalling lives here: every computation happens in the
 gfx950 kernels of ``libfastvol.so``.  The library is loaded after torch so
@@ -8,12 +9,16 @@ makes torch device pointers and streams valid in it.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # FASTVOL_LIBRARY may name another build of the same library (e.g. one
 # compiled with different register-allocation targets)
 LIB_PATH = os.environ.get("FASTVOL_LIBRARY") or os.path.join(HERE, "_build", "libfastvol.so")
+
+BIND_PATH = os.path.join(HERE, "_build", "fv_bind.so")
 
 FV_OK = 0
 FV_E_INVALID_ARG = -1
@@ -71,7 +76,15 @@ EXPORTS = ["fv_price", "fv_implied_vol", "fv_implied_vol_f32", "fv_greeks", "fv_
            "fv_autotune", "fv_launch_shape", "fv_tuning_reset", "fv_tuning_save", "fv_tuning_load",
            "fv_svi_workspace_size", "fv_svi_adam_step", "fv_svi_adam_step_noalloc", "fv_svi_vols", "fv_last_error", "fv_version"]
 
+# functions that the tensor marshalling calls, in its order, and their indices
+BOUND = ("fv_implied_vol", "fv_price", "fv_greeks", "fv_implied_vol_backward", "fv_price_backward",
+         "fv_lbr_trace", "fv_halley_trace", "fv_implied_vol_f32", "fv_implied_vol_chains",
+         "fv_last_error")
+(FN_IV, FN_PRICE, FN_GREEKS, FN_IV_BACKWARD, FN_PRICE_BACKWARD, FN_LBR_TRACE,
+ FN_HALLEY_TRACE) = range(7)
+
 _lib = None
+_bind = None
 
 
 class FastvolError(RuntimeError):
@@ -121,6 +134,33 @@ def load():
     lib.fv_last_error.restype = ctypes.c_char_p
     _lib = lib
     return lib
+
+
+def _current_stream(device):
+    import torch
+    return int(torch.cuda.current_stream(device).cuda_stream)
+
+
+def bind():
+    """The compiled tensor marshalling, bound to the loaded library (raises
+    if either has not been built)."""
+    global _bind
+    if _bind is not None:
+        return _bind
+    lib = load()
+    if not os.path.exists(BIND_PATH):
+        raise FastvolError(
+            "fv_bind.so is not built (%s); run paper_2604_27210_amd/build.py "
+            "or __graft_entry__.build()" % BIND_PATH)
+    import torch
+    loader = importlib.machinery.ExtensionFileLoader("fv_bind", BIND_PATH)
+    mod = importlib.util.module_from_spec(
+        importlib.util.spec_from_file_location("fv_bind", BIND_PATH, loader=loader))
+    # the raw handle of the current stream without building a Stream object
+    mod.init(tuple(ctypes.cast(getattr(lib, nm), ctypes.c_void_p).value for nm in BOUND),
+             FastvolError, getattr(torch._C, "_cuda_getCurrentRawStream", _current_stream))
+    _bind = mod
+    return mod
 
 
 def check(rc: int, what: str) -> None:

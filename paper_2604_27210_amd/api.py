@@ -1,4 +1,5 @@
-"""Python surface of the library: thin marshalling over the C ABI.
+"""Python surface of the library: thin marshalling over the C ABI (tensors
+through csrc/fv_bind.cpp, the rest through ctypes).
 
 Every argument that is a per-quote field may be a Python float (broadcast to
 all quotes) or a contiguous float64 tensor on the GPU.  Results are float64
@@ -55,130 +56,28 @@ def _dev_tensor(t: torch.Tensor, name: str, dtype=torch.float64) -> torch.Tensor
     return t
 
 
-def _flag_arg(flag, n, keep):
-    """(pointer, broadcast value) of a flag argument: 'c'/'p', +1/-1, or an
-    int8 GPU tensor of n entries (kept alive in `keep`)."""
-    if isinstance(flag, str):
-        return None, (1 if flag.lower().startswith("c") else -1)
-    if isinstance(flag, (int, float)):
-        return None, int(flag)
-    if isinstance(flag, torch.Tensor) and flag.dim() > 0:
-        if flag.dtype != torch.int8:
-            raise TypeError("flag tensor must be int8 (+1 call / -1 put)")
-        _dev_tensor(flag, "flag", torch.int8)
-        if flag.numel() != n:
-            raise ValueError("flag length mismatch")
-        keep.append(flag)
-        return ctypes.c_void_p(flag.data_ptr()), 1
-    raise TypeError("flag must be 'c'/'p', +1/-1 or an int8 GPU tensor")
-
-
-class _Batch:
-    """Validates the per-quote fields of one call in a single pass (each
-    tensor: 1-D, on the GPU, float64, contiguous, one common length), and
-    turns each into its fv_arg (device pointer, or broadcast value)."""
-
-    __slots__ = ("n", "device", "args")
-
-    def __init__(self, **fields):
-        n = None
-        device = None
-        args = {}
-        for name, v in fields.items():
-            if name == "flag":
-                continue
-            if v is None:
-                args[name] = _NO_ARG
-            elif isinstance(v, torch.Tensor) and v.dim() > 0:
-                if v.dim() != 1:
-                    raise ValueError("%s must be 1-D" % name)
-                _dev_tensor(v, name)
-                m = v.numel()
-                if n is None:
-                    n, device = m, v.get_device()
-                elif m != n:
-                    raise ValueError("length mismatch: %s has %d, expected %d" % (name, m, n))
-                args[name] = N.FvArg(v.data_ptr(), 0.0)
-            else:
-                args[name] = N.FvArg(None, float(v))
-        if n is None:
-            raise ValueError("at least one per-quote field must be a 1-D GPU tensor")
-        self.n, self.device, self.args = n, device, args
-
-    def arg(self, v, name) -> N.FvArg:
-        a = self.args.get(name)
-        if a is not None:
-            return a
-        # a field that was not part of the batch's construction
-        if v is None:
-            return _NO_ARG
-        if isinstance(v, torch.Tensor) and v.dim() > 0:
-            _dev_tensor(v, name)
-            if v.numel() != self.n:
-                raise ValueError("length mismatch: %s has %d, expected %d"
-                                 % (name, v.numel(), self.n))
-            return N.FvArg(v.data_ptr(), 0.0)
-        return N.FvArg(None, float(v))
-
-    def flag(self, flag):
-        """Returns (pointer, broadcast value)."""
-        return _flag_arg(flag, self.n, [])
-
-    def quotes(self, price=None, fs=None, K=None, T=None, r=None, q=None, flag=1) -> N.FvQuotes:
-        fp, fv = self.flag(flag)
-        return N.FvQuotes(self.n, self.arg(price, "price"), self.arg(fs, "fs"), self.arg(K, "K"),
-                          self.arg(T, "T"), self.arg(r, "r"),
-                          self.arg(q, "q") if q is not None else _ZERO_ARG, fp, fv)
-
-    def empty(self, dtype=torch.float64):
-        return torch.empty(self.n, dtype=dtype, device=self.device)
-
-    def rows(self, names):
-        """One [len(names), n] float64 allocation, returned as a dict of its
-        rows (each contiguous)."""
-        block = torch.empty((len(names), self.n), dtype=torch.float64, device=self.device)
-        return {k: block[i] for i, k in enumerate(names)}
-
-    def stream(self, stream=None) -> ctypes.c_void_p:
-        return ctypes.c_void_p(_stream_ptr(stream, self.device))
-
-
-_NO_ARG = N.FvArg(None, 0.0)
-_ZERO_ARG = N.FvArg(None, 0.0)
-
-
 def _ptr(t: Optional[torch.Tensor]):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else None
 
 
+# options of an implied-volatility call (what it returns)
+_STATUS, _GREEKS, _GREEK_BLOCK = 1, 2, 4
+
+
+def _flat(fn, model, solver, price, fs, K, T, r, q, sigma, grad, flag, option, stream):
+    """One launch over a flat batch (csrc/fv_bind.cpp): checks the fields
+    (each a number, or a contiguous float64 GPU vector, all of one length),
+    allocates the outputs and calls the library's function `fn`."""
+    return N.bind().flat(fn, _model(model), solver, price, fs, K, T, r, q, sigma, grad, flag,
+                         option, None if stream is None else int(stream.cuda_stream))
+
+
 def price(model, fs, K, T, r, sigma, flag="c", q=None, out=None, stream=None) -> torch.Tensor:
     """Model price (Black-76: discounted, on forward fs; else spot fs)."""
-    b = _Batch(fs=fs, K=K, T=T, r=r, q=q, sigma=sigma, flag=flag)
-    qs = b.quotes(None, fs, K, T, r, q, flag)
-    out = b.empty() if out is None else _dev_tensor(out, "out")
-    N.check(N.load().fv_price(_model(model), ctypes.byref(qs), b.arg(sigma, "sigma"),
-                              _ptr(out), b.stream(stream)), "fv_price")
-    return out
+    return _flat(N.FN_PRICE, model, 0, None, fs, K, T, r, q, sigma, None, flag, out, stream)
 
 
 GREEK_NAMES = ("delta", "gamma", "vega", "theta", "rho")
-
-
-def _implied_vol(model, price, fs, K, T, r, flag, q, solver, greeks, with_status, stream):
-    """(sigma, status or None, Greeks as one [5, n] tensor or None)."""
-    b = _Batch(price=price, fs=fs, K=K, T=T, r=r, q=q, flag=flag)
-    qs = b.quotes(price, fs, K, T, r, q, flag)
-    sig = b.empty()
-    st = b.empty(torch.uint8) if with_status else None
-    G = None
-    garr = None
-    if greeks:
-        G = torch.empty((5, b.n), dtype=torch.float64, device=b.device)
-        garr = (ctypes.c_void_p * 5)(*[G[i].data_ptr() for i in range(5)])
-    N.check(N.load().fv_implied_vol(_model(model), _solver(solver), ctypes.byref(qs), _ptr(sig),
-                                    _ptr(st), garr, b.stream(stream)),
-            "fv_implied_vol")
-    return sig, st, G
 
 
 def implied_vol(model, price, fs, K, T, r, flag="c", q=None, solver="lbr", greeks=False,
@@ -186,111 +85,42 @@ def implied_vol(model, price, fs, K, T, r, flag="c", q=None, solver="lbr", greek
     """Implied volatility.  Returns sigma, or (sigma, status) with
     ``with_status``; with ``greeks=True`` a dict of the five Greeks at the
     solved sigma is appended (rows of one [5, n] tensor)."""
-    sig, st, G = _implied_vol(model, price, fs, K, T, r, flag, q, solver, greeks, with_status,
-                              stream)
-    res = [sig]
-    if with_status:
-        res.append(st)
-    if greeks:
-        res.append({k: G[i] for i, k in enumerate(GREEK_NAMES)})
-    return res[0] if len(res) == 1 else tuple(res)
+    return _flat(N.FN_IV, model, _solver(solver), price, fs, K, T, r, q, None, None, flag,
+                 (_STATUS if with_status else 0) | (_GREEKS if greeks else 0), stream)
 
 
 def implied_vol_f32(model, price, fs, K, T, r, flag="c", q=None, with_status=True, stream=None):
     """Implied volatility in binary32 arithmetic (Halley path): per-quote
     fields are Python floats or contiguous float32 GPU tensors; returns a
     float32 sigma (and the uint8 status with ``with_status``)."""
-    fields = dict(price=price, fs=fs, K=K, T=T, r=r, q=q)
-    n, device, keep = None, None, []
-    for name, v in fields.items():
-        if isinstance(v, torch.Tensor) and v.dim() > 0:
-            _dev_tensor(v, name, torch.float32)
-            if v.dim() != 1:
-                raise ValueError("%s must be 1-D" % name)
-            if n is None:
-                n, device = v.numel(), v.device
-            elif v.numel() != n:
-                raise ValueError("length mismatch: %s has %d, expected %d" % (name, v.numel(), n))
-    if n is None:
-        raise ValueError("at least one per-quote field must be a 1-D GPU tensor")
-
-    def arg(v, name):
-        if v is None:
-            return N.FvArgF32(None, 0.0)
-        if isinstance(v, torch.Tensor) and v.dim() > 0:
-            keep.append(v)
-            return N.FvArgF32(ctypes.c_void_p(v.data_ptr()), 0.0)
-        return N.FvArgF32(None, float(v))
-
-    fp, fv = _flag_arg(flag, n, keep)
-    qs = N.FvQuotesF32(n, arg(price, "price"), arg(fs, "fs"), arg(K, "K"), arg(T, "T"),
-                       arg(r, "r"), arg(q if q is not None else 0.0, "q"), fp, fv)
-    sig = torch.empty(n, dtype=torch.float32, device=device)
-    st = torch.empty(n, dtype=torch.uint8, device=device) if with_status else None
-    N.check(N.load().fv_implied_vol_f32(_model(model), ctypes.byref(qs), _ptr(sig), _ptr(st),
-                                        ctypes.c_void_p(_stream_ptr(stream, sig.get_device()))),
-            "fv_implied_vol_f32")
-    return (sig, st) if with_status else sig
+    return N.bind().flat_f32(_model(model), price, fs, K, T, r, q, flag, 1 if with_status else 0,
+                             None if stream is None else int(stream.cuda_stream))
 
 
 def greeks(model, fs, K, T, r, sigma, flag="c", q=None, stream=None) -> dict:
     """delta, gamma, vega, theta (= -dP/dT), rho as raw per-unit derivatives."""
-    b = _Batch(fs=fs, K=K, T=T, r=r, q=q, sigma=sigma, flag=flag)
-    qs = b.quotes(None, fs, K, T, r, q, flag)
-    out = b.rows(("delta", "gamma", "vega", "theta", "rho"))
-    N.check(N.load().fv_greeks(_model(model), ctypes.byref(qs), b.arg(sigma, "sigma"),
-                               *[_ptr(v) for v in out.values()],
-                               b.stream(stream)), "fv_greeks")
-    return out
+    return _flat(N.FN_GREEKS, model, 0, None, fs, K, T, r, q, sigma, None, flag, None, stream)
 
 
 def implied_vol_backward(model, price, fs, K, T, r, sigma, grad_sigma, flag="c", q=None,
                          stream=None) -> dict:
     """dL/d(price, fs, K, T, r, q) from dL/dsigma (implicit-function adjoint)."""
-    b = _Batch(price=price, fs=fs, K=K, T=T, r=r, q=q, flag=flag, sigma=sigma)
-    qs = b.quotes(price, fs, K, T, r, q, flag)
-    _dev_tensor(sigma, "sigma")
-    _dev_tensor(grad_sigma, "grad_sigma")
-    out = b.rows(("price", "fs", "K", "T", "r", "q"))
-    N.check(N.load().fv_implied_vol_backward(_model(model), ctypes.byref(qs), _ptr(sigma),
-                                             _ptr(grad_sigma), *[_ptr(v) for v in out.values()],
-                                             b.stream(stream)),
-            "fv_implied_vol_backward")
-    return out
+    return _flat(N.FN_IV_BACKWARD, model, 0, price, fs, K, T, r, q, sigma, grad_sigma, flag, None,
+                 stream)
 
 
 def price_backward(model, fs, K, T, r, sigma, grad_price, flag="c", q=None, stream=None) -> dict:
     """dL/d(fs, K, T, r, q, sigma) from dL/dprice (adjoint of ``price``)."""
-    b = _Batch(fs=fs, K=K, T=T, r=r, q=q, sigma=sigma, flag=flag, grad_price=grad_price)
-    qs = b.quotes(None, fs, K, T, r, q, flag)
-    _dev_tensor(grad_price, "grad_price")
-    out = b.rows(("fs", "K", "T", "r", "q", "sigma"))
-    N.check(N.load().fv_price_backward(_model(model), ctypes.byref(qs), b.arg(sigma, "sigma"),
-                                       _ptr(grad_price), *[_ptr(v) for v in out.values()],
-                                       b.stream(stream)), "fv_price_backward")
-    return out
+    return _flat(N.FN_PRICE_BACKWARD, model, 0, None, fs, K, T, r, q, sigma, grad_price, flag,
+                 None, stream)
 
 
 def implied_vol_chains(chain_mat_off, mat_quote_off, F, r, T, price, K, flag, solver="lbr",
                        with_status=True, stream=None):
     """Implied volatility of ragged Black-76 chains (CSR offsets, int64)."""
-    for t, nm in ((chain_mat_off, "chain_mat_off"), (mat_quote_off, "mat_quote_off")):
-        _dev_tensor(t, nm, torch.int64)
-    for t, nm in ((F, "F"), (r, "r"), (T, "T"), (price, "price"), (K, "K")):
-        _dev_tensor(t, nm)
-    _dev_tensor(flag, "flag", torch.int8)
-    c = N.FvChains(F.numel(), T.numel(), price.numel(), _ptr(chain_mat_off), _ptr(mat_quote_off),
-                   _ptr(F), _ptr(r), _ptr(T), _ptr(price), _ptr(K), _ptr(flag))
-    if chain_mat_off.numel() != F.numel() + 1 or mat_quote_off.numel() != T.numel() + 1:
-        raise ValueError("offset arrays must have n_chains+1 and n_maturities+1 entries")
-    if K.numel() != price.numel() or flag.numel() != price.numel() or r.numel() != F.numel():
-        raise ValueError("per-quote / per-chain array lengths disagree")
-    sig = torch.empty(price.numel(), dtype=torch.float64, device=price.device)
-    st = torch.empty(price.numel(), dtype=torch.uint8, device=price.device) if with_status else None
-    N.check(N.load().fv_implied_vol_chains(_solver(solver), ctypes.byref(c), _ptr(sig), _ptr(st),
-                                           ctypes.c_void_p(_stream_ptr(stream, sig.get_device()))),
-            "fv_implied_vol_chains")
-    return (sig, st) if with_status else sig
+    return N.bind().chains(_solver(solver), chain_mat_off, mat_quote_off, F, r, T, price, K, flag,
+                           1 if with_status else 0,
+                           None if stream is None else int(stream.cuda_stream))
 
 
 def normalised_black(x, s, flag=None, stream=None) -> torch.Tensor:
@@ -309,22 +139,12 @@ def normalised_black(x, s, flag=None, stream=None) -> torch.Tensor:
 
 def lbr_trace(model, price, fs, K, T, r, flag="c", q=None, stream=None) -> torch.Tensor:
     """Per-quote path code of the LBR solver (see fv_lbr_trace)."""
-    b = _Batch(price=price, fs=fs, K=K, T=T, r=r, q=q, flag=flag)
-    qs = b.quotes(price, fs, K, T, r, q, flag)
-    out = torch.empty(b.n, dtype=torch.int32, device=b.device)
-    N.check(N.load().fv_lbr_trace(_model(model), ctypes.byref(qs), _ptr(out),
-                                  b.stream(stream)), "fv_lbr_trace")
-    return out
+    return _flat(N.FN_LBR_TRACE, model, 0, price, fs, K, T, r, q, None, None, flag, None, stream)
 
 
 def halley_trace(model, price, fs, K, T, r, flag="c", q=None, stream=None) -> torch.Tensor:
     """Per-quote Halley step count and fallback bit (see fv_halley_trace)."""
-    b = _Batch(price=price, fs=fs, K=K, T=T, r=r, q=q, flag=flag)
-    qs = b.quotes(price, fs, K, T, r, q, flag)
-    out = torch.empty(b.n, dtype=torch.int32, device=b.device)
-    N.check(N.load().fv_halley_trace(_model(model), ctypes.byref(qs), _ptr(out),
-                                     b.stream(stream)), "fv_halley_trace")
-    return out
+    return _flat(N.FN_HALLEY_TRACE, model, 0, price, fs, K, T, r, q, None, None, flag, None, stream)
 
 
 def set_halley_steps(steps: int) -> None:

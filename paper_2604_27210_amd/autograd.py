@@ -14,6 +14,7 @@ from __future__ import annotations
 
 import torch
 
+from . import _native as N
 from . import api
 
 
@@ -24,32 +25,29 @@ def _req(t):
 class IVFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, price, fs, K, T, r, q, flag, model, solver, greeks):
-        sig, st, G = api._implied_vol(model, price.detach(), _d(fs), _d(K), _d(T), _d(r), flag,
-                                      _d(q), solver, greeks, True, None)
+        # the five Greeks leave as one [5, n] tensor: every extra output of a
+        # Function costs the autograd engine bookkeeping
+        sig, st, *extra = api._flat(N.FN_IV, model, api._solver(solver), price.detach(), fs, K, T,
+                                    r, q, None, None, flag,
+                                    api._STATUS | (api._GREEKS | api._GREEK_BLOCK if greeks else 0),
+                                    None)
         ctx.model = model
         ctx.flag = flag
         ctx.scalar = [not isinstance(v, torch.Tensor) or v.dim() == 0 for v in (price, fs, K, T, r, q)]
         ctx.save_for_backward(*[v if isinstance(v, torch.Tensor) else torch.tensor(float(v or 0.0))
                                 for v in (price, fs, K, T, r, q)], sig)
-        # the five Greeks leave as one [5, n] tensor: every extra output of a
-        # Function costs the autograd engine bookkeeping
-        extra = (G,) if greeks else ()
         ctx.mark_non_differentiable(st, *extra)
-        return (sig, st) + extra
+        return (sig, st, *extra)
 
     @staticmethod
     def backward(ctx, g_sig, g_st, *g_greeks):
         price, fs, K, T, r, q, sig = ctx.saved_tensors
-        args = [v.item() if s else v.detach() for v, s in zip((price, fs, K, T, r, q), ctx.scalar)]
+        args = [v.item() if s else v for v, s in zip((price, fs, K, T, r, q), ctx.scalar)]
         g = api.implied_vol_backward(ctx.model, args[0], args[1], args[2], args[3], args[4],
                                      sig, g_sig.contiguous(), flag=ctx.flag, q=args[5])
         return (*_input_grads(g, ("price", "fs", "K", "T", "r", "q"), ctx.scalar,
                               ctx.needs_input_grad[:6], (price, fs, K, T, r, q)),
                 None, None, None, None)
-
-
-def _d(v):
-    return v.detach() if isinstance(v, torch.Tensor) else v
 
 
 def _input_grads(g, names, scalar, needs, saved):
@@ -84,7 +82,7 @@ def implied_vol_autograd(model, price, fs, K, T, r, flag="c", q=None, solver="lb
 class PriceFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, fs, K, T, r, q, sigma, flag, model):
-        p = api.price(model, _d(fs), _d(K), _d(T), _d(r), _d(sigma), flag=flag, q=_d(q))
+        p = api.price(model, fs, K, T, r, sigma, flag=flag, q=q)
         ctx.model, ctx.flag = model, flag
         ctx.scalar = [not isinstance(v, torch.Tensor) or v.dim() == 0 for v in (fs, K, T, r, q, sigma)]
         ctx.save_for_backward(*[v if isinstance(v, torch.Tensor) else torch.tensor(float(v or 0.0))
@@ -94,7 +92,7 @@ class PriceFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g_p):
         saved = ctx.saved_tensors
-        a = [v.item() if s else v.detach() for v, s in zip(saved, ctx.scalar)]
+        a = [v.item() if s else v for v, s in zip(saved, ctx.scalar)]
         g = api.price_backward(ctx.model, a[0], a[1], a[2], a[3], a[5], g_p.contiguous(),
                                flag=ctx.flag, q=a[4])
         return (*_input_grads(g, ("fs", "K", "T", "r", "q", "sigma"), ctx.scalar,

@@ -9,6 +9,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -57,6 +58,33 @@ def build_capi_demo(verbose: bool = False) -> str:
     return DEMO
 
 
+BIND_SRC = os.path.join(CSRC, "fv_bind.cpp")
+BIND = os.path.join(OUT_DIR, "fv_bind.so")
+
+
+def build_bind(verbose: bool = False) -> str:
+    """The tensor marshalling: an extension module of the interpreter, host
+    code only, against the headers of the installed torch.  It calls the
+    library through addresses that the loader passes, so it isn't linked to
+    it, and is imported after torch, whose libraries are then mapped."""
+    import torch
+    base = os.path.dirname(torch.__file__)
+    tmp = BIND + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-isystem", os.path.join(base, "include"),
+           "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], BIND_SRC, "-o", tmp,
+           "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
+    os.replace(tmp, BIND)
+    return BIND
+
+
 def build(verbose: bool = False, extra=None, out: str = None) -> str:
     lib = out or LIB
     os.makedirs(os.path.dirname(lib), exist_ok=True)
@@ -78,4 +106,5 @@ def build(verbose: bool = False, extra=None, out: str = None) -> str:
 
 if __name__ == "__main__":
     print(build(verbose=True, extra=sys.argv[1:]))
+    print(build_bind(verbose=True))
     print(build_capi_demo(verbose=True))
