@@ -241,17 +241,19 @@ __global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))
   fv::ChainCursor cur;
   cur.init(c.mat_quote_off, c.n_mat, c.chain_mat_off, c.n_chains, w0);
   const int64_t i = w0 + lane;
-  int64_t m, cc;
-  cur.slice(w0, min(w0 + 63, c.n - 1), i, m, cc);
-  const double* rec = nat + kNatCount * m;
+  int64_t m0, cc0;
+  int key, cc;
+  cur.slice(w0, min(w0 + 63, c.n - 1), m0, key, cc0, cc);
+  const int64_t m = m0 + key;
+  const double* rec = nat + kNatCount * m0 + (unsigned)(kNatCount * key);
   const double sa = rec[kNatA], sb = rec[kNatB], srho = rec[kNatRho], smu = rec[kNatMu],
                ss = rec[kNatS], isqT = rec[kNatIsqT];
   double v[kSumCount], e2 = 0.0;
 #pragma unroll
   for (int j = 0; j < kSumCount; ++j) v[j] = 0.0;
   if (i < c.n) {
-    const double tgt = c.iv_target[i];
-    const double F = c.F[cc], K = c.K[i];
+    const double tgt = (c.iv_target + w0)[(unsigned)lane], K = (c.K + w0)[(unsigned)lane];
+    const double F = (c.F + cc0)[(unsigned)cc];
     double lfk = fv::log_ratio(F, K);  // ln(F/K) = -k
     // (its significands make a finite number of anything: a quote with no
     // logarithm, such as a padding strike of 0, stays NaN and is skipped)
@@ -312,7 +314,6 @@ __global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))
       e2 = e * e;
     }
   }
-  const int key = (int)(m - fv::readlane64(m, 0));
   if (__builtin_amdgcn_readlane(key, 63) == 0) {
     // One maturity, the rule: all six sums at once, halving the values in
     // flight with each of the first two folds (lanes by halves, then rows),

@@ -1,7 +1,7 @@
 // fv_csr.h -- wave-cooperative location of quotes in CSR (offset-array)
 // layouts: chain -> maturity -> quote, as the ragged-chain and calibration
 // kernels read them.  Every helper here is called by all 64 lanes of a wave
-// together and returns wave-uniform results.
+// together and returns wave-uniform results, but the lanes' offsets of a slice.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -82,23 +82,27 @@ struct ChainCursor {
     mw.init(mat_quote_off, n_mat, mstart);
     cw.init(chain_mat_off, n_chains, cstart);
   }
-  // The slice starting at quote i0 whose last quote is ilast; lane's quote i.
-  // Returns the lane's maturity in m and chain in cc.
-  __device__ __forceinline__ void slice(int64_t i0, int64_t ilast, int64_t i, int64_t& m,
-                                        int64_t& cc) {
+  // The slice starting at quote i0 whose last quote is ilast.  The lane's
+  // maturity and chain, as offsets from those of quote i0, which are returned
+  // in m0 and c0: uniform bases and 32-bit lane offsets are what the loads
+  // take, and lane comparisons of 32 bits.
+  __device__ __forceinline__ void slice(int64_t i0, int64_t ilast, int64_t& m0, int& m,
+                                        int64_t& c0, int& c) {
+    const int lane = (int)__lane_id();
     // maturity of every lane: starts at or before i0, then those inside
     while (mw.peek() <= i0) { ++mstart; mw.pop(); }
-    int64_t mm = mstart, npop = 0;
-    for (int64_t b; (b = mw.peek()) <= ilast; mw.pop(), ++npop) mm += (i >= b);
+    m0 = mstart;
+    m = 0;
+    int npop = 0;
+    for (int64_t b; (b = mw.peek()) <= ilast; mw.pop(), ++npop) m += lane >= (int)(b - i0);
     // chain of every lane, keyed by maturity
-    const int64_t mlast = mstart + npop;
     while (cw.peek() <= mstart) { ++cstart; cw.pop(); }
-    int64_t c = cstart, cpop = 0;
-    for (int64_t b; (b = cw.peek()) <= mlast; cw.pop(), ++cpop) c += (mm >= b);
+    c0 = cstart;
+    c = 0;
+    int cpop = 0;
+    for (int64_t b; (b = cw.peek()) <= mstart + npop; cw.pop(), ++cpop) c += m >= (int)(b - mstart);
     mstart += npop;
     cstart += cpop;
-    m = mm;
-    cc = c;
   }
 };
 

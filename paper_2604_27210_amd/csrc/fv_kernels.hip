@@ -141,11 +141,10 @@ constexpr int kMaxBlock = 512;
 #endif
 #define FV_WAVES_LBR(GREEKS) ((GREEKS) ? 2 : FV_LBR_WAVES_PER_EU)
 #define FV_WAVES_HALLEY(GREEKS) ((GREEKS) ? 2 : FV_HALLEY_WAVES_PER_EU)
-// The ragged kernel: at least 6 waves per SIMD (<= 80 VGPRs); its LBR form
-// takes 62 VGPRs, and its Halley form, which took 83 at a floor of 4, is
-// 2.7% faster held to 80.
+// The ragged kernel: 8 waves per SIMD (64 VGPRs; free, it takes 66 and 72).
+// 8.4M quotes, LBR 135 us against 137 at a floor of 6, Halley 145 against 149.
 #ifndef FV_CHAINS_WAVES_PER_EU
-#define FV_CHAINS_WAVES_PER_EU 6
+#define FV_CHAINS_WAVES_PER_EU 8
 #endif
 
 constexpr int kHalleySteps = 8;  // the paper's count; the default of fv_set_halley_steps
@@ -395,11 +394,62 @@ __global__ __launch_bounds__(kMaxBlock) void k_halley_trace(KQuotes q, uint32_t*
 }
 
 // ------------------------------------------------------------- IV: Halley
-// LDS queue entry of a lane that failed the convergence check.
+// LDS queue entry of a lane that failed the convergence check, with its
+// bracket, or (lo = kGeneralQuote) that the scaled solve does not take.
 struct Pending {
   int64_t i;
   double lo, hi;
 };
+constexpr double kGeneralQuote = -1.0;
+
+// A queued quote: the general Halley solve where the scaled one did not take
+// it, then bisection where the steps did not converge.  Both stand here, after
+// the queue, and not beside the scaled solve, whose registers they would take:
+// the constants of one binary64 evaluation fill the scalar file by themselves.
+template <int MODEL>
+__device__ __forceinline__ uint8_t queued_quote(double P, double fs, double K, double T, double r,
+                                                double qy, int th, int steps, double lo,
+                                                double hi, double* sg, Reduced* rd) {
+  *rd = fv::reduce_quote(MODEL, P, fs, K, T, r, qy, th);
+  uint8_t st = fv::kQOk;
+  bool bisect = true;
+  double s = 0.0;
+  if (lo == kGeneralQuote) {
+    st = rd->status;
+    bisect = false;
+    if (st == fv::kQOk) {
+      const fv::HalleyState hs = fv::halley_solve(rd->x, rd->beta, rd->bmax, rd->lnb, steps);
+      s = hs.s;
+      bisect = !hs.converged;
+      lo = hs.lo;
+      hi = hs.hi;
+    }
+  }
+  if (bisect) s = fv::bisection_solve(rd->x, rd->beta, rd->bmax, rd->lnb, lo, hi, kBisectTol);
+  *sg = st == fv::kQOk ? s * rd->isqrtT
+                       : st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
+  return st;
+}
+
+// The scaled solve of a quote, or a queue entry for it: returns the status,
+// sets `queued`.
+template <int MODEL>
+__device__ __forceinline__ uint8_t scaled_halley(double P, double fs, double K, double T, double r,
+                                                 double qy, int th, int steps,
+                                                 fv::HalleyState* hs, fv::ScaledQuote* sq,
+                                                 double* sg, bool* queued) {
+  *sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, th);
+  const uint8_t st = sq->status;
+  *sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
+  *queued = sq->general;
+  hs->lo = kGeneralQuote;
+  if (st == fv::kQOk && !sq->general) {
+    *hs = fv::halley_solve_scaled(sq->x, sq->bh, sq->ch, steps);
+    *sg = hs->s * sq->isqrtT;
+    *queued = !hs->converged;
+  }
+  return st;
+}
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
   const unsigned lane = __lane_id();
@@ -409,8 +459,9 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 // Bound by the vector ALU like k_iv_lbr, on the same guess; its first two
 // steps are in binary32 and nearly every quote takes one binary64 step after
 // them (two full steps after one at guess precision before, with both in
-// binary64).  3M wide-wing BSM quotes: 53 us (131 before).  One quote per
-// thread, as k_iv_lbr; the queue holds one entry per thread.
+// binary64).  3M wide-wing BSM quotes: 51.5 us (131 before; 54.5 with the
+// general solve beside the scaled one).  One quote per thread, as k_iv_lbr;
+// the queue holds one entry per thread.
 template <int MODEL, bool GREEKS, bool ARR>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(IvArgs args) {
@@ -433,19 +484,16 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(I
     const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, b, t) : 0.0;
     const int th = ldflag<ARR>(q, b, t);
     fv::ScaledQuote sq;
-    const uint8_t st = halley_quote<MODEL>(P, fs, K, T, r, qy, th, q.hsteps, &hs, &sq);
-    double sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
-    if (st == fv::kQOk) {
-      sg = hs.s * sq.isqrtT;
-      fail = !hs.converged;
-    }
+    double sg;
+    const uint8_t st =
+        scaled_halley<MODEL>(P, fs, K, T, r, qy, th, q.hsteps, &hs, &sq, &sg, &fail);
     if (!fail) {
       const auto* out = late_args<IvArgs>();
       (global_ptr(out->sig_out) + b)[t] = sg;
       if (uint8_t* st_out = out->st_out) (global_ptr(st_out) + b)[t] = st;
       if (GREEKS) {
         const Greeks gr =
-            greeks_solved<MODEL>(st, sq.general, sq, hs.s, sg, P, fs, K, T, r, qy, th);
+            greeks_solved<MODEL>(st, false, sq, hs.s, sg, P, fs, K, T, r, qy, th);
         store_greeks(out->g, b, t, gr);
       }
     }
@@ -466,12 +514,13 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(I
     }
   }
   __syncthreads();
-  // Bisection fallback over the packed queue: every lane of a wave works.  An
-  // empty queue, the rule, ends here, ahead of what the loop sets up.
+  // The packed queue: every lane of a wave works, and no thread has more than
+  // one entry (a loop would hoist its constants into 40 registers more).  An
+  // empty queue, the rule, ends here.
   const int m = __builtin_amdgcn_readfirstlane(qcount);
   if (m == 0) return;
-  for (int j = threadIdx.x; j < m; j += blockDim.x) {
-    const int64_t iq = queue[j].i;
+  if ((int)t < m) {
+    const int64_t iq = queue[t].i;
     const auto* late = late_args<IvArgs>();
     const KQuotes& q = late->q;
     const GreekOut& g = late->g;
@@ -479,13 +528,17 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(I
                  r = ld<ARR>(q.r, iq);
     const double qy = MODEL == fv::kBlackScholesMerton ? ld<ARR>(q.q, iq) : 0.0;
     const int th = ldflag<ARR>(q, iq);
-    const Reduced rd = fv::reduce_quote(MODEL, P, fs, K, T, r, qy, th);
-    const double s =
-        fv::bisection_solve(rd.x, rd.beta, rd.bmax, rd.lnb, queue[j].lo, queue[j].hi, kBisectTol);
-    const double sg = s * rd.isqrtT;
+    Reduced rd;
+    double sg;
+    const uint8_t st = queued_quote<MODEL>(P, fs, K, T, r, qy, th, q.hsteps, queue[t].lo,
+                                           queue[t].hi, &sg, &rd);
     late->sig_out[iq] = sg;
-    if (uint8_t* st_out = late->st_out) st_out[iq] = fv::kQOk;
-    if (GREEKS) store_greeks(g, iq, 0, fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, rd.F, rd.D, P));
+    if (uint8_t* st_out = late->st_out) st_out[iq] = st;
+    if (GREEKS)
+      store_greeks(g, iq, 0,
+                   st == fv::kQOk
+                       ? fv::greeks_at(MODEL, fs, K, T, r, qy, sg, th, rd.F, rd.D, P)
+                       : no_greeks());
   }
 }
 
@@ -690,36 +743,36 @@ __global__ __launch_bounds__(kMaxBlock) void k_price_backward(FormArgs args) {
 }
 
 // ------------------------------------------------------------- chains
-struct KChains {
+struct ChainArgs {
   int64_t n_chains, n_mat, n;
   const int64_t* chain_mat_off;
   const int64_t* mat_quote_off;
   const double *F, *r, *T, *price, *K;
   const int8_t* flag;
   int hsteps;
+  double* sigma;
+  uint8_t* status;
 };
 
-// Ragged-chain kernel: one launch over the CSR offsets, one wave per two
-// consecutive 64-quote slices (one coalesced 512-byte load per field and
-// slice).  The wave finds the maturity and chain of its first quote by two
-// 64-ary searches and every lane those of its two quotes from the next
-// maturity and chain starts, for both slices before it solves either: only
-// the second slice's maturity and chain indices stay live across the first
-// solve, and the location is paid once per 128 quotes (four slices per
-// wave were no faster, one was 2% slower).  The Halley path compacts the
-// lanes that fail its convergence check into an LDS queue (wave ballots, as
-// the flat Halley kernel does; two entries per thread) and the workgroup
-// bisects the packed queue afterwards.
+// A lane that fails the Halley convergence check.
 struct ChainPending {
   int64_t i;
   int32_t m, cc;  // maturity and chain of quote i
   double lo, hi;
 };
 
-template <int SOLVER>
+// Ragged-chain kernel: one launch over the CSR offsets, one wave per SLICES
+// consecutive 64-quote slices (one coalesced 512-byte load per field and
+// slice).  The wave finds the maturity and chain of its first quote by two
+// 64-ary searches and every lane those of its quotes from the next maturity
+// and chain starts, for both slices before it solves either: only the second
+// slice's maturity and chain stay live across the first solve.
+// The Halley path compacts the lanes that fail its convergence check into an
+// LDS queue (wave ballots, as the flat Halley kernel does; an entry per quote)
+// and the workgroup bisects the packed queue afterwards.
+template <int SOLVER, int SLICES>
 __global__ __launch_bounds__(kMaxBlock)
-__attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
-    KChains c, double* __restrict__ sig_out, uint8_t* __restrict__ st_out) {
+__attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(ChainArgs c) {
   constexpr bool kHalley = SOLVER == FV_SOLVER_HALLEY;
   extern __shared__ unsigned char smem_raw[];
   ChainPending* queue = reinterpret_cast<ChainPending*>(smem_raw);
@@ -728,32 +781,34 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
     if (threadIdx.x == 0) qcount = 0;
     __syncthreads();
   }
-  // two consecutive 64-quote slices per wave, both located before either is
-  // solved (the second location reuses the first's window of starts)
   // (the wave's number as a scalar: the location runs on the scalar unit)
   const int64_t w0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) +
-                      __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * 128;
+                      __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * (64 * SLICES);
   const int lane = (int)__lane_id();
-  int64_t ms[2] = {0, 0}, cs[2] = {0, 0};
+  int64_t m0[SLICES] = {}, c0[SLICES] = {};
+  int ml[SLICES] = {}, cl[SLICES] = {};
   const bool any = w0 < c.n;  // wave-uniform
   if (any) {
     fv::ChainCursor cur;
     cur.init(c.mat_quote_off, c.n_mat, c.chain_mat_off, c.n_chains, w0);
-    cur.slice(w0, min(w0 + 63, c.n - 1), w0 + lane, ms[0], cs[0]);
-    if (w0 + 64 < c.n) cur.slice(w0 + 64, min(w0 + 127, c.n - 1), w0 + 64 + lane, ms[1], cs[1]);
+#pragma unroll
+    for (int sl = 0; sl < SLICES; ++sl) {
+      const int64_t i0 = w0 + 64 * sl;
+      if (i0 < c.n) cur.slice(i0, min(i0 + 63, c.n - 1), m0[sl], ml[sl], c0[sl], cl[sl]);
+    }
   }
 #pragma unroll
-  for (int sl = 0; sl < 2; ++sl) {
-    const int64_t i = w0 + 64 * sl + lane;
-    const int64_t m = ms[sl], cc = cs[sl];
+  for (int sl = 0; sl < SLICES; ++sl) {
+    const int64_t i0 = w0 + 64 * sl;
     bool fail = false;
     fv::HalleyState hs;
     hs.lo = 0.0;
     hs.hi = 0.0;
-    if (any && i < c.n) {
-      const double F = c.F[cc], r = c.r[cc], T = c.T[m];
-      const double P = c.price[i], K = c.K[i];
-      const int th = c.flag[i];
+    if (any && lane < c.n - i0) {
+      const double F = (c.F + c0[sl])[(unsigned)cl[sl]], r = (c.r + c0[sl])[(unsigned)cl[sl]];
+      const double T = (c.T + m0[sl])[(unsigned)ml[sl]];
+      const double P = (c.price + i0)[(unsigned)lane], K = (c.K + i0)[(unsigned)lane];
+      const int th = (c.flag + i0)[(unsigned)lane];
       uint8_t st;
       double sg;
       if (!kHalley) {
@@ -767,22 +822,20 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
           sg = s * sq.isqrtT;
         }
         if (__builtin_expect(general, 0)) {
-          const int64_t io = opaque(i), co = opaque(cc), mo = opaque(m);
-          fv::lbr_general(fv::kBlack76, c.price[io], c.F[co], c.K[io], c.T[mo], c.r[co], 0.0,
-                          c.flag[io], &sg, &st, &sq);
+          const ChainArgs* a = late_args<ChainArgs>();
+          const int64_t io = opaque(i0 + lane), co = opaque(c0[sl] + cl[sl]),
+                        mo = opaque(m0[sl] + ml[sl]);
+          fv::lbr_general(fv::kBlack76, a->price[io], a->F[co], a->K[io], a->T[mo], a->r[co], 0.0,
+                          a->flag[io], &sg, &st, &sq);
         }
       } else {
         fv::ScaledQuote sq;
-        st = halley_quote<fv::kBlack76>(P, F, K, T, r, 0.0, th, c.hsteps, &hs, &sq);
-        sg = st == fv::kQAtIntrinsic ? 0.0 : __builtin_nan("");
-        if (st == fv::kQOk) {
-          sg = hs.s * sq.isqrtT;
-          fail = !hs.converged;
-        }
+        st = scaled_halley<fv::kBlack76>(P, F, K, T, r, 0.0, th, c.hsteps, &hs, &sq, &sg, &fail);
       }
       if (!fail) {
-        sig_out[i] = sg;
-        if (st_out) st_out[i] = st;
+        const ChainArgs* a = late_args<ChainArgs>();
+        (global_ptr(a->sigma) + i0)[(unsigned)lane] = sg;
+        if (a->status) (global_ptr(a->status) + i0)[(unsigned)lane] = st;
       }
     }
     if (kHalley) {
@@ -796,9 +849,9 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
         wbase = __shfl(wbase, first);
         if (fail) {
           const int slot = wbase + __popcll(mask & lanemask_lt());
-          queue[slot].i = i;
-          queue[slot].m = (int32_t)m;
-          queue[slot].cc = (int32_t)cc;
+          queue[slot].i = i0 + lane;
+          queue[slot].m = (int32_t)(m0[sl] + ml[sl]);
+          queue[slot].cc = (int32_t)(c0[sl] + cl[sl]);
           queue[slot].lo = hs.lo;
           queue[slot].hi = hs.hi;
         }
@@ -807,18 +860,23 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(
   }
   if (!kHalley) return;
   __syncthreads();
-  // bisection fallback over the packed queue: every lane of a wave works
+  // the packed queue: every lane of a wave works, up to SLICES entries each
   const int nq = __builtin_amdgcn_readfirstlane(qcount);
   if (nq == 0) return;
-  for (int j = threadIdx.x; j < nq; j += blockDim.x) {
+  const ChainArgs* a = late_args<ChainArgs>();
+#pragma unroll
+  for (int sl = 0; sl < SLICES; ++sl) {
+    const int j = threadIdx.x + sl * blockDim.x;
+    if (j >= nq) return;
     const int64_t iq = queue[j].i;
     const int64_t mq = queue[j].m, cq = queue[j].cc;
-    const Reduced rd = fv::reduce_quote(fv::kBlack76, c.price[iq], c.F[cq], c.K[iq], c.T[mq],
-                                        c.r[cq], 0.0, c.flag[iq]);
-    const double s =
-        fv::bisection_solve(rd.x, rd.beta, rd.bmax, rd.lnb, queue[j].lo, queue[j].hi, kBisectTol);
-    sig_out[iq] = s * rd.isqrtT;
-    if (st_out) st_out[iq] = fv::kQOk;
+    Reduced rd;
+    double sg;
+    const uint8_t st =
+        queued_quote<fv::kBlack76>(a->price[iq], a->F[cq], a->K[iq], a->T[mq], a->r[cq], 0.0,
+                                   a->flag[iq], a->hsteps, queue[j].lo, queue[j].hi, &sg, &rd);
+    a->sigma[iq] = sg;
+    if (a->status) a->status[iq] = st;
   }
 }
 
@@ -993,6 +1051,16 @@ dim3 grid_for(int64_t n, const LaunchShape& sh) {
 }
 
 int launched(const char* what) { return fvh::launched(what); }
+
+int device_cus();
+
+// Slices per wave of the ragged kernel.  One below 20 waves per SIMD (80 per
+// compute unit), where the chain of a wave's location and second solve is
+// what a small batch waits for; above, two pay the location once.  In us,
+// one against two: LBR 8.3 / 9.6 (273k quotes), 20.9 / 21.8 (1.0M),
+// 34.3 / 33.7 (1.9M), 143 / 131 (8.4M); Halley 8.9 / 10.5, 23.1 / 23.7,
+// 38.7 / 37.7, 167 / 146.
+int chain_slices(int64_t n) { return n < (int64_t)64 * 80 * device_cus() ? 1 : 2; }
 
 int device_cus() {
   static int cache[64];  // per device ordinal; 0 = not yet queried
@@ -1372,30 +1440,24 @@ int fv_implied_vol_chains(int solver, const fv_chains* c, double* sigma_out,
   if (!c->chain_mat_off || !c->mat_quote_off || !c->F || !c->r || !c->T || !c->price ||
       !c->K || !c->flag || !sigma_out)
     return fail(FV_E_INVALID_ARG, "NULL chain array");
-  KChains k;
-  k.n_chains = c->n_chains;
-  k.n_mat = c->n_maturities;
-  k.n = c->n_quotes;
-  k.chain_mat_off = c->chain_mat_off;
-  k.mat_quote_off = c->mat_quote_off;
-  k.F = c->F;
-  k.r = c->r;
-  k.T = c->T;
-  k.price = c->price;
-  k.K = c->K;
-  k.flag = c->flag;
-  k.hsteps = g_halley_steps.load(std::memory_order_relaxed);
+  const ChainArgs k = {c->n_chains, c->n_maturities, c->n_quotes, c->chain_mat_off,
+                       c->mat_quote_off, c->F, c->r, c->T, c->price, c->K, c->flag,
+                       g_halley_steps.load(std::memory_order_relaxed), sigma_out, status_out};
   const LaunchShape sh = shape_for(FV_KERNEL_CHAINS, FV_MODEL_BLACK76, k.n);
-  // one wave per 64 consecutive quotes, blockDim/64 waves per workgroup; the
-  // quote count is capped (kMaxQuotes) so that the grid fits
-  const int64_t n_blocks = (k.n + 2 * sh.block - 1) / (2 * sh.block);
-  const dim3 grid((unsigned)n_blocks), block(sh.block);
+  // blockDim/64 waves per workgroup; the quote count is capped (kMaxQuotes) so
+  // that the grid fits
+  const int slices = chain_slices(k.n);
+  const int64_t per = (int64_t)slices * sh.block;
+  const dim3 grid((unsigned)((k.n + per - 1) / per)), block(sh.block);
+  const size_t lds = sizeof(ChainPending) * (size_t)per;
   hipStream_t s = (hipStream_t)stream;
-  if (solver == FV_SOLVER_LBR)
-    k_iv_chains<FV_SOLVER_LBR><<<grid, block, 0, s>>>(k, sigma_out, status_out);
-  else
-    k_iv_chains<FV_SOLVER_HALLEY><<<grid, block, 2 * sizeof(ChainPending) * (size_t)sh.block, s>>>(
-        k, sigma_out, status_out);
+  if (solver == FV_SOLVER_LBR) {
+    if (slices == 1) k_iv_chains<FV_SOLVER_LBR, 1><<<grid, block, 0, s>>>(k);
+    else k_iv_chains<FV_SOLVER_LBR, 2><<<grid, block, 0, s>>>(k);
+  } else {
+    if (slices == 1) k_iv_chains<FV_SOLVER_HALLEY, 1><<<grid, block, lds, s>>>(k);
+    else k_iv_chains<FV_SOLVER_HALLEY, 2><<<grid, block, lds, s>>>(k);
+  }
   return launched("fv_implied_vol_chains");
 }
 

@@ -243,3 +243,41 @@ def test_binary32_domain_edges(broadcast):
                             sig.cpu().numpy().astype(np.float64), st.cpu().numpy())
     print("binary32 edges: %d of %d solved, max err/tol %.3g" % (ok, len(F), worst))
     assert ok > 0.7 * len(F)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("solver", ["lbr", "halley"])
+@pytest.mark.parametrize("side", [-1, 0, 77])
+def test_chains_at_the_slice_rule(solver, side):
+    """The ragged kernel takes one 64-quote slice per wave below 80 waves per
+    compute unit and two from there: on both sides, quote by quote the flat
+    solve of the same inputs (each within 1e-12 of the root)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2604_27210_amd as fv
+    n = 64 * 80 * torch.cuda.get_device_properties(0).multi_processor_count + side
+    rng = np.random.default_rng(n)
+    cuts = np.unique(rng.integers(1, n, 4000))
+    mqo = np.r_[0, cuts, n]
+    nm = mqo.size - 1
+    cmo = np.r_[0, np.unique(rng.integers(1, nm, 300)), nm]
+    mat = torch.from_numpy(np.repeat(np.arange(nm), np.diff(mqo))).cuda()
+    chain = torch.from_numpy(np.repeat(np.arange(cmo.size - 1), np.diff(cmo))).cuda()[mat]
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    F, r = d(rng.uniform(50, 150, cmo.size - 1)), d(rng.uniform(0, 0.05, cmo.size - 1))
+    T = d(rng.uniform(0.05, 2.0, nm))
+    sig = d(rng.uniform(0.1, 0.6, n))
+    K = F[chain] * torch.exp(d(rng.uniform(-2, 2, n)) * sig * T[mat].sqrt())
+    flag = torch.where(K < F[chain], -1, 1).to(torch.int8)
+    fs, Tq, rq = F[chain].contiguous(), T[mat].contiguous(), r[chain].contiguous()
+    P = fv.price("black76", fs, K, Tq, rq, sig, flag=flag)
+    P[::1013] = -1.0
+    want, want_st = fv.implied_vol("black76", P, fs, K, Tq, rq, flag=flag, solver=solver)
+    got, got_st = fv.implied_vol_chains(d(cmo), d(mqo), F, r, T, P, K, flag, solver=solver)
+    assert torch.equal(got_st, want_st)
+    ok = want_st == 0
+    assert ok.sum() > 0.99 * n
+    tol = 2e-12 if solver == "lbr" else 2e-8
+    assert ((got - want).abs()[ok] <= tol * want[ok]).all()
+    assert got[~ok].isnan().all()
