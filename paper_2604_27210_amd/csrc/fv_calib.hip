@@ -19,8 +19,8 @@
 //      maturity where it holds more than one; each (wave, maturity) run
 //      stores its five sums at index wave + maturity (unique: along the
 //      quotes both indices only grow, and each run changes at least one), so
-//      no atomics are needed and results are bitwise reproducible; the wave
-//      stores its sum of squared errors; the first thread also advances the
+//      no atomics are needed and results are bitwise reproducible; each
+//      workgroup stores its sum of squared errors; the first thread also advances the
 //      step counter and forms Adam's bias corrections;
 //   3. eight lanes per maturity: the sums of its runs -> gradient -> Adam
 //      update; one workgroup more sums the squared errors to the loss, in a
@@ -68,7 +68,7 @@ enum SumField : int {
   kSumGIrt,    // sum g_w / sqrt((k - m)^2 + s^2)
   kSumCount
 };
-constexpr int kRecord = 6;  // doubles of workspace per run: its sums, and one for wave_e2
+constexpr int kRecord = 6;  // doubles of workspace per run: its sums, and one for block_e2
 // Control block at the start of the workspace: Adam's bias corrections of
 // the step.
 enum CtlField : int { kCtlC1, kCtlC2, kCtlCount };
@@ -116,8 +116,8 @@ constexpr int kWavesPerBlock = kCalibBlock / 64;
 int64_t n_waves_of(int64_t n) { return (n + 63) / 64; }
 
 // workspace layout (doubles): control block, per-maturity records, the runs'
-// sums, then each wave's sum of squared errors (there are at least as many
-// runs as waves, so a double a run holds them).  ceil(n_mat / 4) more are
+// sums, then each gradient workgroup's sum of squared errors (there are at
+// least as many runs as waves, so a double a run holds them).  ceil(n_mat / 4) more are
 // part of the documented size and not used.
 int64_t workspace_doubles(int64_t n_mat, int64_t n) {
   return kCtlCount + kNatCount * n_mat + (n_mat + 3) / 4 + kRecord * (n_waves_of(n) + n_mat);
@@ -220,24 +220,14 @@ __device__ __forceinline__ double fold16(double a, double b) {
          __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
 }
 
-__global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_svi_grad(
-    KSvi c, const double* __restrict__ nat, double* __restrict__ ctl, double* __restrict__ part,
-    double* __restrict__ wave_e2, int64_t* __restrict__ step, double b1, double b2) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    // the step's counter and bias corrections; nothing else in this launch
-    // reads them, k_svi_adam runs after it on the stream
-    const int64_t t = *step + 1;
-    *step = t;
-    ctl[kCtlC1] = 1.0 - pow(b1, (double)t);
-    ctl[kCtlC2] = 1.0 - pow(b2, (double)t);
-  }
-  // the wave's number as a scalar, so that the location below runs on the
-  // scalar unit
-  const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock +
-                       __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+// One wave of the gradient: its runs' sums to `part`; returns its sum of
+// squared errors, in lane 32.
+__device__ __forceinline__ double grad_wave(const KSvi& c, int64_t wave,
+                                            const double* __restrict__ nat,
+                                            double* __restrict__ part) {
   const int lane = (int)__lane_id();
   const int64_t w0 = wave * 64;
-  if (w0 >= c.n) return;  // wave-uniform
+  if (w0 >= c.n) return 0.0;  // wave-uniform
   fv::ChainCursor cur;
   cur.init(c.mat_quote_off, c.n_mat, c.chain_mat_off, c.n_chains, w0);
   const int64_t i = w0 + lane;
@@ -322,15 +312,15 @@ __global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))
     const double w01 = fold16(fold32(v[0], v[3]), fold32(v[1], v[4]));
     const double w2 = fold32(v[2], e2);
     const double y = row_sum(w01), z = row_sum(fold16(w2, w2));
-    // rows 0 .. 3 hold sums 0, 1, 3, 4; the lower half 2, the upper e2
+    // rows 0 .. 3 hold sums 0, 1, 3, 4; the lower half 2, the upper e2 (lane 32
+    // is read)
     if ((lane & 15) == 0) {
       const int row = lane >> 4;
       double* o = part + kSumCount * (wave + m);
       o[row + (row >> 1)] = y;
       if (row == 0) o[2] = z;
-      if (row == 2) wave_e2[wave] = z;
     }
-    return;
+    return z;
   }
   // Segmented suffix sums over the lanes keyed by maturity: the maturity is
   // non-decreasing along the lanes, so equal keys at distance `off` enclose
@@ -353,15 +343,41 @@ __global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
     for (int j = 0; j < kSumCount; ++j) o[j] = v[j];
   }
-  e2 = row_sum(fold16(fold32(e2, e2), fold32(e2, e2)));
-  if (lane == 0) wave_e2[wave] = e2;
+  return row_sum(fold16(fold32(e2, e2), fold32(e2, e2)));
+}
+
+__global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_svi_grad(
+    KSvi c, const double* __restrict__ nat, double* __restrict__ ctl, double* __restrict__ part,
+    double* __restrict__ block_e2, int64_t* __restrict__ step, double b1, double b2) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    // the step's counter and bias corrections; nothing else in this launch
+    // reads them, k_svi_adam runs after it on the stream
+    const int64_t t = *step + 1;
+    *step = t;
+    ctl[kCtlC1] = 1.0 - pow(b1, (double)t);
+    ctl[kCtlC2] = 1.0 - pow(b2, (double)t);
+  }
+  // the wave's number as a scalar, so that the location runs on the scalar
+  // unit
+  const int wib = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const double e2 = grad_wave(c, (int64_t)blockIdx.x * kWavesPerBlock + wib, nat, part);
+  // one squared-error sum per workgroup: the loss is summed by one workgroup,
+  // which a sum per wave kept 2.5 us longer than the update beside it
+  __shared__ double wave_e2[kWavesPerBlock];
+  if (__lane_id() == 32) wave_e2[wib] = e2;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = wave_e2[0];
+    for (int j = 1; j < kWavesPerBlock; ++j) t += wave_e2[j];
+    block_e2[blockIdx.x] = t;
+  }
 }
 
 // Adam with the counter and bias corrections k_svi_grad set, eight lanes per
 // maturity (5.3 runs each on the 500-chain problem): lane l sums the runs l,
 // l + 8, ... in order, a fixed butterfly over the eight completes the five
 // sums, and lane j < 5 updates parameter j.  One workgroup more, the first,
-// sums the waves' squared errors to the loss in a fixed order meanwhile.
+// sums the workgroups' squared errors to the loss in a fixed order meanwhile.
 // Launch latency and a chain of dependent loads bound it: 7,243 maturities
 // 7.3 us, loss included (9.9 and 4.6 us with a wave per maturity and a launch
 // for the loss).
@@ -371,15 +387,15 @@ __global__ __launch_bounds__(kAdamBlock) void k_svi_adam(
     int64_t n_mat, int64_t n, const int64_t* __restrict__ mat_quote_off,
     const double* __restrict__ nat, const double* __restrict__ part, double* __restrict__ theta,
     double* __restrict__ am, double* __restrict__ av, double* __restrict__ grad,
-    const double* __restrict__ ctl, const double* __restrict__ wave_e2, int64_t waves,
+    const double* __restrict__ ctl, const double* __restrict__ block_e2, int64_t blocks,
     const int64_t* __restrict__ step, double* __restrict__ loss, int64_t loss_len, double lr,
     double b1, double b2, double eps) {
   if (blockIdx.x == 0) {
     if (loss_len == 0) return;
     __shared__ double red[kAdamBlock / 64];
     double a = 0.0;
-#pragma unroll 16
-    for (int64_t w = threadIdx.x; w < waves; w += kAdamBlock) a += wave_e2[w];
+#pragma unroll 8
+    for (int64_t w = threadIdx.x; w < blocks; w += kAdamBlock) a += block_e2[w];
     a = row_sum(fold16(fold32(a, a), fold32(a, a)));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
@@ -500,15 +516,15 @@ int launch_step(const fv_svi_problem* p, double* theta, double* adam_m, double* 
   const KSvi k = to_k(p);
   hipStream_t s = (hipStream_t)stream;
   const Workspace w = carve(ws, k.n_mat, k.n);
-  const int64_t waves = n_waves_of(k.n);
+  const int64_t blocks = (n_waves_of(k.n) + kWavesPerBlock - 1) / kWavesPerBlock;
   const int64_t nb = (k.n_mat + kAdamPerBlock - 1) / kAdamPerBlock + 1;
   k_svi_prep<<<dim3((unsigned)((k.n_mat + kPrepBlock - 1) / kPrepBlock)), dim3(kPrepBlock), 0,
                s>>>(k.n_mat, k.T, theta, w.nat);
-  k_svi_grad<<<dim3((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kCalibBlock),
-               0, s>>>(k, w.nat, w.ctl, w.part, w.e2, step, p->beta1, p->beta2);
+  k_svi_grad<<<dim3((unsigned)blocks), dim3(kCalibBlock), 0, s>>>(
+      k, w.nat, w.ctl, w.part, w.e2, step, p->beta1, p->beta2);
   k_svi_adam<<<dim3((unsigned)nb), dim3(kAdamBlock), 0, s>>>(
       k.n_mat, k.n, k.mat_quote_off, w.nat, w.part, theta, adam_m, adam_v, grad, w.ctl, w.e2,
-      waves, step, loss, loss ? loss_len : 0, p->lr, p->beta1, p->beta2, p->eps);
+      blocks, step, loss, loss ? loss_len : 0, p->lr, p->beta1, p->beta2, p->eps);
   return fvh::launched("fv_svi_adam_step");
 }
 
