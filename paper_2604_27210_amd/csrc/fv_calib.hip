@@ -346,7 +346,13 @@ __device__ __forceinline__ double grad_wave(const KSvi& c, int64_t wave,
   return row_sum(fold16(fold32(e2, e2), fold32(e2, e2)));
 }
 
-__global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_svi_grad(
+// Bound by the vector ALU (about 850 instructions per 64 quotes, a sixth of
+// them the location and a tenth the sums): 1.9M quotes in 7,243 maturities
+// 46 us (the step's start: 81).  At least 7 waves per SIMD: free, it takes 74
+// registers, two too many, and ten steps take 530 us for 517 (below 0.5M
+// quotes, where waves are few, the floor costs 1%).  Two slices per wave, as
+// in the ragged solve, were 1 to 15% slower.
+__global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_svi_grad(
     KSvi c, const double* __restrict__ nat, double* __restrict__ ctl, double* __restrict__ part,
     double* __restrict__ block_e2, int64_t* __restrict__ step, double b1, double b2) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -379,7 +385,7 @@ __global__ __launch_bounds__(kCalibBlock) __attribute__((amdgpu_waves_per_eu(4))
 // sums, and lane j < 5 updates parameter j.  One workgroup more, the first,
 // sums the workgroups' squared errors to the loss in a fixed order meanwhile.
 // Launch latency and a chain of dependent loads bound it: 7,243 maturities
-// 7.3 us, loss included (9.9 and 4.6 us with a wave per maturity and a launch
+// 4.9 us, loss included (9.9 and 4.6 us with a wave per maturity and a launch
 // for the loss).
 constexpr int kAdamBlock = 1024;
 constexpr int kAdamPerBlock = kAdamBlock / 8;
