@@ -334,13 +334,13 @@ __host__ __device__ __attribute__((always_inline)) inline bool halley_solve_scal
   q.ch = sq.ch;
   float s = s32::initial_guess(q.bh, q.ch, q);
   const s32::Eval e0 = s32::eval<s32::kFitStep>(q.ax, s);
-  s = fmaf(s, s32::householder3(q, e0, s), s);
+  s = fmaf(s, s32::householder3(q, e0), s);
   bool done = false;
   for (int k = 1; k < steps && !done; ++k) {
     const s32::Eval e = s32::eval<s32::kFitSolve>(q.ax, s);
-    const float W = s32::kSqrt2Pi * s32::exp(e.g2);  // b_max/b'
+    const float W = s32::exp_sqrt2pi(e.g2);  // b_max/b'
     const float n = (e.comp ? fmaf(-q.ch, W, e.rho) : fmaf(q.bh, W, -e.rho)) * e.is;
-    const float H = e.h2 - 0.25f * s * s;
+    const float H = e.H;
     const float d = n * s32::rcp(fmaf(0.5f * H, n, 1.0f));
     s = fmaf(s, d, s);
     done = fabsf(d) <= 1e-5f && fabsf(n) * (1.0f + fabsf(H)) <= 1e-2f;

@@ -281,8 +281,8 @@ __device__ __forceinline__ Greeks greeks_solved(uint8_t st, bool general,
 // ------------------------------------------------------------- IV: LBR
 // Bound by the vector ALU's issue rate: about 570 vector instructions per
 // quote, every side of the guess a mixed wave takes included (1,157 with the
-// guess and the first step in binary64).  10M wide-wing BSM quotes: 155 us
-// (355 with those), 1M BS quotes with the five Greeks: 26.5 us (54).
+// guess and the first step in binary64).  10M wide-wing BSM quotes: 154 us
+// (355 with those), 1M BS quotes with the five Greeks: 26 us (54).
 // One quote per thread: with a loop over several the compiler keeps the
 // polynomials' constants in registers across the whole solve, 110 VGPRs in
 // place of 55, and the book took 220 us where it then took 190.
@@ -459,7 +459,7 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 // Bound by the vector ALU like k_iv_lbr, on the same guess; its first two
 // steps are in binary32 and nearly every quote takes one binary64 step after
 // them (two full steps after one at guess precision before, with both in
-// binary64).  3M wide-wing BSM quotes: 51.5 us (131 before; 54.5 with the
+// binary64).  3M wide-wing BSM quotes: 51.2 us (131 before; 54.5 with the
 // general solve beside the scaled one).  One quote per thread, as k_iv_lbr;
 // the queue holds one entry per thread.
 template <int MODEL, bool GREEKS, bool ARR>
@@ -577,7 +577,7 @@ struct Pending32 {
 // in float arithmetic throughout.  Bound by the vector ALU: about 430 vector
 // instructions per quote (1,224 with the at-the-money start, whose lanes took
 // up to 8 steps and a wave its slowest lane's).  10M wide-wing BSM quotes:
-// 104 us (288 with that start).
+// 100 us (288 with that start).
 template <int MODEL, bool ARR>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_iv_halley32(
     Iv32Args args) {

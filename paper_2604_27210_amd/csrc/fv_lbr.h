@@ -435,7 +435,7 @@ __host__ __device__ __attribute__((always_inline)) inline bool lbr_solve_scaled(
   s32::Target q = scaled_target(x, bh, ch);
   const float s0 = s32::initial_guess(bh, ch, q);
   const s32::Eval e = s32::eval<s32::kFitStep>(q.ax, s0);
-  double s = (double)fmaf(s0, s32::householder3(q, e, s0), s0);
+  double s = (double)fmaf(s0, s32::householder3(q, e), s0);
   float w;
   bool comp;
   s += scaled_step<4>(x, bh, ch, s, &w, &comp);
@@ -614,8 +614,8 @@ __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_sol
   st.lo = 0.0;
   st.hi = 1e300;
   st.steps = steps >= 3 ? 2 : 1;
-  s0 = fmaf(s0, s32::halley(q, s32::eval<s32::kFitStep>(q.ax, s0), s0), s0);
-  if (steps >= 3) s0 = fmaf(s0, s32::halley(q, s32::eval<s32::kFitStep>(q.ax, s0), s0), s0);
+  s0 = fmaf(s0, s32::halley(q, s32::eval<s32::kFitStep>(q.ax, s0)), s0);
+  if (steps >= 3) s0 = fmaf(s0, s32::halley(q, s32::eval<s32::kFitStep>(q.ax, s0)), s0);
   double s = (double)s0;
   bool stop = false;
   float w;

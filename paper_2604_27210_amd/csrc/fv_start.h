@@ -8,7 +8,7 @@
 // polynomial step takes its constant as a 32-bit literal where binary64
 // first moves it into a register pair.  Per quote of the wide workload the
 // binary64 guess and first step took 640 vector and 270 scalar
-// instructions; these take about 280 and 40.
+// instructions; these take about 260 and 40.
 //
 // Binary32 cannot hold b itself deep in a wing, so everything is scaled by
 // the bound b_max = e^{x/2}: bh = b/b_max in (0, 1) and
@@ -37,6 +37,7 @@ constexpr float kSqrtPi = 1.77245385090551603f;
 constexpr float kSqrtPiOver2 = 1.25331413731550025f;
 constexpr float kTwoOverSqrtPi = 1.12837916709551257f;
 constexpr float kLnSqrt2Pi = 0.91893853320467274f;
+constexpr float kLog2Sqrt2Pi = 1.32574806473616065f;
 constexpr float kLog2E = 1.44269504088896341f;
 constexpr float kLn2 = 0.69314718055994531f;
 constexpr float kCl = 1.20919957615614523f;  // 2 pi/(3 sqrt3)
@@ -55,29 +56,32 @@ __host__ __device__ inline float sqrt(float x) {
   return sqrtf(x);
 #endif
 }
-__host__ __device__ inline float exp(float x) {
+__host__ __device__ inline float exp2(float x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_exp2f(x * kLog2E);
+  return __builtin_amdgcn_exp2f(x);
 #else
-  return exp2f(x * kLog2E);
+  return exp2f(x);
 #endif
 }
-__host__ __device__ inline float log(float x) {
+__host__ __device__ inline float log2(float x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_logf(x) * kLn2;
+  return __builtin_amdgcn_logf(x);
 #else
-  return log2f(x) * kLn2;
+  return log2f(x);
 #endif
+}
+__host__ __device__ inline float exp(float x) { return exp2(x * kLog2E); }
+__host__ __device__ inline float log(float x) { return log2(x) * kLn2; }
+// sqrt(2 pi) e^x and e^-x/sqrt(2 pi), the factor in the exponent
+__host__ __device__ inline float exp_sqrt2pi(float x) { return exp2(fmaf(x, kLog2E, kLog2Sqrt2Pi)); }
+__host__ __device__ inline float exp_over_sqrt2pi(float x) {
+  return exp2(fmaf(-x, kLog2E, -kLog2Sqrt2Pi));
 }
 // ln of a positive normal binary64 number of any exponent
 __host__ __device__ inline float log_of(double v) {
   int e;
   const float m = (float)frexp(v, &e);
-#if defined(__HIP_DEVICE_COMPILE__)
-  return (__builtin_amdgcn_logf(m) + (float)e) * kLn2;
-#else
-  return (log2f(m) + (float)e) * kLn2;
-#endif
+  return (log2(m) + (float)e) * kLn2;
 }
 
 __host__ __device__ inline float log_of(float v) { return log(v); }
@@ -103,10 +107,16 @@ __host__ __device__ inline float erfcx(float z) {
 // 1e-2: far within the few percent the guess is off; the caller knows the
 // form), of degree 9 for the binary32 steps (4e-7, 7e-6: they land as near),
 // or of degree 13 for the binary32 solver's own residual (6e-10).
+//
+// Everything is in hq = |h|/sqrt2 and tq = t/sqrt2, in which the erfcx
+// arguments are q1 = hq - tq = -g/sqrt2 and q2 = hq + tq, and with them
+//   g^2/2 = q1^2,  s b''/b' = h^2 - t^2 = 2 q1 q2.
+// The fits' coefficients carry the factor sqrt(pi/2).
 struct Eval {
-  float is, h2;  // 1/s, h^2
-  float g2;      // g^2/2: b'/b_max = e^{-g2}/sqrt(2 pi)
-  float rho;     // b/b' in the difference form, (b_max - b)/b' in the complement form
+  float is, hq, tq;  // 1/s, |h|/sqrt2, s/(2 sqrt2)
+  float g2;          // g^2/2: b'/b_max = e^{-g2}/sqrt(2 pi)
+  float H;           // s b''/b'
+  float rho;         // b/b' in the difference form, (b_max - b)/b' in the complement form
   bool comp;
 };
 
@@ -120,29 +130,31 @@ __host__ __device__ inline Eval eval(float ax, float s, bool comp = false) {
   constexpr float kB = (float)(FIT == kFitGuess ? coef::kErfcxSB
                                                 : (FIT == kFitStep ? coef::kErfcxTB
                                                                    : coef::kErfcxF32B));
+  constexpr auto c = [](int i) { return (float)(1.25331413731550025 * kC[i]); };
   Eval e;
   e.is = rcp(s);
-  const float h = -ax * e.is, t = 0.5f * s;
-  const float g = h + t;
-  e.h2 = h * h;
-  e.g2 = 0.5f * g * g;
-  const float q1 = -g * kInvSqrt2, q2 = (t - h) * kInvSqrt2;
-  e.comp = FIT == kFitGuess ? comp : g > kInvSqrt2;
+  e.hq = ax * kInvSqrt2 * e.is;
+  const float s2 = s * kInvSqrt2;  // 2 tq
+  e.tq = 0.5f * s2;
+  const float q1 = e.hq - e.tq, q2 = e.hq + e.tq;
+  e.g2 = q1 * q1;
+  e.H = (q1 + q1) * q2;
+  e.comp = FIT == kFitGuess ? comp : q1 < -0.5f;
   const float z1 = e.comp ? -q1 : q1;
   const float a1 = z1 + kB, a2 = q2 + kB;
   const float R12 = rcp(a1 * a2);
   const float R1 = R12 * a2, R2 = R12 * a1;
   constexpr float k2BZ = 2.0f * (kB - kZ0);
   const float y1 = fmaf(-k2BZ, R1, 1.0f), y2 = fmaf(-k2BZ, R2, 1.0f);
-  float D = (float)kC[kDeg], B = fmaf(D, y2, (float)kC[kDeg - 1]);
+  float D = c(kDeg), B = fmaf(D, y2, c(kDeg - 1));
 #pragma unroll
   for (int i = kDeg - 2; i >= 0; --i) {
     D = fmaf(D, y1, B);
-    B = fmaf(B, y2, (float)kC[i]);
+    B = fmaf(B, y2, c(i));
   }
-  const float diff = kSqrtPi * t * R12 * fmaf(-k2BZ * R1, D, B);
+  const float diff = s2 * R12 * fmaf(-k2BZ * R1, D, B);
   const float A = fmaf(y1 - y2, D, B);
-  const float sum = kSqrtPiOver2 * fmaf(A, R1, B * R2);
+  const float sum = fmaf(A, R1, B * R2);
   e.rho = e.comp ? sum : diff;
   return e;
 }
@@ -204,7 +216,7 @@ __host__ __device__ inline float initial_guess(V bh, V ch, Target& q) {
   const float vc = q.lower ? bc : cc;
   const float so = q.lower ? kSqrtPiOver2 * q.ax * tail : fmaf(cc, kSqrt2Pi, sc);
   const Eval e = eval<kFitGuess>(q.ax, so, !q.lower);
-  const float bp = kInvSqrt2Pi * exp(-e.g2);  // b'(s_o)/b_max
+  const float bp = exp_over_sqrt2pi(e.g2);  // b'(s_o)/b_max
   const float vo = e.rho * bp;
   q.wing = q.v < vo;
   // end data of the rational cubic: Yl, Yr its values, Dl, Dr its slopes
@@ -212,15 +224,16 @@ __host__ __device__ inline float initial_guess(V bh, V ch, Target& q) {
   // interval's square (in a wing all divided by v_o times the slope at 0)
   float Yl, Yr, Dl, Dr, C, D, x0;
   if (q.wing) {
-    const float t = 0.5f * so, t2 = t * t, ah = q.ax * e.is;
-    const float z = q.lower ? ah * kInvSqrt3 : t;
-    const float P = 0.5f * erfcx(z * kInvSqrt2);
-    float M = exp(0.5f * (q.lower ? t2 : e.h2));
+    const float hq2 = e.hq * e.hq, tq2 = e.tq * e.tq;
+    const float zq = q.lower ? e.hq * kInvSqrt3 : e.tq;  // z/sqrt2
+    const float P = erfcx(zq);                           // twice the P above
+    float M = exp(q.lower ? tq2 : hq2);
     M = q.lower ? M * P * P : M;
-    Yr = M * P * rcp(e.rho) * (q.lower ? (kCl * kSqrt2Pi) * q.ax : 2.0f * kSqrt2Pi);
-    Dr = q.lower ? (2.0f * 1.04719755119659775f) * e.h2 * M : M;
-    const float k = fmaf(-2.0f / 3.0f, e.h2, (2.0f * kInvSqrt2Pi) * z * rcp(P)) + (t2 - 2.0f);
-    C = 0.5f * e.rho * e.is * Dr * (q.lower ? k : e.h2);
+    Yr = M * P * rcp(e.rho) * (q.lower ? (0.125f * kCl * kSqrt2Pi) * q.ax : kSqrt2Pi);
+    Dr = q.lower ? 1.04719755119659775f * hq2 * M : M;
+    const float k = fmaf(-4.0f / 3.0f, hq2, (4.0f * kSqrt2 * kInvSqrt2Pi) * zq * rcp(P)) +
+                    fmaf(2.0f, tq2, -2.0f);
+    C = e.rho * e.is * Dr * (q.lower ? 0.5f * k : hq2);
     Yl = 0.0f;
     Dl = 1.0f;
     D = vo;
@@ -252,8 +265,8 @@ __host__ __device__ inline float initial_guess(V bh, V ch, Target& q) {
   if (!q.wing) return fmaf(tau, A, Yl * w * w * w) * rcp(den);
   // invert the map from ln p: R1 p = Phi(-z) = (f/cl)^{1/3}, s = |x|/(sqrt3 z);
   // R4 p = Phi(-z) = f, s = 2 z
-  const float lf =
-      fmaf(-0.5f, q.ax, q.lv) + log(fmaxf(A, 1e-30f) * rcp(den * (q.lower ? kCl * q.ax : 2.0f)));
+  const float lf = fmaf(log2(fmaxf(A, 1e-30f) * rcp(den * (q.lower ? kCl * q.ax : 2.0f))), kLn2,
+                        fmaf(-0.5f, q.ax, q.lv));
   const float lnp = q.lower ? lf * (1.0f / 3.0f) : lf;
   const float rr = sqrt(-2.0f * fminf(lnp, -0.69314719f));
   const float pn = fmaf(rr, fmaf(rr, fmaf(rr, (float)coef::kPhiInvGP[3], (float)coef::kPhiInvGP[2]),
@@ -275,20 +288,19 @@ __host__ __device__ inline float initial_guess(V bh, V ch, Target& q) {
 // Every quantity is dimensionless, so nothing overflows for small s.
 //
 // One Householder(3) step, as ds/s.
-__host__ __device__ inline float householder3(const Target& q, const Eval& e, float s) {
-  const float s2 = 0.25f * s * s;
-  const float H = e.h2 - s2;                       // s b''/b'
-  const float H3 = fmaf(H, H, -3.0f * e.h2 - s2);  // s^2 b'''/b'
+__host__ __device__ inline float householder3(const Target& q, const Eval& e) {
+  const float H = e.H;                                                // s b''/b'
+  const float H3 = fmaf(-8.0f * e.hq, e.hq, fmaf(H, H, H));  // s^2 b'''/b' = H^2 - 3 h^2 - t^2
   float n, E2, E3;
   if (!q.wing) {
-    const float W = kSqrt2Pi * exp(e.g2);  // b_max/b'
+    const float W = exp_sqrt2pi(e.g2);  // b_max/b'
     n = (e.comp ? fmaf(-q.ch, W, e.rho) : fmaf(q.bh, W, -e.rho)) * e.is;
     E2 = H;
     E3 = H3;
   } else {
     const float rs = e.rho * e.is;
     const float w = q.lower ? -rcp(rs) : rcp(rs);   // -s b'/b or s b'/(b_max - b)
-    const float lb = log(e.rho) - (e.g2 + kLnSqrt2Pi);  // ln(b/b_max) or ln(1 - b/b_max)
+    const float lb = fmaf(log2(e.rho), kLn2, -kLnSqrt2Pi - e.g2);  // ln(b/b_max) or ln(1 - b/b_max)
     const float u = lb - q.lv;
     const float iL = q.lower ? rcp(fmaf(-0.5f, q.ax, lb)) : 0.0f;  // 1/ln b
     const float k = q.lower ? -1.0f - u * rcp(fmaf(-0.5f, q.ax, q.lv)) : 1.0f;  // -+ln b/ln beta
@@ -302,17 +314,17 @@ __host__ __device__ inline float householder3(const Target& q, const Eval& e, fl
 }
 
 // One Halley step, as ds/s (in R1 on ln b).
-__host__ __device__ inline float halley(const Target& q, const Eval& e, float s) {
-  const float H = e.h2 - 0.25f * s * s;
+__host__ __device__ inline float halley(const Target& q, const Eval& e) {
+  const float H = e.H;
   float n, E2;
   if (!q.wing) {
-    const float W = kSqrt2Pi * exp(e.g2);
+    const float W = exp_sqrt2pi(e.g2);
     n = (e.comp ? fmaf(-q.ch, W, e.rho) : fmaf(q.bh, W, -e.rho)) * e.is;
     E2 = H;
   } else {
     const float rs = e.rho * e.is;
     const float w = rcp(rs);
-    const float u = (log(e.rho) - (e.g2 + kLnSqrt2Pi)) - q.lv;
+    const float u = fmaf(log2(e.rho), kLn2, -kLnSqrt2Pi - e.g2) - q.lv;
     n = q.lower ? -u * rs : u * rs;
     E2 = q.lower ? H - w : H + w;
   }
