@@ -58,8 +58,8 @@ HBM_PEAK_GBS = 8000.0
 # algorithmic HBM bytes per quote: six float64 inputs + int8 flag in,
 # float64 sigma + uint8 status out
 BYTES_PER_QUOTE = 6 * 8 + 1 + 8 + 1
-KERNEL_SOURCES = ("fv_kernels.hip", "fv_math.h", "fv_lbr.h", "fv_quote.h", "fv_coeffs.h",
-                  "fv_host.h", "fv_csr.h", "fv_f32.h")
+KERNEL_SOURCES = ("fv_kernels.hip", "fv_math.h", "fv_lbr.h", "fv_start.h", "fv_quote.h",
+                  "fv_coeffs.h", "fv_host.h", "fv_csr.h", "fv_f32.h")
 
 
 def _code_only(text: str) -> str:

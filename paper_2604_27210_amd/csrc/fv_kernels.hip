@@ -182,16 +182,16 @@ struct FormArgs {
   double* out[6];
 };
 
-template <int MODEL, bool ARR>
+template <int MODEL>
 __device__ __forceinline__ SigmaQuote load_quote(const FormArgs& a, int64_t b, unsigned t) {
   SigmaQuote v;
-  v.fs = ld<ARR>(a.q.fs, b, t);
-  v.K = ld<ARR>(a.q.K, b, t);
-  v.T = ld<ARR>(a.q.T, b, t);
-  v.r = ld<ARR>(a.q.r, b, t);
-  v.q = MODEL == fv::kBlackScholesMerton ? ld<ARR>(a.q.q, b, t) : 0.0;
-  v.sigma = ld<ARR>(a.sigma, b, t);
-  v.th = ldflag<ARR>(a.q, b, t);
+  v.fs = ld<false>(a.q.fs, b, t);
+  v.K = ld<false>(a.q.K, b, t);
+  v.T = ld<false>(a.q.T, b, t);
+  v.r = ld<false>(a.q.r, b, t);
+  v.q = MODEL == fv::kBlackScholesMerton ? ld<false>(a.q.q, b, t) : 0.0;
+  v.sigma = ld<false>(a.sigma, b, t);
+  v.th = ldflag<false>(a.q, b, t);
   return v;
 }
 
@@ -218,12 +218,12 @@ __device__ __forceinline__ SigmaQuote load_late(int64_t i) {
 }
 
 // ------------------------------------------------------------- price
-template <int MODEL, bool ARR>
+template <int MODEL>
 __global__ __launch_bounds__(kMaxBlock) void k_price(FormArgs args) {
   const int64_t b = (int64_t)blockIdx.x * blockDim.x;
   const unsigned t = threadIdx.x;
   if ((int64_t)t >= args.q.n - b) return;
-  const SigmaQuote v = load_quote<MODEL, ARR>(args, b, t);
+  const SigmaQuote v = load_quote<MODEL>(args, b, t);
   fv::ClosedForm c;
   const bool fast = fv::closed_form(MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, &c);
   double p = c.D * c.t.P;
@@ -658,12 +658,12 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4))) 
 }
 
 // ------------------------------------------------------------- Greeks
-template <int MODEL, bool ARR>
+template <int MODEL>
 __global__ __launch_bounds__(kMaxBlock) void k_greeks(FormArgs args) {
   const int64_t b = (int64_t)blockIdx.x * blockDim.x;
   const unsigned t = threadIdx.x;
   if ((int64_t)t >= args.q.n - b) return;
-  const SigmaQuote v = load_quote<MODEL, ARR>(args, b, t);
+  const SigmaQuote v = load_quote<MODEL>(args, b, t);
   fv::ClosedForm c;
   const bool fast = fv::closed_form(MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, &c);
   Greeks gr = fv::greeks_of(c, MODEL, v.fs, v.T, v.r, v.q, v.sigma, v.th, c.D * c.t.P);
@@ -682,15 +682,15 @@ __global__ __launch_bounds__(kMaxBlock) void k_greeks(FormArgs args) {
 }
 
 // ------------------------------------------------------------- backward
-template <int MODEL, bool ARR>
+template <int MODEL>
 __global__ __launch_bounds__(kMaxBlock) void k_iv_backward(FormArgs args) {
   const int64_t b = (int64_t)blockIdx.x * blockDim.x;
   const unsigned t = threadIdx.x;
   if ((int64_t)t >= args.q.n - b) return;
-  const SigmaQuote v = load_quote<MODEL, ARR>(args, b, t);
+  const SigmaQuote v = load_quote<MODEL>(args, b, t);
   const double gs = (args.up + b)[t];
   // the price enters Black-76's theta alone
-  const double P = MODEL == fv::kBlack76 ? ld<ARR>(args.q.price, b, t) : 0.0;
+  const double P = MODEL == fv::kBlack76 ? ld<false>(args.q.price, b, t) : 0.0;
   fv::ClosedForm c;
   const bool fast = fv::closed_form(MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, &c);
   const fv::PricePartials pp =
@@ -714,12 +714,12 @@ __global__ __launch_bounds__(kMaxBlock) void k_iv_backward(FormArgs args) {
 }
 
 // ------------------------------------------------------------- price adjoint
-template <int MODEL, bool ARR>
+template <int MODEL>
 __global__ __launch_bounds__(kMaxBlock) void k_price_backward(FormArgs args) {
   const int64_t b = (int64_t)blockIdx.x * blockDim.x;
   const unsigned t = threadIdx.x;
   if ((int64_t)t >= args.q.n - b) return;
-  const SigmaQuote v = load_quote<MODEL, ARR>(args, b, t);
+  const SigmaQuote v = load_quote<MODEL>(args, b, t);
   const double g = (args.up + b)[t];
   fv::ClosedForm c;
   const bool fast = fv::closed_form(MODEL, v.fs, v.K, v.T, v.r, v.q, v.sigma, v.th, &c);
@@ -1244,9 +1244,9 @@ int fv_get_launch(int kernel, int* block, int* qpt) {
     const dim3 grid = grid_for(q->n, sh), block(sh.block);                                \
     hipStream_t s = (hipStream_t)stream;                                                  \
     switch (model) {                                                                      \
-      case FV_MODEL_BLACK76: KERN<0, false><<<grid, block, 0, s>>>(args); break;          \
-      case FV_MODEL_BLACK_SCHOLES: KERN<1, false><<<grid, block, 0, s>>>(args); break;    \
-      default: KERN<2, false><<<grid, block, 0, s>>>(args); break;                        \
+      case FV_MODEL_BLACK76: KERN<0><<<grid, block, 0, s>>>(args); break;                 \
+      case FV_MODEL_BLACK_SCHOLES: KERN<1><<<grid, block, 0, s>>>(args); break;           \
+      default: KERN<2><<<grid, block, 0, s>>>(args); break;                               \
     }                                                                                     \
   } while (0)
 
