@@ -29,7 +29,8 @@ if ROOT not in sys.path:
 #  * flop_per_quote: algorithmic FP64 work (FMA = 2 FLOPs, every other FP64
 #    VALU instruction = 1 per lane) from SQ_INSTS_VALU_{ADD,MUL,FMA,TRANS}_F64
 #    of one launch over the workload with the quotes sorted by LBR path
-#    (``--census``), where no wave executes a branch another lane skipped;
+#    (``--census``), where no wave executes a branch another lane skipped
+#    (the guess and the first step, in binary32, are not in it);
 #  * executed_flop_per_quote: the same count on the workload as generated
 #    (divergence included);
 #  * valu_per_quote: SQ_INSTS_VALU x 64 / quotes of the same sorted launch,
@@ -40,11 +41,11 @@ if ROOT not in sys.path:
 # The traffic figure is reported only while the kernel sources still hash to
 # ``source_sha256``; the FLOP figure is the algorithmic count of that source.
 LBR_PROFILE = {
-    "source_sha256": "07506ec4e603578bce41630df4e9a1a4b067c5a208677fa6be7c9fa8ba395d60",
-    "flop_per_quote": 1082.5,
-    "executed_flop_per_quote": 1205.6,
-    "valu_per_quote": 1038.6,
-    "fetch_bytes_per_quote": 50.033,
+    "source_sha256": "e44c8e77dd995cf0989a392d4377937630969722d500761755ce2038bb238d06",
+    "flop_per_quote": 309.2,
+    "executed_flop_per_quote": 311.0,
+    "valu_per_quote": 549.9,
+    "fetch_bytes_per_quote": 50.009,
     "write_bytes_per_quote": 9.000,
 }
 FP64_VECTOR_PEAK_TFLOPS = 78.6
