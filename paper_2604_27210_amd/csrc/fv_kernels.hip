@@ -127,12 +127,10 @@ __device__ __forceinline__ Greeks no_greeks() {
 // Largest workgroup the kernels are compiled for (8 waves).
 constexpr int kMaxBlock = 512;
 // Minimum resident waves per SIMD the solver kernels are register-allocated
-// for (2: up to 256 VGPRs, 3: 168, 4: 128, 6: 80).  LBR runs at 4: at 6 it
-// is no faster, and its one-byte flag and status accesses (half a 128-byte
-// line per wave) then get fetched and written back twice as often (53 + 13
-// instead of 49 + 9 bytes per quote on the wide workload).  The Halley
-// kernels, at 80 VGPRs without spills, run 6.  The fused-Greeks variants
-// keep more live values and are held at 2 so that they do not spill.
+// for.  LBR takes 56 VGPRs (8 waves) at a floor of 4, Halley 70 (7 waves) at
+// 6; floors of 4 to 8 are within 1% for both (3M quotes, Halley: 54.3, 54.3,
+// 54.1 and 54.5 us at 4, 6, 7 and 8 on one card).  The fused-Greeks variants
+// take 80 to 84 at a floor of 2, which is as fast as one of 6 or 7 (26.1 us).
 #ifndef FV_LBR_WAVES_PER_EU
 #define FV_LBR_WAVES_PER_EU 4
 #endif
@@ -160,8 +158,8 @@ __device__ __forceinline__ V opaque(V i) {
 }
 
 // The closed-form kernels below (price, Greeks, adjoints) are bound by
-// memory: one evaluation and three exponentials a quote (about 230 vector
-// instructions, 340 to 560 with the general forms) against 57 to 113 bytes.
+// memory: one evaluation and three exponentials a quote (260 to 350 vector
+// instructions, 340 to 500 with the general forms) against 57 to 113 bytes.
 // 5M BSM prices: 57 to 60 us (70 before; 55 at the 5.2 TB/s of a copy), 2M
 // Black-76 Greeks 32 to 36 us (46; 31), the adjoint of 1M BSM quotes 20.5 us
 // (27; 22, part of it served from cache).  One quote per thread, every field
@@ -279,7 +277,7 @@ __device__ __forceinline__ Greeks greeks_solved(uint8_t st, bool general,
 }
 
 // ------------------------------------------------------------- IV: LBR
-// Bound by the vector ALU's issue rate: about 570 vector instructions per
+// Bound by the vector ALU's issue rate: about 580 vector instructions per
 // quote, every side of the guess a mixed wave takes included (1,157 with the
 // guess and the first step in binary64).  10M wide-wing BSM quotes: 154 us
 // (355 with those), 1M BS quotes with the five Greeks: 26 us (54).
@@ -574,8 +572,8 @@ struct Pending32 {
 
 // The binary32 twin of k_iv_halley: the same ballot + LDS compaction of the
 // lanes that fail the convergence check and bisection over the packed queue,
-// in float arithmetic throughout.  Bound by the vector ALU: about 430 vector
-// instructions per quote (1,224 with the at-the-money start, whose lanes took
+// in float arithmetic throughout.  Bound by the vector ALU: about 470 vector
+// instructions per quote (1,150 with the at-the-money start, whose lanes took
 // up to 8 steps and a wave its slowest lane's).  10M wide-wing BSM quotes:
 // 100 us (288 with that start).
 template <int MODEL, bool ARR>
