@@ -41,7 +41,7 @@ if ROOT not in sys.path:
 # The traffic figure is reported only while the kernel sources still hash to
 # ``source_sha256``; the FLOP figure is the algorithmic count of that source.
 LBR_PROFILE = {
-    "source_sha256": "e44c8e77dd995cf0989a392d4377937630969722d500761755ce2038bb238d06",
+    "source_sha256": "0e8930f21b69e7fdef748e001dee6584823185b7e3d6fa210d9054fa20f49faf",
     "flop_per_quote": 309.2,
     "executed_flop_per_quote": 311.0,
     "valu_per_quote": 549.9,
