@@ -1052,13 +1052,13 @@ int launched(const char* what) { return fvh::launched(what); }
 
 int device_cus();
 
-// Slices per wave of the ragged kernel.  One below 20 waves per SIMD (80 per
+// Slices per wave of the ragged kernel.  One below 40 waves per SIMD (160 per
 // compute unit), where the chain of a wave's location and second solve is
-// what a small batch waits for; above, two pay the location once.  In us,
-// one against two: LBR 8.3 / 9.6 (273k quotes), 20.9 / 21.8 (1.0M),
-// 34.3 / 33.7 (1.9M), 143 / 131 (8.4M); Halley 8.9 / 10.5, 23.1 / 23.7,
-// 38.7 / 37.7, 167 / 146.
-int chain_slices(int64_t n) { return n < (int64_t)64 * 80 * device_cus() ? 1 : 2; }
+// what a batch waits for; above, two pay the location once.  In us, one
+// against two: LBR 10.2 / 11.0 (0.5M quotes), 19.2 / 21.1 (1.0M),
+// 31.5 / 32.3 (1.9M), 63.9 / 62.4 (4.2M), 133 / 128 (8.4M); Halley
+// 20.7 / 21.9, 33.5 / 34.6, 68.1 / 66.5, 144 / 135 from 1.0M on.
+int chain_slices(int64_t n) { return n < (int64_t)64 * 160 * device_cus() ? 1 : 2; }
 
 int device_cus() {
   static int cache[64];  // per device ordinal; 0 = not yet queried

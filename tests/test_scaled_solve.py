@@ -249,14 +249,14 @@ def test_binary32_domain_edges(broadcast):
 @pytest.mark.parametrize("solver", ["lbr", "halley"])
 @pytest.mark.parametrize("side", [-1, 0, 77])
 def test_chains_at_the_slice_rule(solver, side):
-    """The ragged kernel takes one 64-quote slice per wave below 80 waves per
+    """The ragged kernel takes one 64-quote slice per wave below 160 waves per
     compute unit and two from there: on both sides, quote by quote the flat
     solve of the same inputs (each within 1e-12 of the root)."""
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2604_27210_amd as fv
-    n = 64 * 80 * torch.cuda.get_device_properties(0).multi_processor_count + side
+    n = 64 * 160 * torch.cuda.get_device_properties(0).multi_processor_count + side
     rng = np.random.default_rng(n)
     cuts = np.unique(rng.integers(1, n, 4000))
     mqo = np.r_[0, cuts, n]
