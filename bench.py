@@ -41,7 +41,7 @@ if ROOT not in sys.path:
 # The traffic figure is reported only while the kernel sources still hash to
 # ``source_sha256``; the FLOP figure is the algorithmic count of that source.
 LBR_PROFILE = {
-    "source_sha256": "0e8930f21b69e7fdef748e001dee6584823185b7e3d6fa210d9054fa20f49faf",
+    "source_sha256": "bbd02861d589c60f2ac342e3ee3e18272cdbd47b6e8032e8e03032c1077cd8b1",
     "flop_per_quote": 309.2,
     "executed_flop_per_quote": 311.0,
     "valu_per_quote": 549.9,
