@@ -18,7 +18,9 @@ __device__ __forceinline__ int64_t ld_off(const int64_t* __restrict__ off, int64
 
 // The starts after an index, relative to a key (lane j holds off[base + 1 + j]
 // - key, or kRelEnd from there on and past the last entry: a wave looks no
-// further than that), consumed in order through a wave-uniform cursor.
+// further than that), consumed in order through a wave-uniform cursor.  A
+// start as far or farther before the key is -kRelEnd: of those only the sign
+// is read (a batch may hold many times 2^31 quotes).
 constexpr int kRelEnd = 0x7fffffff;
 struct OffWindow {
   const int64_t* off;
@@ -26,7 +28,7 @@ struct OffWindow {
   int v, j;
   __device__ __forceinline__ int load() const {
     const int64_t d = ld_off(off, count, base + 1 + __lane_id()) - key;
-    return d < kRelEnd ? (int)d : kRelEnd;
+    return (int)min(max(d, (int64_t)-kRelEnd), (int64_t)kRelEnd);
   }
   // Returns the largest m in [0, count) with off[m] <= key (off
   // non-decreasing, off[0] <= key), and leaves the window at the starts after
