@@ -47,6 +47,14 @@ struct OffWindow {
     const uint32_t next = (uint32_t)__lane_id() + 1;
     base = 0;
     int64_t left = count;  // m is in [base, base + left)
+    // by halves down to what the candidates' 32 bits hold (the calibration
+    // takes any number of chains)
+    while (__builtin_expect(left > kRelEnd, 0)) {
+      const int64_t half = left >> 1;
+      const bool le = off[base + half] <= key;
+      base += le ? half : 0;
+      left = le ? left - half : half;
+    }
     while (left > 64) {
       const uint32_t step = (uint32_t)((left + 63) >> 6);
       const uint32_t at = next * step;

@@ -3,6 +3,7 @@ compiled against a model of the wave, 64 fibers that meet at every cross-lane
 operation, and its maturities and chains are compared with a plain search.  No
 quote is needed, so the offsets can be as large as the entry points accept."""
 import ctypes
+import mmap
 import os
 import subprocess
 
@@ -141,3 +142,18 @@ def test_location_equals_a_plain_search(host, layout):
     for w0 in np.unique(np.clip(at, 0, n - 1) // 128 * 128):
         for slices in (1, 2):
             _check(host, mqo, cmo, int(w0), slices)
+
+
+@pytest.mark.parametrize("chains", [(1 << 31) + 5, (1 << 32) - 10, (1 << 32) + 1000, (1 << 33) + 77])
+@pytest.mark.parametrize("tail", [1, 300])
+def test_chains_beyond_32_bits(host, chains, tail):
+    """The calibration takes any number of chains, most of them empty here:
+    all but the last `tail` start at maturity 0 (untouched pages of a mapping),
+    those at one maturity each."""
+    size = 8 * (chains + 1)
+    buf = mmap.mmap(-1, size, flags=mmap.MAP_PRIVATE | mmap.MAP_ANONYMOUS | 0x4000)  # not reserved
+    cmo = np.frombuffer(buf, dtype=np.int64)
+    cmo[-tail:] = np.arange(1, tail + 1)
+    mqo = np.arange(0, 65 * tail + 1, 65, dtype=np.int64)
+    for w0 in range(0, int(mqo[-1]), 64 if tail == 1 else 1280):
+        _check(host, mqo, cmo, w0, 1)
