@@ -350,7 +350,11 @@ struct ScaledTerms {
 };
 
 // False outside the domain (the caller takes the general forms): |x| above
-// 128, total volatility outside [2^-60, 64], a density below e^-690.
+// 128, total volatility outside [2^-60, 64], a density below e^-600, or
+// F phi(d1) below 2^-640: what is made of it (b/b_max down to 2^-70 of the
+// density, the two terms, the discounted values down to 2^-288 of those) stays
+// a normal number, where the general forms multiply by the spot last or not at
+// all.
 __host__ __device__ __attribute__((always_inline)) inline bool scaled_terms(double F, double K,
                                                                             double x, double s,
                                                                             int theta,
@@ -371,7 +375,7 @@ __host__ __device__ __attribute__((always_inline)) inline bool scaled_terms(doub
   o->KN = as_call ? t3 : t1;
   o->P = fma(m, bh, itm ? fabs(F - K) : 0.0);
   o->V = m * dens;
-  return all(x >= -128.0, s >= 0x1p-60, s <= 64.0, ea >= -690.0);
+  return all(x >= -128.0, s >= 0x1p-60, s <= 64.0, ea >= -600.0, o->V >= 0x1p-640);
 }
 
 // A quote the scaled closed forms take: every quantity they divide by or
@@ -429,7 +433,7 @@ __host__ __device__ inline Greeks greeks_of(const ClosedForm& c, int model, doub
   const double dFN = dth * c.D * c.t.FN;
   g.vega = V * c.sqT;
   g.delta = dFN * ifs;
-  g.gamma = V * ifs * ifs * rcp(c.s);
+  g.gamma = V * ifs * (ifs * rcp(c.s));  // V/S^2 itself may leave the normal range
   if (model == kBlack76) {
     g.theta = fma(r, price, -decay);
     g.rho = -T * price;
