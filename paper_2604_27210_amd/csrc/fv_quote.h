@@ -106,8 +106,11 @@ __host__ __device__ inline double forward_of(int model, double fs, double T, dou
   return model == kBlack76 ? fs : fs * growth_of(model, T, r, q);
 }
 
-// ln(F/K) for positive finite F and K
-__host__ __device__ inline double log_moneyness(double F, double K) { return log_ratio(F, K); }
+// ln(F/K) for positive K and F >= 0: a forward that underflowed has none
+// (log_ratio would make a finite number of its significand)
+__host__ __device__ inline double log_moneyness(double F, double K) {
+  return F == 0.0 ? -__builtin_inf() : log_ratio(F, K);
+}
 
 __host__ __device__ __attribute__((always_inline)) inline Reduced reduce_quote(int model, double price, double fs, double K,
                                                 double T, double r, double q, int theta) {

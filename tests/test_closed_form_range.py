@@ -37,6 +37,11 @@ extern "C" void h_forms(int model, int64_t n, const double* fs, const double* K,
     }
   }
 }
+extern "C" void h_at(double F, double K, double D, double sg, int th, double* o) {
+  o[0] = fv::price_at(F, K, D, sg, 1.0, th);
+  const fv::Greeks g = fv::greeks_at(1, 1e-200, K, 1.0, -2.0, 0.0, sg, th, F, D, o[0]);
+  o[1] = g.delta, o[2] = g.gamma, o[3] = g.vega, o[4] = g.rho;
+}
 '''
 NAMES = ["price", "delta", "gamma", "vega", "rho", "dK", "dq"]
 
@@ -93,3 +98,14 @@ def test_small_and_large_spots(host, model, th):
         i = np.where(bad[:, j])[0]
         assert len(i) == 0, (name, len(i), ["fs %.3g T %.3g r %.3g s %.3g h %.3g: %.17g %.17g" % (fs[k], T[k], r[k], s[k], h[k], a[k, j], b[k, j])
                                             for k in i[:3]])
+
+
+@pytest.mark.parametrize("K", [100.0, 1e-3, 1e-200])
+@pytest.mark.parametrize("sigma", [0.3, 0.0])
+def test_forward_that_underflows(host, K, sigma):
+    """A forward of 0 has no logarithm: each value is NaN or the limit (a call
+    worth nothing, a put worth the discounted strike), never another number."""
+    for th, limit in ((1, [0.0, 0.0, 0.0, 0.0, 0.0]), (-1, [2.0 * K, 0.0, 0.0, 0.0, -2.0 * K])):
+        o = np.empty(5)
+        host.h_at(*[ctypes.c_double(v) for v in (0.0, K, 2.0, sigma)], th, o.ctypes.data_as(ctypes.c_void_p))
+        assert np.all(np.isnan(o) | (o == limit)), (th, o)
