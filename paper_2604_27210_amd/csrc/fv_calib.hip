@@ -264,9 +264,8 @@ __device__ __forceinline__ double grad_wave(const KSvi& c, int64_t wave,
       double s2 = s1;
       bool solved = false;
       if (x >= -128.0 && s1 > 1e-20 && s1 < 1e3) {
-        const fv::ScaledEval ev = fv::scaled_eval(x, s1);
-        const double part = fv::kInvSqrt2Pi * fv::fexp(-0.5 * ev.g * ev.g) * ev.rho;
-        const double bh = ev.comp ? 1.0 - part : part, ch = ev.comp ? part : 1.0 - part;
+        double bh, ch;
+        fv::scaled_value(x, s1, &bh, &ch);
         solved = fv::scaled_domain(x, bh, ch) && fv::lbr_solve_scaled(x, bh, ch, &s2);
       }
       if (__builtin_expect(!solved, 0)) {

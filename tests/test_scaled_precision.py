@@ -1,0 +1,63 @@
+"""What the scaled solve leaves in a root it is handed the value of, on the
+CPU: the calibration prices a volatility and takes the implied one, and its
+gradient sums the difference over thousands of quotes, so the systematic part
+counts and not only the largest error."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from _helpers import U
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SRC = r'''
+#include <cstdint>
+#include "fv_quote.h"
+extern "C" void h_back(int64_t n, const double* x, const double* s, double* scaled, double* general) {
+  for (int64_t i = 0; i < n; ++i) {
+    double bh, ch;
+    fv::scaled_value(x[i], s[i], &bh, &ch);
+    scaled[i] = -1.0;
+    if (fv::scaled_domain(x[i], bh, ch)) fv::lbr_solve_scaled(x[i], bh, ch, &scaled[i]);
+    const double bmax = fv::fexp(0.5 * x[i]);
+    const fv::NBlack nb = fv::normalised_black(x[i], s[i], bmax);
+    general[i] = fv::lbr_solve(x[i], nb.b, bmax, nb.lnbp + fv::flog(nb.ratio), fv::kLbrMinSteps,
+                               fv::kLbrMaxSteps, fv::kLbrStepTol).s;
+  }
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    d = tmp_path_factory.mktemp("back")
+    src, so = str(d / "s.cpp"), str(d / "s.so")
+    with open(src, "w") as f:
+        f.write(SRC)
+    csrc = os.path.join(ROOT, "paper_2604_27210_amd", "csrc")
+    subprocess.run(["g++", "-O2", "-std=gnu++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-I" + csrc, src, "-o", so], check=True)
+    return ctypes.CDLL(so)
+
+
+def test_a_priced_volatility_comes_back(host):
+    """Strikes and volatilities of the calibration's chains.  The mean of
+    s'/s - 1 stays below a quarter of the unit roundoff (its sampling error is
+    3e-16 / sqrt(n) = 5e-19), as that of the general solve does; no root is
+    further off than 32 u."""
+    rng = np.random.default_rng(1)
+    n = 300_000
+    T = np.exp(rng.uniform(np.log(1.0 / 365.0), np.log(5.0), n))
+    k = rng.uniform(-1.2, 1.2, n) * np.sqrt(T)
+    s = np.ascontiguousarray((rng.uniform(0.12, 0.4, n) + 0.1 * k * k - 0.05 * k) * np.sqrt(T))
+    x = -np.abs(k)
+    out = [np.empty(n) for _ in range(2)]
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    host.h_back(ctypes.c_int64(n), p(x), p(s), *[p(o) for o in out])
+    for root in out:
+        err = root / s - 1.0
+        assert np.max(np.abs(err)) <= 32 * U
+        assert abs(err.mean()) <= 0.25 * U, err.mean()
