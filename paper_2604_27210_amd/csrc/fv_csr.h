@@ -19,8 +19,8 @@ __device__ __forceinline__ int64_t ld_off(const int64_t* __restrict__ off, int64
 // The starts after an index, relative to a key (lane j holds off[base + 1 + j]
 // - key, or kRelEnd from there on and past the last entry: a wave looks no
 // further than that), consumed in order through a wave-uniform cursor.  A
-// start as far or farther before the key is -kRelEnd: of those only the sign
-// is read (a batch may hold many times 2^31 quotes).
+// start before the key is -1: of those only the sign is read, and a batch may
+// hold many times 2^31 quotes.
 constexpr int kRelEnd = 0x7fffffff;
 struct OffWindow {
   const int64_t* off;
@@ -28,7 +28,7 @@ struct OffWindow {
   int v, j;
   __device__ __forceinline__ int load() const {
     const int64_t d = ld_off(off, count, base + 1 + __lane_id()) - key;
-    return (int)min(max(d, (int64_t)-kRelEnd), (int64_t)kRelEnd);
+    return d < kRelEnd ? (d < 0 ? -1 : (int)d) : kRelEnd;
   }
   // Returns the largest m in [0, count) with off[m] <= key (off
   // non-decreasing, off[0] <= key), and leaves the window at the starts after
@@ -48,8 +48,9 @@ struct OffWindow {
     base = 0;
     int64_t left = count;  // m is in [base, base + left)
     // by halves down to what the candidates' 32 bits hold (the calibration
-    // takes any number of chains)
-    while (__builtin_expect(left > kRelEnd, 0)) {
+    // takes any number of chains; the shift is scalar, a 64-bit comparison
+    // is not)
+    while (__builtin_expect((int)(left >> 31), 0)) {
       const int64_t half = left >> 1;
       const bool le = off[base + half] <= key;
       base += le ? half : 0;
