@@ -73,6 +73,18 @@ const at::Tensor& dev_tensor(PyObject* v, const char* name, at::ScalarType type)
   return *t;
 }
 
+// The same with an entry for each of n quotes at least (a 0-dim tensor, which a
+// field reads as a number, has one).
+const at::Tensor& whole_tensor(PyObject* v, const char* name, at::ScalarType type, int64_t n) {
+  const at::Tensor& t = dev_tensor(v, name, type);
+  if (t.numel() < n) {
+    PyErr_Format(PyExc_ValueError, "length mismatch: %s has %lld, expected %lld", name,
+                 (long long)t.numel(), (long long)n);
+    throw Raised{};
+  }
+  return t;
+}
+
 void* ptr(const at::Tensor& t) { return t.data_ptr(); }
 
 double number(PyObject* v) {
@@ -235,14 +247,15 @@ PyObject* flat(PyObject* const* a) {
   q.n = b.n;
   b.flag(a[11], q.flag, q.flag_value);
   const double *sig = nullptr, *grad = nullptr;
-  if (which == kIvBackward) sig = (const double*)ptr(dev_tensor(a[9], "sigma", at::kDouble));
+  if (which == kIvBackward)
+    sig = (const double*)ptr(whole_tensor(a[9], "sigma", at::kDouble, b.n));
   if (which == kIvBackward || which == kPriceBackward)
-    grad = (const double*)ptr(dev_tensor(
-        a[10], which == kIvBackward ? "grad_sigma" : "grad_price", at::kDouble));
+    grad = (const double*)ptr(whole_tensor(
+        a[10], which == kIvBackward ? "grad_sigma" : "grad_price", at::kDouble, b.n));
   at::Tensor out, status, block;
   int option = 0;
   if (which == kIv) option = integer(a[12]);
-  if (which == kPrice && a[12] != Py_None) out = dev_tensor(a[12], "out", at::kDouble);
+  if (which == kPrice && a[12] != Py_None) out = whole_tensor(a[12], "out", at::kDouble, b.n);
   void* s = stream_of(a[13], b.device);
   int rc = 0;
   {

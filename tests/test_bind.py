@@ -171,3 +171,36 @@ def test_gpu_refusals():
     e = torch.empty(0, dtype=torch.float64, device="cuda")
     s, st = fv.implied_vol("bs", e, e, e, e, e)
     assert s.shape == st.shape == (0,)
+
+
+@pytest.mark.gpu
+def test_gpu_buffers_hold_every_quote():
+    """A buffer that the kernels index by quote and that is shorter than the
+    batch (or 0-dim) is refused before any launch; a longer one is read and
+    written as far as the batch goes."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    v = torch.full((4,), 2.0, dtype=torch.float64, device="cuda")
+    w = torch.full((6,), 2.0, dtype=torch.float64, device="cuda")
+    for short in (v[:3], v[0], v[:0]):
+        m = short.numel()
+        for text, call in [
+                ("grad_sigma has %d, expected 4" % m,
+                 lambda: fv.implied_vol_backward("bs", v, v, v, v, v, v, short)),
+                ("sigma has %d, expected 4" % m,
+                 lambda: fv.implied_vol_backward("bs", v, v, v, v, v, short, v)),
+                ("grad_price has %d, expected 4" % m,
+                 lambda: fv.price_backward("bs", v, v, v, v, v, short)),
+                ("out has %d, expected 4" % m, lambda: fv.price("bs", v, v, v, v, v, out=short))]:
+            with pytest.raises(ValueError, match="length mismatch: " + text):
+                call()
+    P = fv.price("bs", v, v, v, v, v)
+    out = torch.full((6,), -1.0, dtype=torch.float64, device="cuda")
+    assert fv.price("bs", v, v, v, v, v, out=out) is out
+    assert torch.equal(out[:4], P) and (out[4:] == -1.0).all()
+    a = fv.implied_vol_backward("bs", P, v, v, v, v, v, v)
+    b = fv.implied_vol_backward("bs", P, v, v, v, v, v, w)
+    assert all(torch.equal(a[k], b[k]) for k in a)
+    one = fv.price("bs", v[:1], v[:1], v[:1], v[:1], v[:1])
+    got = fv.implied_vol_backward("bs", one, v[:1], v[:1], v[:1], v[:1], v[0], v[1])
+    assert all(torch.equal(got[k], a[k][:1]) for k in a)
