@@ -23,9 +23,10 @@
  *    call only enqueues work and returns; nothing synchronises the host.
  *  - Return value: FV_OK, or a negative fv_status when the call itself is
  *    invalid (nothing is launched; fv_last_error() says why).  n == 0 is a
- *    no-op returning FV_OK; n above (2^31 - 1) * 64 (more workgroups than a
- *    launch can have) is FV_E_INVALID_ARG.  Per-quote problems never fail a call: they are
- *    reported in the per-quote status array (fv_quote_status).
+ *    no-op returning FV_OK; n above (2^31 - 1) * 64 is FV_E_INVALID_ARG (more
+ *    than 2^31 quotes are launched in parts, one after the other on the
+ *    stream).  Per-quote problems never fail a call: they are reported in the
+ *    per-quote status array (fv_quote_status).
  *  - Black-76 prices are DISCOUNTED (section 2.4): price = e^{-rT} Black(F).
  *    T is in years; r, q continuously compounded.
  *  - Greeks are raw per-unit partial derivatives: delta = dP/dS (dP/dF for

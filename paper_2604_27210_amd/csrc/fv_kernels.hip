@@ -317,33 +317,36 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_LBR(GREEKS)))) void k_iv_lbr(IvArgs 
   }
 }
 
+// Arguments of the diagnostic kernels.
+struct TraceArgs {
+  KQuotes q;
+  uint32_t* out;
+};
+
 // Diagnostic twin of k_iv_lbr: the same per-quote solve, recording the path
 // each quote takes (guess region, evaluation forms, number of steps).
 template <int MODEL>
-__global__ __launch_bounds__(kMaxBlock) void k_lbr_trace(KQuotes q, uint32_t* __restrict__ out,
-                                                         int qpt) {
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    if (i >= q.n) return;
-    const double P = ld(q.price, i), fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i),
-                 r = ld(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    fv::ScaledQuote sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, ldflag(q, i));
-    uint32_t code = 0xFFFFFFFFu;  // not solved (status != OK)
-    bool general = sq.general;
-    if (sq.status == fv::kQOk && !general) {
-      double s;
-      general = !fv::lbr_solve_scaled(sq.x, sq.bh, sq.ch, &s, &code);
-    }
-    if (general) {
-      double sg;
-      uint8_t st;
-      code = 0xFFFFFFFFu;
-      lbr_general_at<MODEL, false>(q, i, &sg, &st, &sq, &code);
-    }
-    out[i] = code;
+__global__ __launch_bounds__(kMaxBlock) void k_lbr_trace(TraceArgs args) {
+  const KQuotes& q = args.q;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= q.n) return;
+  const double P = ld(q.price, i), fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i),
+               r = ld(q.r, i);
+  const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
+  fv::ScaledQuote sq = fv::scaled_quote(MODEL, P, fs, K, T, r, qy, ldflag(q, i));
+  uint32_t code = 0xFFFFFFFFu;  // not solved (status != OK)
+  bool general = sq.general;
+  if (sq.status == fv::kQOk && !general) {
+    double s;
+    general = !fv::lbr_solve_scaled(sq.x, sq.bh, sq.ch, &s, &code);
   }
+  if (general) {
+    double sg;
+    uint8_t st;
+    code = 0xFFFFFFFFu;
+    lbr_general_at<MODEL, false>(q, i, &sg, &st, &sq, &code);
+  }
+  args.out[i] = code;
 }
 
 // The Halley iteration of one quote: the scaled solve, or the general one for
@@ -373,22 +376,19 @@ __device__ __forceinline__ uint8_t halley_quote(double P, double fs, double K, d
 // takes, with bit 8 set when it fails the convergence check (and would go
 // through the bisection fallback).
 template <int MODEL>
-__global__ __launch_bounds__(kMaxBlock) void k_halley_trace(KQuotes q, uint32_t* __restrict__ out,
-                                                            int qpt) {
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x * qpt + threadIdx.x;
-  for (int k = 0; k < qpt; ++k) {
-    const int64_t i = base + (int64_t)k * blockDim.x;
-    if (i >= q.n) return;
-    const double P = ld(q.price, i), fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i),
-                 r = ld(q.r, i);
-    const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
-    fv::HalleyState hs;
-    fv::ScaledQuote sq;
-    const uint8_t st = halley_quote<MODEL>(P, fs, K, T, r, qy, ldflag(q, i), q.hsteps, &hs, &sq);
-    uint32_t code = 0xFFFFFFFFu;  // not solved (status != OK)
-    if (st == fv::kQOk) code = (uint32_t)hs.steps | (hs.converged ? 0u : 0x100u);
-    out[i] = code;
-  }
+__global__ __launch_bounds__(kMaxBlock) void k_halley_trace(TraceArgs args) {
+  const KQuotes& q = args.q;
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= q.n) return;
+  const double P = ld(q.price, i), fs = ld(q.fs, i), K = ld(q.K, i), T = ld(q.T, i),
+               r = ld(q.r, i);
+  const double qy = MODEL == fv::kBlackScholesMerton ? ld(q.q, i) : 0.0;
+  fv::HalleyState hs;
+  fv::ScaledQuote sq;
+  const uint8_t st = halley_quote<MODEL>(P, fs, K, T, r, qy, ldflag(q, i), q.hsteps, &hs, &sq);
+  uint32_t code = 0xFFFFFFFFu;  // not solved (status != OK)
+  if (st == fv::kQOk) code = (uint32_t)hs.steps | (hs.converged ? 0u : 0x100u);
+  args.out[i] = code;
 }
 
 // ------------------------------------------------------------- IV: Halley
@@ -743,6 +743,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_price_backward(FormArgs args) {
 // ------------------------------------------------------------- chains
 struct ChainArgs {
   int64_t n_chains, n_mat, n;
+  int64_t first;  // the launch's first quote
   const int64_t* chain_mat_off;
   const int64_t* mat_quote_off;
   const double *F, *r, *T, *price, *K;
@@ -780,7 +781,8 @@ __attribute__((amdgpu_waves_per_eu(FV_CHAINS_WAVES_PER_EU))) void k_iv_chains(Ch
     __syncthreads();
   }
   // (the wave's number as a scalar: the location runs on the scalar unit)
-  const int64_t w0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) +
+  const int64_t w0 = c.first +
+                     ((int64_t)blockIdx.x * (blockDim.x >> 6) +
                       __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * (64 * SLICES);
   const int lane = (int)__lane_id();
   int64_t m0[SLICES] = {}, c0[SLICES] = {};
@@ -1009,8 +1011,7 @@ size_t queue_bytes(int kernel, int block, int qpt) {
   return 0;
 }
 
-// Largest batch any launch covers: every launch has at least 64 quotes per
-// workgroup and at most 2^31 - 1 workgroups.
+// Largest batch of a call.
 constexpr int64_t kMaxQuotes = (int64_t)0x7fffffff * 64;
 
 int check_quotes(int model, const fv_quotes* q) {
@@ -1043,12 +1044,64 @@ KQuotes to_k(const fv_quotes* q) {
   return k;
 }
 
-dim3 grid_for(int64_t n, const LaunchShape& sh) {
-  const int64_t per = (int64_t)sh.block * sh.qpt;
-  return dim3((unsigned)((n + per - 1) / per));
+int launched(const char* what) { return fvh::launched(what); }
+
+// A launch holds fewer than 2^32 work items: of a larger grid the count is
+// taken modulo 2^32, with no error, and the quotes past it stay unwritten.
+// With a quote per thread a batch may be larger, so it is launched in parts
+// of at most kPart quotes, one as a rule.
+constexpr int64_t kPart = (int64_t)1 << 31;
+
+template <class A>
+void advance(A& field, int64_t by) {  // fv_arg, fv_arg_f32
+  if (field.ptr) field.ptr += by;
+}
+template <class V>
+void advance(V*& p, int64_t by) {
+  if (p) p += by;
+}
+template <class Q>
+void advance_quotes(Q& q, int64_t by) {
+  advance(q.price, by);
+  advance(q.fs, by);
+  advance(q.K, by);
+  advance(q.T, by);
+  advance(q.r, by);
+  advance(q.q, by);
+  advance(q.flag, by);
+}
+void advance(FormArgs& a, int64_t by) {
+  advance_quotes(a.q, by);
+  advance(a.sigma, by);
+  advance(a.up, by);
+  for (double*& p : a.out) advance(p, by);
+}
+void advance(IvArgs& a, int64_t by) {
+  advance_quotes(a.q, by);
+  advance(a.sig_out, by);
+  advance(a.st_out, by);
+  for (double*& p : a.g.p) advance(p, by);
+}
+void advance(Iv32Args& a, int64_t by) {
+  advance_quotes(a.q, by);
+  advance(a.sig_out, by);
+  advance(a.st_out, by);
+}
+void advance(TraceArgs& a, int64_t by) {
+  advance_quotes(a.q, by);
+  advance(a.out, by);
 }
 
-int launched(const char* what) { return fvh::launched(what); }
+// launch(args, grid) for every part of a flat batch in workgroups of `block`
+// quotes.
+template <class ARGS, class LAUNCH>
+void in_parts(ARGS args, int block, LAUNCH launch) {
+  for (int64_t left = args.q.n; left > 0; left -= kPart) {
+    args.q.n = std::min(left, kPart);
+    launch(args, dim3((unsigned)((args.q.n + block - 1) / block)));
+    if (left > kPart) advance(args, kPart);
+  }
+}
 
 int device_cus();
 
@@ -1234,18 +1287,19 @@ int fv_get_launch(int kernel, int* block, int* qpt) {
   return FV_OK;
 }
 
-// Launches the closed-form kernel KERN of `model` on `args` with the shape of
-// family FAMILY, one quote per thread.
+// Launches the kernel KERN of `model` on `args`, one quote per thread, in
+// workgroups of the family's size.
 #define FV_LAUNCH_FORM(KERN, FAMILY)                                                      \
   do {                                                                                    \
-    const LaunchShape sh{shape_for(FAMILY, model, q->n).block, 1};                        \
-    const dim3 grid = grid_for(q->n, sh), block(sh.block);                                \
+    const int block = shape_for(FAMILY, model, q->n).block;                               \
     hipStream_t s = (hipStream_t)stream;                                                  \
-    switch (model) {                                                                      \
-      case FV_MODEL_BLACK76: KERN<0><<<grid, block, 0, s>>>(args); break;                 \
-      case FV_MODEL_BLACK_SCHOLES: KERN<1><<<grid, block, 0, s>>>(args); break;           \
-      default: KERN<2><<<grid, block, 0, s>>>(args); break;                               \
-    }                                                                                     \
+    in_parts(args, block, [=](const auto& part, dim3 grid) {                              \
+      switch (model) {                                                                    \
+        case FV_MODEL_BLACK76: KERN<0><<<grid, block, 0, s>>>(part); break;               \
+        case FV_MODEL_BLACK_SCHOLES: KERN<1><<<grid, block, 0, s>>>(part); break;         \
+        default: KERN<2><<<grid, block, 0, s>>>(part); break;                             \
+      }                                                                                   \
+    });                                                                                   \
   } while (0)
 
 int fv_price(int model, const fv_quotes* q, fv_arg sigma, double* price_out, void* stream) {
@@ -1277,39 +1331,27 @@ int fv_implied_vol(int model, int solver, const fv_quotes* q, double* sigma_out,
   // every per-quote field an array (q only matters for Black-Scholes-Merton)
   const bool arr = q->price.ptr && q->fs.ptr && q->K.ptr && q->T.ptr && q->r.ptr && q->flag &&
                    (model != FV_MODEL_BSM || q->q.ptr);
-  if (solver == FV_SOLVER_LBR) {
-    const LaunchShape sh{shape_for(FV_KERNEL_IV_LBR, model, q->n).block, 1};
-    const dim3 grid = grid_for(q->n, sh), block(sh.block);
-#define FV_LBR(M, G)                                                                   \
-  (arr ? k_iv_lbr<M, G, true><<<grid, block, 0, s>>>(args) \
-       : k_iv_lbr<M, G, false><<<grid, block, 0, s>>>(args))
-    switch (model * 2 + (g.any ? 1 : 0)) {
-      case 0: FV_LBR(0, false); break;
-      case 1: FV_LBR(0, true); break;
-      case 2: FV_LBR(1, false); break;
-      case 3: FV_LBR(1, true); break;
-      case 4: FV_LBR(2, false); break;
-      default: FV_LBR(2, true); break;
+  const int family = solver == FV_SOLVER_LBR ? FV_KERNEL_IV_LBR : FV_KERNEL_IV_HALLEY;
+  const int block = shape_for(family, model, q->n).block;
+  const size_t lds = sizeof(Pending) * (size_t)block;
+  in_parts(args, block, [=](const IvArgs& part, dim3 grid) {
+#define FV_IV(M, G)                                                            \
+  (solver == FV_SOLVER_LBR                                                     \
+       ? (arr ? k_iv_lbr<M, G, true><<<grid, block, 0, s>>>(part)              \
+              : k_iv_lbr<M, G, false><<<grid, block, 0, s>>>(part))            \
+       : (arr ? k_iv_halley<M, G, true><<<grid, block, lds, s>>>(part)         \
+              : k_iv_halley<M, G, false><<<grid, block, lds, s>>>(part)))
+    switch (model * 2 + (part.g.any ? 1 : 0)) {
+      case 0: FV_IV(0, false); break;
+      case 1: FV_IV(0, true); break;
+      case 2: FV_IV(1, false); break;
+      case 3: FV_IV(1, true); break;
+      case 4: FV_IV(2, false); break;
+      default: FV_IV(2, true); break;
     }
-#undef FV_LBR
-    return launched("fv_implied_vol(LBR)");
-  }
-  const LaunchShape sh{shape_for(FV_KERNEL_IV_HALLEY, model, q->n).block, 1};
-  const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  const size_t lds = sizeof(Pending) * (size_t)sh.block;
-#define FV_HAL(M, G)                                                                    \
-  (arr ? k_iv_halley<M, G, true><<<grid, block, lds, s>>>(args) \
-       : k_iv_halley<M, G, false><<<grid, block, lds, s>>>(args))
-  switch (model * 2 + (g.any ? 1 : 0)) {
-    case 0: FV_HAL(0, false); break;
-    case 1: FV_HAL(0, true); break;
-    case 2: FV_HAL(1, false); break;
-    case 3: FV_HAL(1, true); break;
-    case 4: FV_HAL(2, false); break;
-    default: FV_HAL(2, true); break;
-  }
-#undef FV_HAL
-  return launched("fv_implied_vol(Halley)");
+#undef FV_IV
+  });
+  return launched(solver == FV_SOLVER_LBR ? "fv_implied_vol(LBR)" : "fv_implied_vol(Halley)");
 }
 
 int fv_implied_vol_f32(int model, const fv_quotes_f32* q, float* sigma_out,
@@ -1334,22 +1376,23 @@ int fv_implied_vol_f32(int model, const fv_quotes_f32* q, float* sigma_out,
   k.flag = q->flag;
   k.flag_value = q->flag_value;
   k.hsteps = g_halley_steps.load(std::memory_order_relaxed);
-  const LaunchShape sh{shape_for(FV_KERNEL_IV_HALLEY_F32, model, q->n).block, 1};
-  const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  const size_t lds = sizeof(Pending32) * (size_t)sh.block;
+  const int block = shape_for(FV_KERNEL_IV_HALLEY_F32, model, q->n).block;
+  const size_t lds = sizeof(Pending32) * (size_t)block;
   const Iv32Args args = {k, sigma_out, status_out};
   hipStream_t s = (hipStream_t)stream;
   const bool arr = q->price.ptr && q->fs.ptr && q->K.ptr && q->T.ptr && q->r.ptr && q->flag &&
                    (model != FV_MODEL_BSM || q->q.ptr);
+  in_parts(args, block, [=](const Iv32Args& part, dim3 grid) {
 #define FV_HAL32(M)                                           \
-  (arr ? k_iv_halley32<M, true><<<grid, block, lds, s>>>(args) \
-       : k_iv_halley32<M, false><<<grid, block, lds, s>>>(args))
-  switch (model) {
-    case FV_MODEL_BLACK76: FV_HAL32(0); break;
-    case FV_MODEL_BLACK_SCHOLES: FV_HAL32(1); break;
-    default: FV_HAL32(2); break;
-  }
+  (arr ? k_iv_halley32<M, true><<<grid, block, lds, s>>>(part) \
+       : k_iv_halley32<M, false><<<grid, block, lds, s>>>(part))
+    switch (model) {
+      case FV_MODEL_BLACK76: FV_HAL32(0); break;
+      case FV_MODEL_BLACK_SCHOLES: FV_HAL32(1); break;
+      default: FV_HAL32(2); break;
+    }
 #undef FV_HAL32
+  });
   return launched("fv_implied_vol_f32");
 }
 
@@ -1393,15 +1436,8 @@ int fv_lbr_trace(int model, const fv_quotes* q, uint32_t* path_out, void* stream
   if (rc) return rc;
   if (q->n == 0) return FV_OK;
   if (!path_out) return fail(FV_E_INVALID_ARG, "path_out is NULL");
-  const LaunchShape sh = shape_for(FV_KERNEL_IV_LBR, model, q->n);
-  const KQuotes k = to_k(q);
-  hipStream_t s = (hipStream_t)stream;
-  const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  switch (model) {
-    case FV_MODEL_BLACK76: k_lbr_trace<0><<<grid, block, 0, s>>>(k, path_out, sh.qpt); break;
-    case FV_MODEL_BLACK_SCHOLES: k_lbr_trace<1><<<grid, block, 0, s>>>(k, path_out, sh.qpt); break;
-    default: k_lbr_trace<2><<<grid, block, 0, s>>>(k, path_out, sh.qpt); break;
-  }
+  const TraceArgs args = {to_k(q), path_out};
+  FV_LAUNCH_FORM(k_lbr_trace, FV_KERNEL_IV_LBR);
   return launched("fv_lbr_trace");
 }
 
@@ -1410,15 +1446,8 @@ int fv_halley_trace(int model, const fv_quotes* q, uint32_t* steps_out, void* st
   if (rc) return rc;
   if (q->n == 0) return FV_OK;
   if (!steps_out) return fail(FV_E_INVALID_ARG, "steps_out is NULL");
-  const LaunchShape sh = shape_for(FV_KERNEL_IV_LBR, model, q->n);
-  const KQuotes k = to_k(q);
-  hipStream_t s = (hipStream_t)stream;
-  const dim3 grid = grid_for(q->n, sh), block(sh.block);
-  switch (model) {
-    case FV_MODEL_BLACK76: k_halley_trace<0><<<grid, block, 0, s>>>(k, steps_out, sh.qpt); break;
-    case FV_MODEL_BLACK_SCHOLES: k_halley_trace<1><<<grid, block, 0, s>>>(k, steps_out, sh.qpt); break;
-    default: k_halley_trace<2><<<grid, block, 0, s>>>(k, steps_out, sh.qpt); break;
-  }
+  const TraceArgs args = {to_k(q), steps_out};
+  FV_LAUNCH_FORM(k_halley_trace, FV_KERNEL_IV_LBR);
   return launched("fv_halley_trace");
 }
 
@@ -1438,23 +1467,25 @@ int fv_implied_vol_chains(int solver, const fv_chains* c, double* sigma_out,
   if (!c->chain_mat_off || !c->mat_quote_off || !c->F || !c->r || !c->T || !c->price ||
       !c->K || !c->flag || !sigma_out)
     return fail(FV_E_INVALID_ARG, "NULL chain array");
-  const ChainArgs k = {c->n_chains, c->n_maturities, c->n_quotes, c->chain_mat_off,
+  ChainArgs k = {c->n_chains, c->n_maturities, c->n_quotes, 0, c->chain_mat_off,
                        c->mat_quote_off, c->F, c->r, c->T, c->price, c->K, c->flag,
                        g_halley_steps.load(std::memory_order_relaxed), sigma_out, status_out};
   const LaunchShape sh = shape_for(FV_KERNEL_CHAINS, FV_MODEL_BLACK76, k.n);
-  // blockDim/64 waves per workgroup; the quote count is capped (kMaxQuotes) so
-  // that the grid fits
   const int slices = chain_slices(k.n);
   const int64_t per = (int64_t)slices * sh.block;
-  const dim3 grid((unsigned)((k.n + per - 1) / per)), block(sh.block);
+  const dim3 block(sh.block);
   const size_t lds = sizeof(ChainPending) * (size_t)per;
   hipStream_t s = (hipStream_t)stream;
-  if (solver == FV_SOLVER_LBR) {
-    if (slices == 1) k_iv_chains<FV_SOLVER_LBR, 1><<<grid, block, 0, s>>>(k);
-    else k_iv_chains<FV_SOLVER_LBR, 2><<<grid, block, 0, s>>>(k);
-  } else {
-    if (slices == 1) k_iv_chains<FV_SOLVER_HALLEY, 1><<<grid, block, lds, s>>>(k);
-    else k_iv_chains<FV_SOLVER_HALLEY, 2><<<grid, block, lds, s>>>(k);
+  for (; k.first < k.n; k.first += kPart / per * per) {  // whole waves, in order
+    const int64_t part = std::min(k.n - k.first, kPart / per * per);
+    const dim3 grid((unsigned)((part + per - 1) / per));
+    if (solver == FV_SOLVER_LBR) {
+      if (slices == 1) k_iv_chains<FV_SOLVER_LBR, 1><<<grid, block, 0, s>>>(k);
+      else k_iv_chains<FV_SOLVER_LBR, 2><<<grid, block, 0, s>>>(k);
+    } else {
+      if (slices == 1) k_iv_chains<FV_SOLVER_HALLEY, 1><<<grid, block, lds, s>>>(k);
+      else k_iv_chains<FV_SOLVER_HALLEY, 2><<<grid, block, lds, s>>>(k);
+    }
   }
   return launched("fv_implied_vol_chains");
 }
@@ -1464,8 +1495,11 @@ int fv_normalised_black(int64_t n, const double* x, const double* s, const int8_
   if (n < 0) return fail(FV_E_INVALID_ARG, "n < 0");
   if (n == 0) return FV_OK;
   if (!x || !s || !out) return fail(FV_E_INVALID_ARG, "NULL array");
-  const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-  k_normalised_black<<<grid, block, 0, (hipStream_t)stream>>>(n, x, s, flag, out);
+  for (int64_t at = 0; at < n; at += kPart) {
+    const int64_t part = std::min(n - at, kPart);
+    k_normalised_black<<<(unsigned)((part + 255) / 256), 256, 0, (hipStream_t)stream>>>(
+        part, x + at, s + at, flag ? flag + at : nullptr, out + at);
+  }
   return launched("fv_normalised_black");
 }
 
