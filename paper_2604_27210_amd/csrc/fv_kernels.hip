@@ -265,7 +265,9 @@ __device__ __forceinline__ Greeks greeks_solved(uint8_t st, bool general,
                                                 double P, double fs, double K, double T, double r,
                                                 double qy, int th) {
   fv::ClosedForm c;
-  const bool fast = !general && fv::closed_form_at(MODEL, sq, s, fs, K, T, r, qy, th, &c);
+  // (no short circuit: c is read below whatever comes of it)
+  const bool fast =
+      fv::all(fv::closed_form_at(MODEL, sq, s, fs, K, T, r, qy, th, &c), !general);
   Greeks gr = fv::greeks_of(c, MODEL, fs, T, r, qy, sg, th, P);
   if (__builtin_expect(!fast, 0)) {
     gr = no_greeks();
@@ -474,6 +476,7 @@ __attribute__((amdgpu_waves_per_eu(FV_WAVES_HALLEY(GREEKS)))) void k_iv_halley(I
   const unsigned t = threadIdx.x;
   bool fail = false;
   fv::HalleyState hs;
+  hs.s = 0.0;  // (what the Greeks of a quote without a volatility start from)
   hs.lo = 0.0;
   hs.hi = 0.0;
   if ((int64_t)t < q.n - b) {
