@@ -316,36 +316,31 @@ int fv_set_halley_steps(int steps);
 int fv_get_halley_steps(void);
 
 /* Launch-shape control.  fv_set_launch(kernel, block, quotes_per_thread)
- * overrides the launch shape of one kernel family (FV_KERNEL_*); block must
- * be a multiple of 64 in [64, 512] and quotes_per_thread in [1, 16], and for
- * the Halley families the workgroup's queue of unconverged quotes (24 bytes
- * per quote, 16 for binary32; the ragged-chain kernel, which takes one or two
- * 64-quote slices per wave and ignores quotes_per_thread, up to 64 bytes per
- * thread) must fit in 64 KiB of LDS
- * (FV_E_INVALID_ARG otherwise; the shape in force is kept).  All
- * binary64 kernels but the ragged one take one quote per thread at any
- * quotes_per_thread.
- * fv_get_launch reads the configured shape.  The shape applies as set to
- * batches large enough to fill the device; a batch that would give fewer
- * than 8 waves per SIMD (32 per compute unit) runs with fewer quotes per
- * thread (halved until it has them, or one per thread), and with fewer than
- * one workgroup per compute unit also with 64-thread workgroups.  No result
- * depends on the
- * shape.
+ * sets the workgroup size of one kernel family (FV_KERNEL_*); block must be a
+ * multiple of 64 in [64, 512].  Every kernel takes one quote per thread, but
+ * the ragged one one or two (by the batch's size): quotes_per_thread is
+ * checked (in [1, 16]; for the Halley families block x quotes_per_thread
+ * entries of 24 bytes, 16 for binary32, and for the ragged family 64 bytes per
+ * thread within 64 KiB), kept and given back, and changes nothing.
+ * FV_E_INVALID_ARG otherwise; the shape in force is kept.  fv_get_launch reads
+ * the configured shape.  A batch that would not give every compute unit a
+ * workgroup of the configured size runs in workgroups of 64.  No result
+ * depends on the shape.
  *
- * Autotuner: fv_autotune(kernel, model, n_hint, stream) times the candidate
- * shapes (block 64..512, 1..8 quotes per thread, within the LDS limit above)
+ * Autotuner: fv_autotune(kernel, model, n_hint, stream) times workgroups of
+ * 64, 128, 256 and 512 threads
  * of one kernel family on `stream` with synthetic in-range quotes, on a
  * batch of min(n_hint, 2^24) quotes (whole groups of 2,048), and keeps the
  * fastest for that family, model and the size class of n_hint -- the
  * classes are n < 2^14, [2^14, 2^16), [2^16, 2^18), [2^18, 2^20),
  * [2^20, 2^22), [2^22, 2^24) and n >= 2^24 (the ragged family is always
  * Black-76).  From then on a launch whose batch falls in a tuned class uses
- * the tuned shape as measured; untuned classes keep the configured shape and
+ * the tuned size as measured; untuned classes keep the configured size and
  * its narrowing.  fv_autotune allocates and frees scratch for this call only
  * and synchronises the stream: it is not graph-capturable.  fv_set_launch
  * clears the family's tuned classes (an explicit shape wins).
- * fv_launch_shape reports the shape a launch of n >= 1 quotes would use.
+ * fv_launch_shape reports the workgroup size and the quotes per thread that a
+ * launch of n >= 1 quotes would use.
  * fv_tuning_save writes every tuned class to a JSON file stamped with the
  * device's architecture name (hipDeviceProp_t::gcnArchName);
  * fv_tuning_load replaces the tuned classes with a file's, validating every

@@ -169,8 +169,9 @@ def get_launch(kernel):
 
 
 def autotune(kernel, model="bsm", n_hint: int = 1 << 22, stream=None):
-    """Time the launch shapes of one kernel family on `n_hint` synthetic
-    quotes and keep the fastest for that model and size class; returns it."""
+    """Time the workgroup sizes of one kernel family on `n_hint` synthetic
+    quotes and keep the fastest for that model and size class; returns the
+    shape a launch then has."""
     k = N.KERNELS[kernel] if isinstance(kernel, str) else int(kernel)
     N.check(N.load().fv_autotune(k, _model(model), int(n_hint),
                                  ctypes.c_void_p(_stream_ptr(stream))), "fv_autotune")

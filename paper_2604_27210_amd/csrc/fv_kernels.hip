@@ -1,15 +1,15 @@
 // fv_kernels.hip -- gfx950 kernels and the C ABI declared in include/fastvol.h.
 //
-// Every kernel is a single pass over struct-of-arrays FP64 inputs: each lane
-// loads its quote once (coalesced: consecutive lanes read consecutive
-// quotes), keeps the whole solve in registers and stores once.  A thread
-// handles `qpt` quotes spaced one block apart (one in the LBR kernels) so
-// that every load of a wave stays one contiguous 512-byte segment.  Divergent regions (solver
-// branches, extra Householder steps, rare evaluator forms) are plain
-// per-lane control flow: the hardware skips a side whose exec mask is empty,
-// so a wave pays only for the branches its own lanes take.  The Halley
-// kernel compacts its non-converged lanes with wave ballots into an LDS
-// queue and runs the bisection fallback over the packed queue.
+// Every kernel is a single pass over struct-of-arrays inputs: each lane loads
+// its quote once (consecutive lanes read consecutive quotes, so every load of
+// a wave is one contiguous segment), keeps the whole solve in registers and
+// stores once.  One quote per thread; a wave of the ragged kernel takes one
+// or two consecutive 64-quote slices.  Divergent regions (solver branches, a
+// further step, quotes outside the scaled forms' domain) are plain per-lane
+// control flow: the hardware skips a side whose exec mask is empty, so a wave
+// pays only for the branches its own lanes take.  The Halley kernels compact
+// the lanes that need more (bisection, the general solve) with wave ballots
+// into an LDS queue and work the packed queue off afterwards.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -983,11 +983,15 @@ __global__ void k_tune_expand(int64_t n, int mats, int per_mat, const double* cT
 // ------------------------------------------------------------- host side
 int fail(int code, const std::string& msg) { return fvh::fail(code, msg); }
 
+// A configured shape.  The workgroup size is what launches take;
+// quotes_per_thread is checked, kept and given back by fv_get_launch and the
+// tuning files, whose format and refusals stay as they were, and no launch
+// reads it (one quote per thread was the fastest in every kernel).
 struct LaunchShape {
   int block, qpt;
 };
-// Defaults from timing sweeps on MI355X (the wide-wing 10M-quote batch for
-// the solvers); fv_autotune re-derives them for other shapes of work.
+// Workgroup sizes from timing sweeps on MI355X (the wide-wing 10M-quote batch
+// for the solvers); fv_autotune re-derives them for other shapes of work.
 LaunchShape g_shape[FV_KERNEL_COUNT] = {
     {256, 2},  // price
     {64, 1},   // IV LBR
@@ -1002,9 +1006,9 @@ bool valid_shape(int block, int qpt) {
   return block >= 64 && block <= kMaxBlock && block % 64 == 0 && qpt >= 1 && qpt <= 16;
 }
 
-// Dynamic LDS a kernel family needs per workgroup at a shape: the Halley
-// paths' queue of failed lanes (one entry per quote of the workgroup); no
-// other family uses dynamic LDS.  Shapes above kMaxQueueBytes are refused.
+// What a shape is refused by: the Halley paths' LDS queue of the lanes that
+// need more, at block x qpt entries (the launches take one per thread and
+// slice).  Shapes above kMaxQueueBytes are refused.
 constexpr size_t kMaxQueueBytes = 65536;
 
 size_t queue_bytes(int kernel, int block, int qpt) {
@@ -1130,7 +1134,7 @@ int device_cus() {
 
 // ---------------------------------------------------------- tuning table
 // fv_autotune's results per (kernel family, model, size class of the batch);
-// a launch uses the entry of its class, as measured, when there is one.
+// a launch takes the workgroup size of its class when there is one.
 constexpr int kModels = 3;
 constexpr int kBuckets = 7;
 struct Tuned {
@@ -1138,9 +1142,9 @@ struct Tuned {
   float ms;        // the winning candidate's time when it was measured
 };
 Tuned g_tuned[FV_KERNEL_COUNT][kModels][kBuckets];
-// while fv_autotune times a candidate, launches of that family take it as is
+// while fv_autotune times a workgroup size, launches of that family take it
 int g_tuning_kernel = -1;
-LaunchShape g_tuning_shape = {0, 0};
+int g_tuning_block = 0;
 
 // Size class of a batch of n >= 1 quotes: 0 below 2^14, then one class per
 // factor of 4 ([2^14, 2^16) is 1, ...), 6 from 2^24 up.
@@ -1151,25 +1155,16 @@ int bucket_of(int64_t n) {
   return std::min(kBuckets - 1, (lg - 14) / 2 + 1);
 }
 
-// The shape a launch of n quotes of `kernel` under `model` uses: a tuned
-// entry of its size class if there is one, else the configured shape,
-// narrowed for a batch too small to keep every SIMD busy: quotes per thread
-// halve until the launch has at least 8 waves per SIMD (32 per CU; fewer,
-// longer waves leave SIMDs idle at the end), and the workgroup drops to one
-// wave if there is still less than one workgroup per CU.  Results never
-// depend on the shape.
-LaunchShape shape_for(int kernel, int model, int64_t n) {
-  if (kernel == g_tuning_kernel) return g_tuning_shape;
+// The workgroup size a launch of n quotes of `kernel` under `model` takes: a
+// tuned entry of its size class if there is one, else the configured size, or
+// one wave for a batch that would not give every CU a workgroup of that.
+// Results never depend on it.
+int block_for(int kernel, int model, int64_t n) {
+  if (kernel == g_tuning_kernel) return g_tuning_block;
   const Tuned& t = g_tuned[kernel][model][bucket_of(n > 0 ? n : 1)];
-  if (t.block) return LaunchShape{t.block, t.qpt};
-  LaunchShape sh = g_shape[kernel];
-  const int64_t cus = device_cus();
-  auto waves = [n](const LaunchShape& t) {
-    return (n + (int64_t)t.block * t.qpt - 1) / ((int64_t)t.block * t.qpt) * (t.block / 64);
-  };
-  while (sh.qpt > 1 && waves(sh) < 32 * cus) sh.qpt = (sh.qpt + 1) / 2;
-  if ((n + sh.block - 1) / sh.block < cus) sh.block = 64;
-  return sh;
+  if (t.block) return t.block;
+  const int block = g_shape[kernel].block;
+  return (n + block - 1) / block < device_cus() ? 64 : block;
 }
 
 // Architecture name of the current device (hipDeviceProp_t::gcnArchName,
@@ -1294,7 +1289,7 @@ int fv_get_launch(int kernel, int* block, int* qpt) {
 // workgroups of the family's size.
 #define FV_LAUNCH_FORM(KERN, FAMILY)                                                      \
   do {                                                                                    \
-    const int block = shape_for(FAMILY, model, q->n).block;                               \
+    const int block = block_for(FAMILY, model, q->n);                               \
     hipStream_t s = (hipStream_t)stream;                                                  \
     in_parts(args, block, [=](const auto& part, dim3 grid) {                              \
       switch (model) {                                                                    \
@@ -1335,7 +1330,7 @@ int fv_implied_vol(int model, int solver, const fv_quotes* q, double* sigma_out,
   const bool arr = q->price.ptr && q->fs.ptr && q->K.ptr && q->T.ptr && q->r.ptr && q->flag &&
                    (model != FV_MODEL_BSM || q->q.ptr);
   const int family = solver == FV_SOLVER_LBR ? FV_KERNEL_IV_LBR : FV_KERNEL_IV_HALLEY;
-  const int block = shape_for(family, model, q->n).block;
+  const int block = block_for(family, model, q->n);
   const size_t lds = sizeof(Pending) * (size_t)block;
   in_parts(args, block, [=](const IvArgs& part, dim3 grid) {
 #define FV_IV(M, G)                                                            \
@@ -1379,7 +1374,7 @@ int fv_implied_vol_f32(int model, const fv_quotes_f32* q, float* sigma_out,
   k.flag = q->flag;
   k.flag_value = q->flag_value;
   k.hsteps = g_halley_steps.load(std::memory_order_relaxed);
-  const int block = shape_for(FV_KERNEL_IV_HALLEY_F32, model, q->n).block;
+  const int block = block_for(FV_KERNEL_IV_HALLEY_F32, model, q->n);
   const size_t lds = sizeof(Pending32) * (size_t)block;
   const Iv32Args args = {k, sigma_out, status_out};
   hipStream_t s = (hipStream_t)stream;
@@ -1473,10 +1468,8 @@ int fv_implied_vol_chains(int solver, const fv_chains* c, double* sigma_out,
   ChainArgs k = {c->n_chains, c->n_maturities, c->n_quotes, 0, c->chain_mat_off,
                        c->mat_quote_off, c->F, c->r, c->T, c->price, c->K, c->flag,
                        g_halley_steps.load(std::memory_order_relaxed), sigma_out, status_out};
-  const LaunchShape sh = shape_for(FV_KERNEL_CHAINS, FV_MODEL_BLACK76, k.n);
-  const int slices = chain_slices(k.n);
-  const int64_t per = (int64_t)slices * sh.block;
-  const dim3 block(sh.block);
+  const int block = block_for(FV_KERNEL_CHAINS, FV_MODEL_BLACK76, k.n), slices = chain_slices(k.n);
+  const int64_t per = (int64_t)slices * block;
   const size_t lds = sizeof(ChainPending) * (size_t)per;
   hipStream_t s = (hipStream_t)stream;
   for (; k.first < k.n; k.first += kPart / per * per) {  // whole waves, in order
@@ -1633,40 +1626,34 @@ int fv_autotune(int kernel, int model, int64_t n_hint, void* stream) {
       default: return fv_implied_vol_chains(FV_SOLVER_LBR, &cs, o1, st, stream);
     }
   };
-  const int blocks[] = {64, 128, 256, 512};
-  const int qpts[] = {1, 2, 4, 8};
-  LaunchShape best = {0, 0};
+  int best = 0;
   float best_ms = 1e30f;
-  for (int b : blocks) {
-    for (int qq : qpts) {
-      if (rc != FV_OK) break;
-      if (queue_bytes(kernel, b, qq) > kMaxQueueBytes) continue;
-      g_tuning_kernel = kernel;
-      g_tuning_shape = LaunchShape{b, qq};
-      rc = run();  // warm-up
-      float mn = 1e30f;
-      for (int rep = 0; rep < 3 && rc == FV_OK; ++rep) {
-        if (hipEventRecord(e0, s) != hipSuccess) {
-          rc = fail(FV_E_HIP, "fv_autotune: event record");
-          break;
-        }
-        rc = run();
-        float ms = 0.0f;
-        if (rc == FV_OK && (hipEventRecord(e1, s) != hipSuccess ||
-                            hipEventSynchronize(e1) != hipSuccess ||
-                            hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
-          rc = fail(FV_E_HIP, "fv_autotune: event timing");
-        mn = std::min(mn, ms);
+  for (int b : {64, 128, 256, 512}) {
+    if (rc != FV_OK) break;
+    g_tuning_kernel = kernel;
+    g_tuning_block = b;
+    rc = run();  // warm-up
+    float mn = 1e30f;
+    for (int rep = 0; rep < 3 && rc == FV_OK; ++rep) {
+      if (hipEventRecord(e0, s) != hipSuccess) {
+        rc = fail(FV_E_HIP, "fv_autotune: event record");
+        break;
       }
-      if (rc == FV_OK && mn < best_ms) {
-        best_ms = mn;
-        best = {b, qq};
-      }
+      rc = run();
+      float ms = 0.0f;
+      if (rc == FV_OK && (hipEventRecord(e1, s) != hipSuccess ||
+                          hipEventSynchronize(e1) != hipSuccess ||
+                          hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
+        rc = fail(FV_E_HIP, "fv_autotune: event timing");
+      mn = std::min(mn, ms);
+    }
+    if (rc == FV_OK && mn < best_ms) {
+      best_ms = mn;
+      best = b;
     }
   }
   g_tuning_kernel = -1;
-  if (rc == FV_OK && best.block)
-    g_tuned[kernel][tuned_model][bucket] = Tuned{best.block, best.qpt, best_ms};
+  if (rc == FV_OK && best) g_tuned[kernel][tuned_model][bucket] = Tuned{best, 1, best_ms};
   // best-effort cleanup: an error here cannot change the result above
   (void)hipStreamSynchronize(s);
   (void)hipEventDestroy(e0);
@@ -1681,10 +1668,8 @@ int fv_launch_shape(int kernel, int model, int64_t n, int* block, int* qpt) {
   if (model < FV_MODEL_BLACK76 || model > FV_MODEL_BSM)
     return fail(FV_E_INVALID_ARG, "model out of range");
   if (n < 1) return fail(FV_E_INVALID_ARG, "n < 1");
-  const LaunchShape sh =
-      shape_for(kernel, kernel == FV_KERNEL_CHAINS ? FV_MODEL_BLACK76 : model, n);
-  *block = sh.block;
-  *qpt = sh.qpt;
+  *block = block_for(kernel, kernel == FV_KERNEL_CHAINS ? FV_MODEL_BLACK76 : model, n);
+  *qpt = kernel == FV_KERNEL_CHAINS ? chain_slices(n) : 1;
   return FV_OK;
 }
 
