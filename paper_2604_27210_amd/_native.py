@@ -18,8 +18,6 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 # compiled with different register-allocation targets)
 LIB_PATH = os.environ.get("FASTVOL_LIBRARY") or os.path.join(HERE, "_build", "libfastvol.so")
 
-BIND_PATH = os.path.join(HERE, "_build", "fv_bind.so")
-
 FV_OK = 0
 FV_E_INVALID_ARG = -1
 FV_E_HIP = -2
@@ -142,20 +140,26 @@ def _current_stream(device):
 
 
 def bind():
-    """The compiled tensor marshalling, bound to the loaded library (raises
-    if either has not been built)."""
+    """The compiled tensor marshalling, bound to the loaded library (raises if
+    that has not been built).  Where none was built for this torch (another one
+    was installed since, or FASTVOL_LIBRARY names a library that came without
+    it) it is compiled first, once: host code, no GPU compiler."""
     global _bind
     if _bind is not None:
         return _bind
     lib = load()
-    if not os.path.exists(BIND_PATH):
-        raise FastvolError(
-            "fv_bind.so is not built (%s); run paper_2604_27210_amd/build.py "
-            "or __graft_entry__.build()" % BIND_PATH)
+    from . import build
+    path = build.bind_path()
+    if not os.path.exists(path):
+        try:
+            build.build_bind()
+        except (OSError, RuntimeError) as e:
+            raise FastvolError("no tensor marshalling for torch here (%s), and it cannot be built: %s"
+                               % (path, e)) from e
     import torch
-    loader = importlib.machinery.ExtensionFileLoader("fv_bind", BIND_PATH)
+    loader = importlib.machinery.ExtensionFileLoader("fv_bind", path)
     mod = importlib.util.module_from_spec(
-        importlib.util.spec_from_file_location("fv_bind", BIND_PATH, loader=loader))
+        importlib.util.spec_from_file_location("fv_bind", path, loader=loader))
     # the raw handle of the current stream without building a Stream object
     mod.init(tuple(ctypes.cast(getattr(lib, nm), ctypes.c_void_p).value for nm in BOUND),
              FastvolError, getattr(torch._C, "_cuda_getCurrentRawStream", _current_stream))

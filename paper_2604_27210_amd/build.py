@@ -59,7 +59,15 @@ def build_capi_demo(verbose: bool = False) -> str:
 
 
 BIND_SRC = os.path.join(CSRC, "fv_bind.cpp")
-BIND = os.path.join(OUT_DIR, "fv_bind.so")
+
+
+def bind_path() -> str:
+    """The tensor marshalling for the interpreter and the torch in use: it
+    reads torch's own structures, so each build of torch has its own, and one
+    that was compiled for another is never loaded."""
+    import torch
+    return os.path.join(OUT_DIR, "fv_bind-%s-torch-%s.so"
+                        % (sys.implementation.cache_tag, torch.__version__))
 
 
 def build_bind(verbose: bool = False) -> str:
@@ -69,7 +77,9 @@ def build_bind(verbose: bool = False) -> str:
     it, and is imported after torch, whose libraries are then mapped."""
     import torch
     base = os.path.dirname(torch.__file__)
-    tmp = BIND + ".tmp%d" % os.getpid()
+    out = bind_path()
+    os.makedirs(os.path.dirname(out), exist_ok=True)
+    tmp = out + ".tmp%d" % os.getpid()
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            "-isystem", os.path.join(base, "include"),
@@ -81,8 +91,8 @@ def build_bind(verbose: bool = False) -> str:
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
-    os.replace(tmp, BIND)
-    return BIND
+    os.replace(tmp, out)
+    return out
 
 
 def build(verbose: bool = False, extra=None, out: str = None) -> str:
