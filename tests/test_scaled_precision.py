@@ -1,5 +1,5 @@
-"""What the scaled solve leaves in a root it is handed the value of, on the
-CPU: the calibration prices a volatility and takes the implied one, and its
+"""What the scaled solve leaves in a root it is handed the value of, on the CPU.
+The calibration prices a volatility and takes the implied one, and its
 gradient sums the difference over thousands of quotes, so the systematic part
 counts and not only the largest error."""
 import ctypes
@@ -26,6 +26,20 @@ extern "C" void h_back(int64_t n, const double* x, const double* s, double* scal
     const fv::NBlack nb = fv::normalised_black(x[i], s[i], bmax);
     general[i] = fv::lbr_solve(x[i], nb.b, bmax, nb.lnbp + fv::flog(nb.ratio), fv::kLbrMinSteps,
                                fv::kLbrMaxSteps, fv::kLbrStepTol).s;
+  }
+}
+extern "C" void h_plane(int64_t n, const double* x, const double* s, double* lbr, double* hal,
+                        double* cond) {
+  for (int64_t i = 0; i < n; ++i) {
+    const double bmax = fv::fexp(0.5 * x[i]);
+    const fv::NBlack nb = fv::normalised_black(x[i], s[i], bmax);
+    const double bh = nb.b / bmax, ch = nb.c / bmax;
+    cond[i] = fmin(nb.b, nb.c) / (s[i] * nb.bp);
+    lbr[i] = hal[i] = -1.0;
+    if (!fv::scaled_domain(x[i], bh, ch)) continue;
+    if (!fv::lbr_solve_scaled(x[i], bh, ch, &lbr[i])) lbr[i] = -2.0;
+    const fv::HalleyState hs = fv::halley_solve_scaled(x[i], bh, ch, 8);
+    hal[i] = hs.converged ? hs.s : -2.0;
   }
 }
 '''
@@ -61,3 +75,28 @@ def test_a_priced_volatility_comes_back(host):
         err = root / s - 1.0
         assert np.max(np.abs(err)) <= 32 * U
         assert abs(err.mean()) <= 0.25 * U, err.mean()
+
+
+def test_roots_by_their_conditioning(host):
+    """The whole plane that the scaled solve takes, the upper wing down to
+    1 - beta/b_max = 2^-40 with it: a value within a few u of its own (b, or
+    b_max - b where that is the smaller) gives its s back within 16 u times
+    1 + b/(s b') (or (b_max - b)/(s b')), and every quote settles."""
+    rng = np.random.default_rng(2)
+    n = 400_000
+    s = np.exp(rng.uniform(np.log(1e-9), np.log(15.0), n))
+    g = rng.uniform(-36.0, 7.3, n)  # h + t
+    x = np.minimum(s * (g - 0.5 * s), 0.0)
+    x[:2000] = 0.0
+    keep = x >= -128.0
+    x, s = np.ascontiguousarray(x[keep]), np.ascontiguousarray(s[keep])
+    lbr, hal, cond = (np.empty(len(x)) for _ in range(3))
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    host.h_plane(ctypes.c_int64(len(x)), p(x), p(s), p(lbr), p(hal), p(cond))
+    inside = lbr != -1.0
+    assert inside.mean() > 0.8
+    assert not np.any(lbr[inside] == -2.0) and not np.any(hal[inside] == -2.0)
+    err = np.abs(lbr / s - 1.0)[inside] / (U * (1.0 + cond[inside]))
+    print("LBR: %.3g u of the conditioning at most" % err.max())
+    assert np.all(err <= 16.0)
+    assert np.all(np.abs(hal / s - 1.0)[inside] <= 1e-8)
