@@ -161,10 +161,12 @@ __host__ __device__ __attribute__((always_inline)) inline Reduced reduce_quote(i
   return o;
 }
 
-// What the scaled solvers (fv_lbr.h) need of a quote.  The status is decided
-// by the very expressions of reduce_quote; `general` marks a quote outside
-// the scaled solvers' domain, or whose status these forms cannot decide: it
-// goes through reduce_quote and the general solver.
+// What the scaled solvers (fv_lbr.h) need of a quote.  The status comes from
+// the comparisons of reduce_quote on the same quantities (F - K is rounded
+// here and may be contracted there, so a quote within an ulp of its intrinsic
+// value can fall on either side); `general` marks a quote outside the scaled
+// solvers' domain, or whose status these forms cannot decide: it goes through
+// reduce_quote, which decides it whole, and the general solver.
 // Against reduce_quote this drops ln beta (a logarithm) and 1/sqrt(F K)
 // (two reciprocal square roots): bh = beta/b_max = (Pu - I)/min(F, K).
 struct ScaledQuote {
@@ -353,32 +355,36 @@ struct ScaledTerms {
 };
 
 // False outside the domain (the caller takes the general forms): |x| above
-// 128, total volatility outside [2^-60, 64], a density below e^-600, or
-// F phi(d1) below 2^-640: what is made of it (b/b_max down to 2^-70 of the
-// density, the two terms, the discounted values down to 2^-288 of those) stays
-// a normal number, where the general forms multiply by the spot last or not at
-// all.
+// 128, total volatility outside [2^-60, 64], b/b_max (or its complement) below
+// 2^-1010 (which a clamped exponent does not reach), or the time value m part,
+// discounted or not, below 2^-1000: it is at most four times F phi(d1), so
+// that, both terms and their discounted values are normal numbers then.  The
+// general forms multiply by the spot last or not at all.
 __host__ __device__ __attribute__((always_inline)) inline bool scaled_terms(double F, double K,
-                                                                            double x, double s,
-                                                                            int theta,
+                                                                            double D, double x,
+                                                                            double s, int theta,
                                                                             ScaledTerms* o) {
   const ScaledEval e = scaled_eval(x, s);
   const double ea = -0.5 * e.g * e.g;
   const double E = fexp_in(fmax(ea, -700.0));
   const double dens = kInvSqrt2Pi * E;  // b'/b_max
   const double part = dens * e.rho;
-  const double bh = e.comp ? 1.0 - part : part;
-  const double U2 = 0.5 * E * e.e2, U1 = U2 + bh;
-  const double V1 = e.comp ? part - U2 : 1.0 - U1;  // 1 - U1
+  // (products that meet a sum are written as fmas: left to the compiler, one
+  // kernel contracts them and another does not)
+  const double hE = 0.5 * E;
+  const double bh = e.comp ? fma(-dens, e.rho, 1.0) : part;
+  const double U2 = hE * e.e2, U1 = fma(hE, e.e2, bh);
+  const double V1 = e.comp ? fma(dens, e.rho, -U2) : 1.0 - U1;  // 1 - U1
   const bool low = F < K, call = theta > 0, itm = call ? F > K : low;
   const double m = low ? F : K, M = low ? K : F;
   const bool as_call = call != itm;  // the out-of-the-money counterpart's kind
-  const double t1 = m * (itm ? V1 : U1), t2 = m * U2, t3 = itm ? M - t2 : t2;
+  const double t1 = m * (itm ? V1 : U1), t2 = m * U2, t3 = itm ? fma(-m, U2, M) : t2;
   o->FN = as_call ? t1 : t3;
   o->KN = as_call ? t3 : t1;
   o->P = fma(m, bh, itm ? fabs(F - K) : 0.0);
   o->V = m * dens;
-  return all(x >= -128.0, s >= 0x1p-60, s <= 64.0, ea >= -600.0, o->V >= 0x1p-640);
+  return all(x >= -128.0, s >= 0x1p-60, s <= 64.0, part >= 0x1p-1010,
+             fmin(D, 1.0) * (m * part) >= 0x1p-1000);
 }
 
 // A quote the scaled closed forms take: every quantity they divide by or
@@ -406,7 +412,7 @@ __host__ __device__ __attribute__((always_inline)) inline bool closed_form(
   o->sqT = T * o->isqT;
   o->s = sigma * o->sqT;
   const double x = -fabs(log_ratio(o->F, K));
-  return all(scaled_terms(o->F, K, x, o->s, theta, &o->t), in, ((theta + 1) & ~2) == 0);
+  return all(scaled_terms(o->F, K, o->D, x, o->s, theta, &o->t), in, ((theta + 1) & ~2) == 0);
 }
 
 // The same for a quote the scaled path has just solved: its total volatility
@@ -420,7 +426,7 @@ __host__ __device__ __attribute__((always_inline)) inline bool closed_form_at(
   o->isqT = sq.isqrtT;
   o->sqT = T * sq.isqrtT;
   o->s = s;
-  return all(scaled_terms(sq.F, K, sq.x, s, theta, &o->t),
+  return all(scaled_terms(sq.F, K, sq.D, sq.x, s, theta, &o->t),
              closed_form_domain(fs, K, T, r * T, cT));
 }
 
@@ -442,7 +448,7 @@ __host__ __device__ inline Greeks greeks_of(const ClosedForm& c, int model, doub
     g.rho = -T * price;
   } else {
     const double dKN = dth * c.D * c.t.KN;
-    g.theta = -decay - r * dKN;
+    g.theta = fma(-r, dKN, -decay);
     if (model == kBlackScholesMerton) g.theta = fma(q, dFN, g.theta);
     g.rho = T * dKN;
   }

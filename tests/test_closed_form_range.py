@@ -8,6 +8,7 @@ import subprocess
 import numpy as np
 import pytest
 
+import oracle
 from _helpers import U
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -94,10 +95,21 @@ def test_small_and_large_spots(host, model, th):
     assert fast.mean() > 0.2
     tol = (64 * U * (1.0 + 0.5 * (h + s) ** 2))[:, None]
     bad = fast[:, None] & ~(np.abs(a - b) <= tol * np.abs(b) + 2.0 ** -1070)
+    # where the general form's own density or tail (at h + s/2) leaves the
+    # normal range it is the one that is off: binary128 there
+    i = np.where(bad.any(axis=1) & (h + 0.5 * s > 37.0))[0]
+    if len(i):
+        fl = np.full(len(i), th, dtype=np.int8)
+        name = ["black76", "bs", "bsm"][model]
+        c = [v[i] for v in (fs, K, T, r, q, s / np.sqrt(T))]
+        P, g = oracle.price(name, *c, fl), oracle.greeks(name, *c, fl)
+        v = oracle.iv_grad_at(name, *c, fl)  # -(dP/dX)/vega
+        ref = np.stack([P, g["delta"], g["gamma"], g["vega"], g["rho"], -v[:, 2] * g["vega"], -v[:, 5] * g["vega"]], 1)
+        bad[i] &= ~(np.abs(a[i] - ref) <= tol[i] * np.abs(ref) + 2.0 ** -1070)
     for j, name in enumerate(NAMES):
         i = np.where(bad[:, j])[0]
-        assert len(i) == 0, (name, len(i), ["fs %.3g T %.3g r %.3g s %.3g h %.3g: %.17g %.17g" % (fs[k], T[k], r[k], s[k], h[k], a[k, j], b[k, j])
-                                            for k in i[:3]])
+        assert len(i) == 0, (name, len(i), ["fs %.3g T %.3g r %.3g s %.3g h %.3g: %.17g %.17g"
+                                            % (fs[k], T[k], r[k], s[k], h[k], a[k, j], b[k, j]) for k in i[:3]])
 
 
 @pytest.mark.parametrize("K", [100.0, 1e-3, 1e-200])
