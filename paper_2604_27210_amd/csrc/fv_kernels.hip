@@ -264,11 +264,13 @@ __device__ __forceinline__ Greeks greeks_solved(uint8_t st, bool general,
                                                 const fv::ScaledQuote& sq, double s, double sg,
                                                 double P, double fs, double K, double T, double r,
                                                 double qy, int th) {
-  fv::ClosedForm c;
-  // (no short circuit: c is read below whatever comes of it)
-  const bool fast =
-      fv::all(fv::closed_form_at(MODEL, sq, s, fs, K, T, r, qy, th, &c), !general);
-  Greeks gr = fv::greeks_of(c, MODEL, fs, T, r, qy, sg, th, P);
+  Greeks gr = no_greeks();
+  bool fast = false;
+  if (!general) {
+    fv::ClosedForm c;
+    fast = fv::closed_form_at(MODEL, sq, s, fs, K, T, r, qy, th, &c);
+    gr = fv::greeks_of(c, MODEL, fs, T, r, qy, sg, th, P);
+  }
   if (__builtin_expect(!fast, 0)) {
     gr = no_greeks();
     if (st == fv::kQOk)
