@@ -250,9 +250,9 @@ __host__ __device__ __attribute__((always_inline)) inline HalleyState halley_sol
 }
 
 // What the scaled solve needs of a quote, as fv::scaled_quote: the status by
-// the very expressions of reduce_quote; `general` marks a quote outside its
-// domain, or whose status these forms cannot decide, which goes through
-// reduce_quote and halley_solve.  ln(F/K) comes from the significands'
+// the comparisons of reduce_quote; `general` marks a quote outside its domain,
+// or whose status these forms cannot decide, which goes through reduce_quote
+// and halley_solve.  ln(F/K) comes from the significands'
 // difference (fv::log_ratio), 1/sqrt(T) from the hardware reciprocal root and
 // one Newton step.
 struct ScaledQuote {

@@ -15,9 +15,9 @@
 //   b'/b_max = e^{-g^2/2}/sqrt(2 pi),  g = h + t
 // (h = x/s, t = s/2; h t = x/2 cancels in the exponent), with ratios to b'
 // in place of values and logarithms in place of the values that leave the
-// range.  Domain (start_in_domain): |x| zero or in [2^-60, 128], bh above
-// 2^-1000; a quote outside it, or whose iteration does not settle, takes the
-// binary64 path.
+// range.  Domain (scaled_domain, fv_lbr.h): |x| zero or in [2^-60, 128], bh
+// above 2^-960, 1 - bh above 2^-40; a quote outside it, or whose iteration
+// does not settle, takes the binary64 path.
 #pragma once
 
 #include <hip/hip_runtime.h>
