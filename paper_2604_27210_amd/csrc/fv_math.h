@@ -57,6 +57,20 @@ __host__ __device__ inline double rcp(double x) {
 #endif
 }
 
+// 1/(a b) for a product in range, without the product's own rounding: its
+// error, exact in an fma, goes into the residual of the refinement.
+__host__ __device__ inline double rcp_product(double a, double b) {
+  const double p = a * b, pe = fma(a, b, -p);
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double r = __builtin_amdgcn_rcp(p);
+  const double e = fma(-pe, r, fma(-p, r, 1.0));
+  return fma(r, fma(e, e, e), r);
+#else
+  const double r = 1.0 / p;
+  return fma(-pe * r, r, r);
+#endif
+}
+
 // As rcp, but 1/0 = inf and 1/inf = 0 as for a division (the hardware
 // estimate is exact there and is kept when the refinement turns to NaN).
 __host__ __device__ inline double rcp_safe(double x) {
