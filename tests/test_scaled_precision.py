@@ -15,6 +15,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SRC = r'''
 #include <cstdint>
+#include "fv_f32.h"
 #include "fv_quote.h"
 extern "C" void h_back(int64_t n, const double* x, const double* s, double* scaled, double* general) {
   for (int64_t i = 0; i < n; ++i) {
@@ -35,6 +36,16 @@ extern "C" void h_ratio(int64_t n, const double* x, const double* s, double* sca
     const fv::NBlack nb = fv::normalised_black(x[i], s[i], fv::fexp(0.5 * x[i]));
     scaled[i] = e.rho;
     general[i] = e.comp ? nb.cratio : nb.ratio;
+  }
+}
+extern "C" void h_ratio32(int64_t n, const double* x, const double* s, double* scaled,
+                          double* general) {
+  for (int64_t i = 0; i < n; ++i) {
+    const float xf = (float)x[i], sf = (float)s[i];
+    const fv::s32::Eval e = fv::s32::eval<fv::s32::kFitSolve>(-xf, sf);
+    const fv32::NBlack nb = fv32::normalised_black(xf, sf, fv32::fexp(0.5f * xf));
+    scaled[i] = e.rho;
+    general[i] = (double)(e.comp ? nb.c : nb.b) / nb.bp;
   }
 }
 extern "C" void h_plane(int64_t n, const double* x, const double* s, double* lbr, double* hal,
@@ -111,20 +122,23 @@ def test_roots_by_their_conditioning(host):
     assert np.all(np.abs(hal / s - 1.0)[inside] <= 1e-8)
 
 
-def test_evaluation_as_precise_as_the_general_one(host):
+@pytest.mark.parametrize("bits", [64, 32])
+def test_evaluation_as_precise_as_the_general_one(host, bits):
     """b/b' (or its complement) near the money, where an error in it is the
     root's: rms against 40 digits no larger than the general evaluator's, which
     takes both reciprocals by themselves (25% for the sample of 1,500 and the
-    two roundings that the common reciprocal leaves)."""
+    two roundings that the binary64 evaluation's common reciprocal leaves)."""
     mp = pytest.importorskip("mpmath").mp
     mp.dps = 40
     rng = np.random.default_rng(3)
     n = 1500
     s = np.exp(rng.uniform(np.log(0.01), np.log(2.0), n))
     x = -rng.uniform(0.0, 0.5, n) * s
+    if bits == 32:
+        s, x = (v.astype(np.float32).astype(np.float64) for v in (s, x))
     out = [np.empty(n) for _ in range(2)]
     p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
-    host.h_ratio(ctypes.c_int64(n), p(x), p(s), *[p(o) for o in out])
+    (host.h_ratio if bits == 64 else host.h_ratio32)(ctypes.c_int64(n), p(x), p(s), *[p(o) for o in out])
     want = []
     for xi, si in zip(x, s):
         h, t = mp.mpf(float(xi)) / mp.mpf(float(si)), mp.mpf(float(si)) / 2
