@@ -41,11 +41,11 @@ if ROOT not in sys.path:
 # The traffic figure is reported only while the kernel sources still hash to
 # ``source_sha256``; the FLOP figure is the algorithmic count of that source.
 LBR_PROFILE = {
-    "source_sha256": "bbd02861d589c60f2ac342e3ee3e18272cdbd47b6e8032e8e03032c1077cd8b1",
-    "flop_per_quote": 309.2,
-    "executed_flop_per_quote": 311.0,
-    "valu_per_quote": 549.9,
-    "fetch_bytes_per_quote": 50.009,
+    "source_sha256": "5c95dc1cabb9f2fb8df0364bcf44160309d7584c11f55bd60bd2680c80dcf8c8",
+    "flop_per_quote": 314.1,
+    "executed_flop_per_quote": 316.0,
+    "valu_per_quote": 555.8,
+    "fetch_bytes_per_quote": 50.012,
     "write_bytes_per_quote": 9.000,
 }
 FP64_VECTOR_PEAK_TFLOPS = 78.6

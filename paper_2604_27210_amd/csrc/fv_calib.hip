@@ -345,10 +345,9 @@ __device__ __forceinline__ double grad_wave(const KSvi& c, int64_t wave,
   return row_sum(fold16(fold32(e2, e2), fold32(e2, e2)));
 }
 
-// Bound by the vector ALU (about 790 instructions per 64 quotes, an eighth of
-// them the location and a tenth the sums; 1,347 with the solve in binary64 and
-// the sums through LDS): 2.1M quotes in 7,529 maturities 46 us (88 with
-// those).  At least 7 waves per SIMD: free, it takes 74
+// Bound by the vector ALU (805 instructions per 64 quotes, an eighth of them
+// the location and a tenth the sums; 1,347 with the solve in binary64 and the
+// sums through LDS): 2.1M quotes in 7,529 maturities 47 us (88 with those).  At least 7 waves per SIMD: free, it takes 74
 // registers, two too many, and ten steps take 530 us for 517 (below 0.5M
 // quotes, where waves are few, the floor costs 1%).  Two slices per wave, as
 // in the ragged solve, were 1 to 15% slower.

@@ -158,11 +158,11 @@ __device__ __forceinline__ V opaque(V i) {
 }
 
 // The closed-form kernels below (price, Greeks, adjoints) are bound by
-// memory: one evaluation and three exponentials a quote (260 to 350 vector
+// memory: one evaluation and three exponentials a quote (266 to 363 vector
 // instructions, 340 to 500 with the general forms) against 57 to 113 bytes.
 // 5M BSM prices: 57 to 60 us (70 before; 55 at the 5.2 TB/s of a copy), 2M
-// Black-76 Greeks 32 to 36 us (46; 31), the adjoint of 1M BSM quotes 20.5 us
-// (27; 22, part of it served from cache).  One quote per thread, every field
+// Black-76 Greeks 29 to 37 us (45; 31), the adjoint of 1M BSM quotes 20 to 22
+// us (27; 22, part of it served from cache).  One quote per thread, every field
 // on a scalar base.  Quotes outside the scaled forms' domain take the general
 // ones, read again from memory.
 
@@ -281,10 +281,10 @@ __device__ __forceinline__ Greeks greeks_solved(uint8_t st, bool general,
 }
 
 // ------------------------------------------------------------- IV: LBR
-// Bound by the vector ALU's issue rate: about 580 vector instructions per
-// quote, every side of the guess a mixed wave takes included (1,157 with the
-// guess and the first step in binary64).  10M wide-wing BSM quotes: 154 us
-// (355 with those), 1M BS quotes with the five Greeks: 26 us (54).
+// Bound by the vector ALU's issue rate: 584 vector instructions per quote,
+// every side of the guess a mixed wave takes included (1,157 with the guess
+// and the first step in binary64).  10M wide-wing BSM quotes: 156 to 159 us
+// (355 with those), 1M BS quotes with the five Greeks: 26 to 27 us (54).
 // One quote per thread: with a loop over several the compiler keeps the
 // polynomials' constants in registers across the whole solve, 110 VGPRs in
 // place of 55, and the book took 220 us where it then took 190.
