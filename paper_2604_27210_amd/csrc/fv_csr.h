@@ -37,9 +37,10 @@ struct OffWindow {
   // itself: a dependent load less per search than with a window of its own,
   // and the location is a chain of those.  With the window in 32 bits, 273k
   // quotes in 60 chains (Halley) 8.8 -> 8.2 us, 8.4M in 2,000 (LBR) 130 ->
-  // 125, the calibration's step on 500 chains 51.6 -> 49.1.  The loads stay
-  // below `count`; malformed (decreasing) offsets still shrink the range every
-  // level and give an m below it.
+  // 125, the calibration's step on 500 chains 51.6 -> 49.1 (any count and any
+  // distance, below, take 0.5 of that back).  The loads stay below `count`;
+  // malformed (decreasing) offsets still shrink the range every level and give
+  // an m below it.
   __device__ __forceinline__ int64_t locate(const int64_t* __restrict__ o, int64_t c, int64_t k) {
     off = o;
     count = c;
