@@ -41,7 +41,7 @@ if ROOT not in sys.path:
 # The traffic figure is reported only while the kernel sources still hash to
 # ``source_sha256``; the FLOP figure is the algorithmic count of that source.
 LBR_PROFILE = {
-    "source_sha256": "5c95dc1cabb9f2fb8df0364bcf44160309d7584c11f55bd60bd2680c80dcf8c8",
+    "source_sha256": "c0de04df62a6634c70e2f0a71c2c1e90a2d1e6c25c1ad85e7b2bd6f80494e142",
     "flop_per_quote": 314.1,
     "executed_flop_per_quote": 316.0,
     "valu_per_quote": 555.8,
