@@ -350,8 +350,8 @@ __host__ __device__ __attribute__((always_inline)) inline bool halley_solve_scal
   st->s = s;
   st->converged = done && s > 0.0f;
   // ln 2^-100 = -69.3.  The upper branch holds small prices only at the money,
-  // where beta is bh to within 1e-4.
-  return q.lower ? fmaf(-0.5f, q.ax, q.lv) >= -69.0f : q.bh >= 0x1p-99f;  // ln 2^-100 = -69.3
+  // where beta is bh to within 1e-4; below it bh is the larger of the two.
+  return fv::all(!q.lower || fmaf(-0.5f, q.ax, q.lv) >= -69.0f, q.bh >= 0x1p-99f);
 }
 
 // Geometric bisection on s inside [lo, hi] to rel_tol (midpoints as
