@@ -41,7 +41,7 @@ if ROOT not in sys.path:
 # The traffic figure is reported only while the kernel sources still hash to
 # ``source_sha256``; the FLOP figure is the algorithmic count of that source.
 LBR_PROFILE = {
-    "source_sha256": "c0de04df62a6634c70e2f0a71c2c1e90a2d1e6c25c1ad85e7b2bd6f80494e142",
+    "source_sha256": "3a89d62c495e8c3c8168814066d7ce0665433750697722c24a0935a56956b697",
     "flop_per_quote": 314.1,
     "executed_flop_per_quote": 316.0,
     "valu_per_quote": 555.8,
